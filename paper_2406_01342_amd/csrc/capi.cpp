@@ -126,7 +126,7 @@ pc_status pc_plan_get_info(const pc_plan* p, pc_plan_info* info) {
     info->band_nu = p->g.nu;
     info->band_v0 = p->g.v0;
     info->band_nv = p->g.nv;
-    info->wraps = p->g.wrap;
+    info->wraps = p->wraps;
     info->tile = kTile;
     info->n_tiles = (int64_t)p->g.ntu * p->g.ntv;
     info->n_chunks = p->n_chunks;
@@ -301,14 +301,17 @@ static RowMask upload_rows(pc_plan* p, const uint32_t* row_mask, hipStream_t s) 
   PC_REQUIRE(row_mask != nullptr, "row_mask is NULL");
   const int n = p->g.n, words = (n + 31) / 32;
   int64_t count = 0;
+  std::vector<uint32_t> up((size_t)kMaxRowWords + words);  // the mask, then its row pairs
   for (int w = 0; w < words; ++w) {
     const uint32_t m = row_mask[w];
     if (w == words - 1 && n % 32) PC_REQUIRE((m >> (n % 32)) == 0, "row_mask has bits past npix");
     count += __builtin_popcount(m);
+    up[w] = m;
+    up[kMaxRowWords + w] = m | ((m & 0x55555555u) << 1) | ((m >> 1) & 0x55555555u);
   }
-  PC_HIP(hipMemcpyAsync(p->rowmask, row_mask, (size_t)words * 4, hipMemcpyHostToDevice, s));
-  PC_HIP(hipStreamSynchronize(s));  // the caller's array may go away on return
-  return RowMask{p->rowmask, count};
+  PC_HIP(hipMemcpyAsync(p->rowmask, up.data(), up.size() * 4, hipMemcpyHostToDevice, s));
+  PC_HIP(hipStreamSynchronize(s));  // the staging above goes out of scope
+  return RowMask{p->rowmask, count, p->rowmask + kMaxRowWords};
 }
 
 pc_status pc_forward_grid_rows(pc_plan* p, const float* image, const uint32_t* row_mask,

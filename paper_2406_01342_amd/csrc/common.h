@@ -122,9 +122,21 @@ struct GridGeom {
   int32_t u0, nu;  // band origin / extent along u (cells, multiple of kTile)
   int32_t v0, nv;  // band along v
   int32_t ntu, ntv;
-  int32_t wrap;
+  // wrap: the band is the whole periodic grid along u, wrapv: along v.
+  // Coplanar plans hold the half plane v >= 0 only: the image is real, and
+  // Re(h e^{+i t}) = Re(h* e^{-i t}), so a visibility with v < 0 is gridded as
+  // its conjugate at (-u, -v) (kFlip in its cell).  Their band runs from
+  // about M/2 (zero frequency) up to at most M + W/2 and never wraps along v
+  // (cells at M and past it alias cells 0 ... of the periodic transform).
+  int32_t wrap, wrapv;
   double dl;       // pixel step (direction cosine)
 };
+
+// A visibility's packed first cell: u in bits 0-15, v in bits 16-30, and
+// whether the visibility is gridded as its conjugate.
+constexpr uint32_t kFlip = 0x80000000u;
+__host__ __device__ constexpr int cell_u(uint32_t c) { return (int)(c & 0xffffu); }
+__host__ __device__ constexpr int cell_v(uint32_t c) { return (int)((c & ~kFlip) >> 16); }
 
 struct DeviceBuf {
   void* ptr = nullptr;
@@ -222,6 +234,7 @@ struct pc_plan {
   int64_t L = 0;
   pc::GridGeom g{};
   int64_t n_chunks = 0, n_partials = 0, n_fold = 0, n_interp = 0;
+  int wraps = 0;              // footprints cross the periodic grid's edge
   bool spread_quads = false;  // work items grouped by workgroup (FP32, kernel width <= 8)
   size_t footprint = 0;
 
@@ -229,7 +242,7 @@ struct pc_plan {
   int32_t* perm = nullptr;      // sorted index -> caller index
   double* AB = nullptr;         // [2L] (u dl, v dl) turns per pixel, FP64
   double* Cw = nullptr;         // [L] w in wavelengths (NULL: coplanar plan)
-  uint32_t* cell = nullptr;     // [L] packed first cell (v << 16 | u), absolute
+  uint32_t* cell = nullptr;     // [L] packed first cell, absolute (cell_u, cell_v, kFlip)
   void* off = nullptr;          // [2L] float or double: (s_u, s_v) offsets
   // Spreading work list.
   pc::SpreadChunk* chunks = nullptr;
@@ -245,7 +258,7 @@ struct pc_plan {
   void* corr = nullptr;         // real [n]: (-1)^a / psi(a), a = i - n/2
   // Small scratch.
   unsigned long long* maxkey = nullptr;  // packed (|x| bits, ~index)
-  uint32_t* rowmask = nullptr;  // a caller's row mask (after the max key)
+  uint32_t* rowmask = nullptr;  // a caller's row mask and its row pairs (after the max key)
   int max_positive = 0;  // the key holds max(x, 0) in place of |x| (positivity-constrained solve)
   void* vis_scratch = nullptr;  // complex [L] in plan order (residual etc.)
   pc::WStack ws;                // w-stacking planes (nplanes 0: coplanar)
@@ -341,9 +354,14 @@ void dict_gather(pc_plan* p, const DictSpec& D, int64_t nS, const int32_t* atoms
 // the forward, rows whose bit is clear must be zero and are not read; for
 // the adjoint, only the rows set are computed (the others are left as they
 // were, and no maximum is formed).
+// pair_bits: the rows whose pass-A columns are formed.  Pass B transforms
+// rows 2k and 2k + 1 together (a pair of real rows is one complex sequence),
+// so its masks hold both rows of every pair with a row set; the operators that
+// evaluate pass B directly need no more than the rows set.
 struct RowMask {
   const uint32_t* bits;
   int64_t count;
+  const uint32_t* pair_bits;
 };
 constexpr int kMaxRowWords = 8192 / 32;  // npix <= 8192
 template <typename R>

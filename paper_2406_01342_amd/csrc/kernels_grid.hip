@@ -99,10 +99,10 @@ __device__ __forceinline__ int block_key(int bu, int bv) { return ((bv + 64) << 
 constexpr int kNoBlock = -1;
 
 // Adds a run's per-cell register sums into the LDS tile and clears them.
-// single: the periodic grid is one tile wide, so window cells left of (or
-// above) the tile wrap onto its other end.
+// single_u, single_v: the periodic grid is one tile wide along that axis, so
+// window cells left of (above) the tile wrap onto its other end.
 template <typename R, int W>
-__device__ __forceinline__ void spread_flush(int lane, int key, bool single, int M,
+__device__ __forceinline__ void spread_flush(int lane, int key, bool single_u, bool single_v,
                                              R (&accr)[SpreadCfg<R, W>::NPASS],
                                              R (&acci)[SpreadCfg<R, W>::NPASS], R* tre,
                                              R* tim) {
@@ -114,10 +114,8 @@ __device__ __forceinline__ void spread_flush(int lane, int key, bool single, int
       const int tap = lane + 64 * ps;
       const int a = tap / C::BS, b = tap - (tap / C::BS) * C::BS;
       int y = bv + a, x = bu + b;
-      if (single) {
-        y &= kTile - 1;
-        x &= kTile - 1;
-      }
+      if (single_v) y &= kTile - 1;
+      if (single_u) x &= kTile - 1;
       if ((C::BS * C::BS % 64 == 0 || tap < C::BS * C::BS) && (unsigned)y < (unsigned)kTile &&
           (unsigned)x < (unsigned)kTile) {
         tre[y * C::S + x] += accr[ps];
@@ -175,7 +173,7 @@ __device__ __forceinline__ void spread_body(
   R* stg = tim + C::TILE;  // [64][REC]
   const int tv = ch.tile / g.ntu, tu = ch.tile - tv * g.ntu;
   const int ov = g.v0 + tv * kTile, ou = g.u0 + tu * kTile;
-  const bool single = g.wrap && g.M == kTile;
+  const bool single_u = g.wrap && g.M == kTile, single_v = g.wrapv && g.M == kTile;
   const R inv = R(2) / R(W);
   const R beta = sizeof(R) == 4 ? (R)g.beta : (R)g.beta64;
   // cumulative range boundaries
@@ -214,10 +212,10 @@ __device__ __forceinline__ void spread_body(
     const int q = base + lane;
     R* my = stg + lane * C::REC;
     if (q < total) {
-      const int cu = (int)(nx.cell & 0xffffu), cv = (int)(nx.cell >> 16);
+      const int cu = cell_u(nx.cell), cv = cell_v(nx.cell);
       const int du = cu % C::RB, dv = cv % C::RB;
       const int bu = tile_base(cu - du, ou, g.M, C::BS, g.wrap);
-      const int bv = tile_base(cv - dv, ov, g.M, C::BS, g.wrap);
+      const int bv = tile_base(cv - dv, ov, g.M, C::BS, g.wrapv);
       // the W taps of each axis land at window positions d .. d + W - 1
       // (d = dv or du < RB); the other BS - W positions are zero
 #pragma unroll
@@ -228,7 +226,7 @@ __device__ __forceinline__ void spread_body(
         my[C::BS + du + t] = es_kernel<R>((nx.su + R(t)) * inv, beta);
       }
       my[2 * C::BS] = nx.val.x;
-      my[2 * C::BS + 1] = nx.val.y;
+      my[2 * C::BS + 1] = nx.cell & kFlip ? -nx.val.y : nx.val.y;
       *reinterpret_cast<int*>(&my[2 * C::BS + 2]) = block_key(bu, bv);  // in the R-sized slot
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -257,7 +255,7 @@ __device__ __forceinline__ void spread_body(
         if (v0 + u < nb) {
           const int k = __builtin_amdgcn_readfirstlane(key[u]);
           if (k != ckey) {  // same for every lane of the wave
-            spread_flush<R, W>(lane, ckey, single, g.M, accr, acci, tre, tim);
+            spread_flush<R, W>(lane, ckey, single_u, single_v, accr, acci, tre, tim);
             ckey = k;
           }
 #pragma unroll
@@ -272,7 +270,7 @@ __device__ __forceinline__ void spread_body(
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
-  spread_flush<R, W>(lane, ckey, single, g.M, accr, acci, tre, tim);
+  spread_flush<R, W>(lane, ckey, single_u, single_v, accr, acci, tre, tim);
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -354,7 +352,7 @@ __device__ __forceinline__ void spread_group_accumulate(
   const int a = lane >> 3, b = lane & 7;
   const int tv = ch.tile / g.ntu, tu = ch.tile - tv * g.ntu;
   const int ov = g.v0 + tv * kTile, ou = g.u0 + tu * kTile;
-  const bool single = g.wrap && g.M == kTile;
+  const bool single_u = g.wrap && g.M == kTile, single_v = g.wrapv && g.M == kTile;
   constexpr float R = 0.5f * (float)W;
   const float c0 = g.beta * 1.44269504088896341f;  // beta log2(e)
   const float c1 = c0 / R;
@@ -406,10 +404,8 @@ __device__ __forceinline__ void spread_group_accumulate(
   auto flush = [&]() {
     if (ckey != kNoBlock) {
       int y = ((ckey >> 8) - 64) + a, x = ((ckey & 0xff) - 64) + b;
-      if (single) {
-        y &= kTile - 1;
-        x &= kTile - 1;
-      }
+      if (single_v) y &= kTile - 1;
+      if (single_u) x &= kTile - 1;
       if ((unsigned)y < (unsigned)kTile && (unsigned)x < (unsigned)kTile) {
         float2* cp = reinterpret_cast<float2*>(tile) + y * C::S + x;
         float2 o = *cp;
@@ -429,13 +425,13 @@ __device__ __forceinline__ void spread_group_accumulate(
     int key = kNoBlock, du = 0, dv = 0;
     float fy[W], fx[W], vr = 0.f, vi = 0.f;
     if (valid) {
-      const int cu = (int)(rk.cell & 0xffffu), cv = (int)(rk.cell >> 16);
+      const int cu = cell_u(rk.cell), cv = cell_v(rk.cell);
       du = cu % C::RB;
       dv = cv % C::RB;
       key = block_key(tile_base(cu - du, ou, g.M, C::BS, g.wrap),
-                      tile_base(cv - dv, ov, g.M, C::BS, g.wrap));
+                      tile_base(cv - dv, ov, g.M, C::BS, g.wrapv));
       vr = rk.val.x;
-      vi = rk.val.y;
+      vi = __uint_as_float(__float_as_uint(rk.val.y) ^ (rk.cell & kFlip));  // conjugate if flipped
       // tap t lies x = s + t cells from the visibility, s in (-R, -R + 1],
       // so |x| <= R (z = x / R in (-1, 1])
 #pragma unroll
@@ -946,9 +942,6 @@ __device__ __forceinline__ unsigned long long max_key(float a, int idx) {
   return ((unsigned long long)__float_as_uint(a) << 32) | (unsigned long long)(0xffffffffu - (unsigned)idx);
 }
 
-// Pass B of the adjoint: NB image rows i; FFT along v of H[:, i]; correction;
-// write image rows; fused max |eta| (max(eta, 0) with ``positive``, the
-// positivity-constrained solve) with lowest-index ties.
 // One w-plane of the w-stacked adjoint: its position, the phase reference
 // c_mid, and whether it is the first plane (which writes instead of adding).
 struct WPlane {
@@ -956,29 +949,20 @@ struct WPlane {
   int first;
 };
 
-template <typename R, int M, int NB, int NT, bool WACC = false>
-__device__ __forceinline__ void passB_adj_body(const GridGeom& g, const cpx<R>* __restrict__ H,
-                                               R* __restrict__ image,
-                                               const cpx<R>* __restrict__ tw,
-                                               const R* __restrict__ corr, R scale,
-                                               unsigned long long* __restrict__ maxkey,
-                                               int positive, int iblock,
-                                               WPlane wp = WPlane{0.0, 0.0, 1},
-                                               const uint32_t* __restrict__ rows = nullptr) {
+// Pass B of a w-plane: NB image rows i; FFT along v of H[:, i] (the whole
+// plane: the rotation makes the transform's outputs complex), correction,
+// rotation by the plane's phase, and the real part added into the image rows.
+template <typename R, int M, int NB, int NT>
+__device__ __forceinline__ void passB_adj_w_body(const GridGeom& g, const cpx<R>* __restrict__ H,
+                                                 R* __restrict__ image,
+                                                 const cpx<R>* __restrict__ tw,
+                                                 const R* __restrict__ corr, R scale, int iblock,
+                                                 WPlane wp) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   cpx<R>* buf = reinterpret_cast<cpx<R>*>(smem_raw);
   __shared__ cpx<R> tws[tw_count(M)];
   constexpr int n = M / 2;
   const int i0 = iblock * NB;
-  // with a row mask: workgroups without a row set return at once, the others
-  // store only their rows that are set
-  unsigned rowbits = (1u << NB) - 1u;
-  if (rows) {
-    rowbits = 0;
-#pragma unroll
-    for (int b = 0; b < NB; ++b) rowbits |= (unsigned)row_set(rows, i0 + b) << b;
-    if (rowbits == 0) return;  // the whole workgroup
-  }
   load_twiddles<R, M, NT>(tws, tw);
   // element (m, b): band row m - v0 of column i0 + b of the pass-A buffer,
   // whose KHB-wide column blocks are row-major over the band rows
@@ -1042,39 +1026,23 @@ __device__ __forceinline__ void passB_adj_body(const GridGeom& g, const cpx<R>* 
     }
   }
   __syncthreads();
-  unsigned long long best = 0;
   const R dl = (R)g.dl;
   // pixel (i, j) from frequency f = j - n/2 (mod M) of column i, stored from
-  // the last stage's registers with the correction and the max key
+  // the last stage's registers: Re(exp(2 pi i w_j c') v), c' = n - 1 - c_mid,
+  // phase in FP64
   auto keep = [](int, int f) { return 4 * f < M || 4 * f >= 3 * M; };
   auto store = [&](int bb, int f, cpx<R> v) {
-    if (!((rowbits >> bb) & 1u)) return;
     const int i = i0 + bb;
     const int j = f < n / 2 ? f + n / 2 : f - M + n / 2;
     const R l = (R)(i - n / 2) * dl, mm = (R)(j - n / 2) * dl;
-    R inv_n;
-    if constexpr (sizeof(R) == 4) {
-      inv_n = __builtin_amdgcn_rsqf(R(1) - l * l - mm * mm);
-    } else {
-      inv_n = R(1) / sqrt(R(1) - l * l - mm * mm);
-    }
-    if constexpr (WACC) {
-      // Re(exp(2 pi i w_j c') v), c' = n - 1 - c_mid, phase in FP64
-      double th = wp.wj * (n_minus_one((double)(i - n / 2) * g.dl, (double)(j - n / 2) * g.dl) -
-                           wp.cmid);
-      th -= rint(th);
-      const R sn = (R)__builtin_amdgcn_sinf((float)th), cs = (R)__builtin_amdgcn_cosf((float)th);
-      const R val = (v.x * cs - v.y * sn) * (corr[i] * scale) * corr[j] * inv_n;
-      R* dst = image + (size_t)i * n + j;
-      *dst = wp.first ? val : *dst + val;
-      return;
-    }
-    const R val = v.x * (corr[i] * scale) * corr[j] * inv_n;
-    image[(size_t)i * n + j] = val;
-    // positive part: +0 for every val <= 0 (never -0, whose bits would win)
-    const float kv = positive ? (val > R(0) ? (float)val : 0.0f) : (float)fabs(val);
-    const unsigned long long key = max_key(kv, i * n + j);
-    best = key > best ? key : best;
+    const R inv_n = __builtin_amdgcn_rsqf(R(1) - l * l - mm * mm);
+    double th = wp.wj * (n_minus_one((double)(i - n / 2) * g.dl, (double)(j - n / 2) * g.dl) -
+                         wp.cmid);
+    th -= rint(th);
+    const R sn = (R)__builtin_amdgcn_sinf((float)th), cs = (R)__builtin_amdgcn_cosf((float)th);
+    const R val = (v.x * cs - v.y * sn) * (corr[i] * scale) * corr[j] * inv_n;
+    R* dst = image + (size_t)i * n + j;
+    *dst = wp.first ? val : *dst + val;
   };
   if constexpr (RAD0 <= 4) {
     if (pruned)
@@ -1084,7 +1052,216 @@ __device__ __forceinline__ void passB_adj_body(const GridGeom& g, const cpx<R>* 
   } else {
     lds_fft_store<R, M, NB, NT, +1>(buf, tws, keep, store);
   }
-  if constexpr (WACC) return;  // the maximum comes after the last plane
+}
+
+// Two adjacent columns of the pass-A buffer at one band row.
+template <typename R>
+struct alignas(4 * sizeof(R)) cpair {
+  cpx<R> a, b;
+};
+
+// The half plane's Hermitian completion.  Coplanar plans hold the band rows
+// v >= 0 (and the kernel's reach below), H_i(c) for cells c = v0 + rel; image
+// row i is Re sum_c H_i(c) e^{2 pi i c f / M} = 1/2 sum_m z_i(m) e^{...} with
+// z_i(m) = H_i(m) + conj H_i(-m) (cells mod M), whose transform is real.  Two
+// image rows 2k and 2k + 1 are therefore the real and imaginary parts of ONE
+// complex transform, of z_2k + i z_2k+1: half the transforms, and half the
+// rows of pass A and of the pass-A buffer, of a full-plane grid.
+//
+// z of a pair at slot c in [0, M).  Away from the half plane's edges exactly
+// one of the four cells c, c + M, M - c, 2M - c lies in the band: pair_main
+// names it (rel, and whether its conjugate enters), pair_rest adds the others
+// (called for the few slots where pair_edge says so).
+struct PairGeom {
+  int M, v0, nv;
+};
+__device__ __forceinline__ int pair_main(const PairGeom& q, int c, bool& conj, bool& ok) {
+  conj = 2 * c < q.M;
+  const int rel = (conj ? q.M - c : c) - q.v0;
+  ok = rel < q.nv;  // (rel >= 0: the band starts at or before M/2)
+  return rel;
+}
+__device__ __forceinline__ bool pair_edge(const PairGeom& q, int c) {
+  const int k = c - q.M / 2;
+  return (k < 0 ? -k : k) <= q.M / 2 - q.v0 || c + q.M - q.v0 < q.nv || 2 * q.M - c - q.v0 < q.nv;
+}
+// H_a + i H_b, or conj H_a + i conj H_b
+template <typename R>
+__device__ __forceinline__ cpx<R> pair_z(const cpair<R>& h, bool conj) {
+  return conj ? cpx<R>{h.a.x + h.b.y, h.b.x - h.a.y} : cpx<R>{h.a.x - h.b.y, h.a.y + h.b.x};
+}
+template <typename R, typename Load>
+__device__ __forceinline__ cpx<R> pair_rest(const PairGeom& q, int c, Load load) {
+  cpx<R> z{R(0), R(0)};
+  auto add = [&](int rel, bool conj) {
+    if ((unsigned)rel < (unsigned)q.nv) {
+      const cpx<R> t = pair_z<R>(load(rel), conj);
+      z = {z.x + t.x, z.y + t.y};
+    }
+  };
+  if (2 * c < q.M)
+    add(c - q.v0, false);
+  else
+    add(q.M - c - q.v0, true);
+  add(c + q.M - q.v0, false);
+  add(2 * q.M - c - q.v0, true);
+  return z;
+}
+
+// Pass B of the adjoint (coplanar plans): NB pairs of image rows; FFT along v
+// of each pair's completed column; correction; both image rows written; fused
+// max |eta| (max(eta, 0) with ``positive``, the positivity-constrained solve)
+// with lowest-index ties.
+template <typename R, int M, int NB, int NT>
+__device__ __forceinline__ void passB_adj_body(const GridGeom& g, const cpx<R>* __restrict__ H,
+                                               R* __restrict__ image,
+                                               const cpx<R>* __restrict__ tw,
+                                               const R* __restrict__ corr, R scale,
+                                               unsigned long long* __restrict__ maxkey,
+                                               int positive, int iblock,
+                                               const uint32_t* __restrict__ rows = nullptr) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  cpx<R>* buf = reinterpret_cast<cpx<R>*>(smem_raw);
+  __shared__ cpx<R> tws[tw_count(M)];
+  constexpr int n = M / 2;
+  const int i0 = iblock * NB * 2;
+  // with a row mask: workgroups without a row set return at once, the others
+  // store only their rows that are set
+  static_assert(NB <= 8, "row bits");
+  unsigned rowbits = (1u << (2 * NB)) - 1u;
+  if (rows) {
+    rowbits = 0;
+#pragma unroll
+    for (int b = 0; b < 2 * NB; ++b) rowbits |= (unsigned)row_set(rows, i0 + b) << b;
+    if (rowbits == 0) return;  // the whole workgroup
+  }
+  load_twiddles<R, M, NT>(tws, tw);
+  // slot m of pair b, whose KHB-wide column blocks are row-major over the
+  // band rows
+  static_assert((NB & (NB - 1)) == 0 && NT % NB == 0, "pass-B layout");
+  constexpr int IT = (NB * M + NT - 1) / NT;
+  constexpr int MSTEP = NT / NB;  // a thread's m advances by this per element
+  const int b = (int)threadIdx.x & (NB - 1), m0 = (int)threadIdx.x / NB;
+  const int col = i0 + 2 * b;
+  constexpr int KHB = khb_for<M>();
+  const cpx<R>* hcol = H + (size_t)(col / KHB) * g.nv * KHB + (col % KHB);
+  auto load = [&](int rel) {
+    return *reinterpret_cast<const cpair<R>*>(hcol + (size_t)rel * KHB);
+  };
+  const PairGeom q{M, g.v0, g.nv};
+  // Input pruning: the completed column occupies the slots within E of M/2;
+  // with a first radix of 2 or 4 and those no more than M / radix, each
+  // first-stage butterfly (inputs j + r M / radix) holds at most one, so the
+  // stage is applied while loading: output s of butterfly j is that value
+  // rotated by r s quarter (or half) turns, exactly what the full stage
+  // computes.  The remaining stages follow as usual.
+  constexpr int RAD0 = first_radix(M);
+  constexpr int NBF0 = M / RAD0;
+  const int E = g.v0 + g.nv - 1 - M / 2 > M / 2 - g.v0 ? g.v0 + g.nv - 1 - M / 2 : M / 2 - g.v0;
+  bool pruned = false;
+  if constexpr (RAD0 <= 4) {
+    if (2 * E + 1 <= NBF0) {  // uniform
+      pruned = true;
+      constexpr int ITJ = (NBF0 + MSTEP - 1) / MSTEP;
+      cpair<R> t[ITJ];
+      int cc[ITJ];  // the slot, or -1
+      auto slot = [&](int j) {
+        const int d = M / 2 - E - j;
+        const int r = d > 0 ? (d + NBF0 - 1) / NBF0 : 0;  // first input in the support
+        return (j < NBF0 && r < RAD0 && j + r * NBF0 <= M / 2 + E) ? j + r * NBF0 : -1;
+      };
+#pragma unroll
+      for (int it = 0; it < ITJ; ++it) {
+        const int c = slot(m0 + it * MSTEP);
+        bool conj, ok;
+        const int rel = pair_main(q, c < 0 ? 0 : c, conj, ok);
+        ok = ok && c >= 0;
+        t[it] = load(ok ? rel : 0);
+        cc[it] = ok ? c : -1;
+      }
+#pragma unroll
+      for (int it = 0; it < ITJ; ++it) {
+        const int j = m0 + it * MSTEP;
+        if (NBF0 % MSTEP == 0 || j < NBF0) {
+          cpx<R> z{R(0), R(0)};
+          if (cc[it] >= 0) {
+            z = pair_z<R>(t[it], 2 * cc[it] < M);
+            if (pair_edge(q, cc[it])) {
+              const cpx<R> e = pair_rest<R>(q, cc[it], load);
+              z = {z.x + e.x, z.y + e.y};
+            }
+          }
+          const int r = cc[it] >= 0 ? cc[it] / NBF0 : 0;
+#pragma unroll
+          for (int s = 0; s < RAD0; ++s)
+            buf[pidx(b * M + j * RAD0 + s)] = turns_pos<R, RAD0>(z, r * s);
+        }
+      }
+    }
+  }
+  if (!pruned) {
+    cpair<R> t[IT];
+    bool ok[IT];
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      const int m = m0 + it * MSTEP;
+      bool conj;
+      const int rel = pair_main(q, m < M ? m : 0, conj, ok[it]);
+      ok[it] = ok[it] && m < M;
+      t[it] = load(ok[it] ? rel : 0);
+    }
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      const int m = m0 + it * MSTEP;
+      if ((NB * M) % NT == 0 || m < M) {
+        cpx<R> z{R(0), R(0)};
+        if (ok[it]) z = pair_z<R>(t[it], 2 * m < M);
+        if (pair_edge(q, m)) {
+          const cpx<R> e = pair_rest<R>(q, m, load);
+          z = {z.x + e.x, z.y + e.y};
+        }
+        buf[pidx(b * M + m)] = z;
+      }
+    }
+  }
+  __syncthreads();
+  unsigned long long best = 0;
+  const R dl = (R)g.dl;
+  // pixels (i, j) and (i + 1, j) from frequency f = j - n/2 (mod M) of the
+  // pair, stored from the last stage's registers with the correction (and the
+  // completion's 1/2) and the max key
+  auto keep = [](int, int f) { return 4 * f < M || 4 * f >= 3 * M; };
+  auto store = [&](int bb, int f, cpx<R> v) {
+    const int j = f < n / 2 ? f + n / 2 : f - M + n / 2;
+    const R mm = (R)(j - n / 2) * dl;
+    const R cj = corr[j];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      if (!((rowbits >> (2 * bb + h)) & 1u)) continue;
+      const int i = i0 + 2 * bb + h;
+      const R l = (R)(i - n / 2) * dl;
+      R inv_n;
+      if constexpr (sizeof(R) == 4) {
+        inv_n = __builtin_amdgcn_rsqf(R(1) - l * l - mm * mm);
+      } else {
+        inv_n = R(1) / sqrt(R(1) - l * l - mm * mm);
+      }
+      const R val = (h ? v.y : v.x) * (corr[i] * (R(0.5) * scale)) * cj * inv_n;
+      image[(size_t)i * n + j] = val;
+      // positive part: +0 for every val <= 0 (never -0, whose bits would win)
+      const float kv = positive ? (val > R(0) ? (float)val : 0.0f) : (float)fabs(val);
+      const unsigned long long key = max_key(kv, i * n + j);
+      best = key > best ? key : best;
+    }
+  };
+  if constexpr (RAD0 <= 4) {
+    if (pruned)
+      lds_fft_store<R, M, NB, NT, +1, RAD0>(buf, tws, keep, store);
+    else
+      lds_fft_store<R, M, NB, NT, +1>(buf, tws, keep, store);
+  } else {
+    lds_fft_store<R, M, NB, NT, +1>(buf, tws, keep, store);
+  }
   // block max
   for (int o = 32; o > 0; o >>= 1) {
     unsigned long long other = __shfl_xor(best, o, 64);
@@ -1110,7 +1287,7 @@ __global__ __launch_bounds__(NT) void passB_adj_kernel(GridGeom g, const cpx<R>*
                                                         int positive,
                                                         const uint32_t* __restrict__ rows) {
   passB_adj_body<R, M, NB, NT>(g, H, image, tw, corr, scale, maxkey, positive,
-                               xcd_local(blockIdx.x, gridDim.x), WPlane{0.0, 0.0, 1}, rows);
+                               xcd_local(blockIdx.x, gridDim.x), rows);
 }
 
 template <typename R, int M, int NB, int NT>
@@ -1119,8 +1296,8 @@ __global__ __launch_bounds__(NT) void passB_adj_w_kernel(GridGeom g, const cpx<R
                                                           const cpx<R>* __restrict__ tw,
                                                           const R* __restrict__ corr, R scale,
                                                           WPlane wp) {
-  passB_adj_body<R, M, NB, NT, true>(g, H, image, tw, corr, scale, nullptr, 0,
-                                     xcd_local(blockIdx.x, gridDim.x), wp);
+  passB_adj_w_body<R, M, NB, NT>(g, H, image, tw, corr, scale,
+                                 xcd_local(blockIdx.x, gridDim.x), wp);
 }
 
 // Visibility weights of w-plane w_j (plan order): h_k exp(2 pi i w_k c_mid)
@@ -1206,7 +1383,7 @@ __global__ __launch_bounds__(NT) void passB_batch_kernel(const AdjJob* __restric
   const int2 it = items[xcd_local(blockIdx.x, gridDim.x)];
   const AdjJob& J = jobs[it.x];
   passB_adj_body<float, M, NB, NT>(J.g, J.H, J.image, J.tw, J.corr, J.scale, J.maxkey,
-                                   J.positive, it.y, WPlane{0.0, 0.0, 1}, J.rows);
+                                   J.positive, it.y, J.rows);
 }
 
 // First stage of a forward transform whose input is the n = M/2 central
@@ -1274,10 +1451,13 @@ __device__ __forceinline__ void central_first_stage(cpx<R>* buf, Load load) {
   }
 }
 
-// Forward pass B^T: NB image rows i, pre-correct, FFT along v (sign -1),
-// keep the band rows: H[v_rel][i] (the pass-A layout).  The first stage is
-// applied while loading (the row's n pixels are the central frequencies) and
-// the band rows are stored from the last stage's registers.
+// Forward pass B^T: NB pairs of image rows, pre-correct, FFT along v (sign
+// -1), keep the band rows: H[v_rel][i] (the pass-A layout).  The rows 2k and
+// 2k + 1 of the real image are the real and imaginary parts of one sequence
+// (see pair_main); its transform Z is taken apart as H_2k(c) =
+// (Z(c) + conj Z(-c)) / 2 and H_2k+1(c) = (Z(c) - conj Z(-c)) / 2i at the band
+// cells c.  The first stage is applied while loading (a row's n pixels are
+// the central frequencies).
 template <typename R, int M, int NB, int NT>
 __device__ __forceinline__ void passB_fwd_body(const GridGeom& g, const R* __restrict__ image,
                                                cpx<R>* __restrict__ H,
@@ -1288,29 +1468,42 @@ __device__ __forceinline__ void passB_fwd_body(const GridGeom& g, const R* __res
   cpx<R>* buf = reinterpret_cast<cpx<R>*>(smem_raw);
   __shared__ cpx<R> tws[tw_count(M)];
   constexpr int n = M / 2;
-  const int i0 = iblock * NB;
+  const int i0 = iblock * NB * 2;
   // with a row mask, workgroups of zero rows write nothing (pass A reads
-  // those columns of H as zeros)
-  if (rows && !any_row_set<NB>(rows, i0)) return;
+  // those columns of H as zeros), and the rows cleared are not read
+  if (rows && !any_row_set<2 * NB>(rows, i0)) return;
   load_twiddles<R, M, NT>(tws, tw);
   const R dl = (R)g.dl;
   central_first_stage<R, M, NB, NT, -1>(buf, [&](int b, int j) -> cpx<R> {
-    const int i = i0 + b;
-    const R l = (R)(i - n / 2) * dl, mm = (R)(j - n / 2) * dl;
-    R inv_n;
-    if constexpr (sizeof(R) == 4) {
-      inv_n = __builtin_amdgcn_rsqf(R(1) - l * l - mm * mm);
-    } else {
-      inv_n = R(1) / sqrt(R(1) - l * l - mm * mm);
+    R x[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int i = i0 + 2 * b + h;
+      const R l = (R)(i - n / 2) * dl, mm = (R)(j - n / 2) * dl;
+      R inv_n;
+      if constexpr (sizeof(R) == 4) {
+        inv_n = __builtin_amdgcn_rsqf(R(1) - l * l - mm * mm);
+      } else {
+        inv_n = R(1) / sqrt(R(1) - l * l - mm * mm);
+      }
+      x[h] = (!rows || row_set(rows, i)) ? image[(size_t)i * n + j] * corr[i] * corr[j] * inv_n
+                                         : R(0);
     }
-    return {image[(size_t)i * n + j] * corr[i] * corr[j] * inv_n, R(0)};
+    return {x[0], x[1]};
   });
   __syncthreads();
+  fft_stages<R, M, NB, NT, -1, first_radix(M)>(buf, tws);  // ends with a barrier
   constexpr int KHB = khb_for<M>();
   const int v0 = g.v0, nv = g.nv;
-  auto keep = [&](int, int f) { return (unsigned)(f - v0) < (unsigned)nv; };
-  auto store = [&](int b, int f, cpx<R> v) { H[h_index<KHB>(f - v0, i0 + b, nv)] = v; };
-  lds_fft_store<R, M, NB, NT, -1, first_radix(M)>(buf, tws, keep, store);
+  for (int e = (int)threadIdx.x; e < NB * nv; e += NT) {
+    const int b = e & (NB - 1), rel = e / NB;
+    const int c = v0 + rel;
+    const cpx<R> z = buf[pidx(b * M + (c & (M - 1)))];
+    const cpx<R> w = buf[pidx(b * M + ((M - c) & (M - 1)))];
+    *reinterpret_cast<cpair<R>*>(H + h_index<KHB>(rel, i0 + 2 * b, nv)) =
+        cpair<R>{{R(0.5) * (z.x + w.x), R(0.5) * (z.y - w.y)},
+                 {R(0.5) * (z.y + w.y), R(0.5) * (w.x - z.x)}};
+  }
 }
 
 template <typename R, int M, int NB, int NT, bool MASKED>
@@ -1367,7 +1560,7 @@ __global__ __launch_bounds__(256) void interp_kernel(GridGeom g, int64_t L,
   const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (s >= L) return;
   const uint32_t c = cell[s];
-  const int cu = (int)(c & 0xffffu), cv = (int)(c >> 16);
+  const int cu = cell_u(c), cv = cell_v(c);
   const R su = off[2 * s], sv = off[2 * s + 1];
   const R inv = R(2) / R(W);
   const R beta = sizeof(R) == 4 ? (R)g.beta : (R)g.beta64;
@@ -1381,7 +1574,7 @@ __global__ __launch_bounds__(256) void interp_kernel(GridGeom g, int64_t L,
   for (int a = 0; a < W; ++a) {
     const R kva = es_kernel<R>((sv + R(a)) * inv, beta);
     int y = cv + a - g.v0;
-    if (g.wrap && y >= g.M) y -= g.M;
+    if (g.wrapv && y >= g.M) y -= g.M;
     R rx = 0, ry = 0;
 #pragma unroll
     for (int b = 0; b < W; ++b) {
@@ -1395,7 +1588,7 @@ __global__ __launch_bounds__(256) void interp_kernel(GridGeom g, int64_t L,
     ay += ry * kva;
   }
   const int64_t d = perm ? perm[s] : s;
-  out[d] = {ax, ay};
+  out[d] = {ax, c & kFlip ? -ay : ay};
 }
 
 // Interpolation from LDS (FP32, kernel widths up to 16): one workgroup of
@@ -1437,10 +1630,8 @@ __global__ __launch_bounds__(kInterpThreads) void interp_lds_kernel(GridGeom g,
     const int y = e / C::S, x = e - y * C::S;
     int rv = rv0 + y, ru = ru0 + x;
     float2 v = make_float2(0.f, 0.f);
-    if (g.wrap) {
-      if (rv >= g.M) rv -= g.M;
-      if (ru >= g.M) ru -= g.M;
-    }
+    if (g.wrapv && rv >= g.M) rv -= g.M;
+    if (g.wrap && ru >= g.M) ru -= g.M;
     if (rv < g.nv && ru < g.nu) {
       const c32 c = grid[(size_t)rv * g.nu + ru];
       v = make_float2(c.x, c.y);
@@ -1455,7 +1646,7 @@ __global__ __launch_bounds__(kInterpThreads) void interp_lds_kernel(GridGeom g,
   double r2 = 0.0, vr = 0.0;
   for (int sidx = it.beg + tid; sidx < it.end; sidx += kInterpThreads) {
     const uint32_t c = cell[sidx];
-    const int x = (int)(c & 0xffffu) - ou, y = (int)(c >> 16) - ov;  // in [0, kTile)
+    const int x = cell_u(c) - ou, y = cell_v(c) - ov;  // in [0, kTile)
     const float2 o = reinterpret_cast<const float2*>(off)[sidx];
     float ku[W];
 #pragma unroll
@@ -1475,6 +1666,7 @@ __global__ __launch_bounds__(kInterpThreads) void interp_lds_kernel(GridGeom g,
       ax += rx * kva;
       ay += ry * kva;
     }
+    ay = __uint_as_float(__float_as_uint(ay) ^ (c & kFlip));  // conjugate if flipped
     if (base) {
       const c32 v = base[sidx];
       const c32 r = {v.x - ax, v.y - ay};
@@ -1694,15 +1886,15 @@ static void set_lds(const void* kernel, size_t bytes) {
     PC_HIP(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
 }
 
-// Sequences per pass-B workgroup: about n/256 (so a launch has >= 256
-// workgroups), capped by the LDS budget and at 16.
-template <typename R, int M>
+// Sequences per pass-B workgroup (pairs of image rows; single rows for a
+// w-plane): so many that a launch has >= 256 workgroups, capped by the LDS
+// budget.
+template <typename R, int M, int ROWS = 2>
 constexpr int nb_passB() {
   constexpr int CB = sizeof(cpx<R>);
   constexpr int lim = (M * CB >= Shapes<R>::lds_b) ? 1 : Shapes<R>::lds_b / (M * CB);
-  constexpr int want = (M / 2) / 256 < 1 ? 1 : (M / 2) / 256;
-  constexpr int a = want < lim ? want : lim;
-  return a > 16 ? 16 : a;
+  constexpr int want = (M / 2) / ROWS / 256 < 1 ? 1 : (M / 2) / ROWS / 256;
+  return want < lim ? want : lim;
 }
 
 template <int TOTAL_BUTTERFLIES>
@@ -1725,6 +1917,7 @@ static void run_passes_adj(pc_plan* p, R* image, R scale, hipStream_t s,
   // with a row mask: the H columns and image rows of the rows set (the
   // passes appear under names of their own)
   const uint32_t* bits = rows ? rows->bits : nullptr;
+  const uint32_t* cols = rows ? rows->pair_bits : nullptr;
   const double nr = rows ? (double)rows->count : (double)g.n;
   const double nvr = (double)g.nv * nr * CB;
   {
@@ -1734,7 +1927,7 @@ static void run_passes_adj(pc_plan* p, R* image, R scale, hipStream_t s,
   set_lds((const void*)passA_adj_kernel<R, M, NBA, NTA, MASKED>, lda);                         \
   hipLaunchKernelGGL((passA_adj_kernel<R, M, NBA, NTA, MASKED>), dim3((g.nv + NBA - 1) / NBA), \
                      dim3(NTA), lda, s, g, (const cpx<R>*)p->grid, p->tile_flags,              \
-                     (cpx<R>*)p->H, (const cpx<R>*)p->twiddle, bits)
+                     (cpx<R>*)p->H, (const cpx<R>*)p->twiddle, cols)
     if (rows) {
       PC_PASS_A(true);
     } else {
@@ -1745,20 +1938,26 @@ static void run_passes_adj(pc_plan* p, R* image, R scale, hipStream_t s,
   }
   if (!pass_b) return;  // (the caller evaluates pass B itself)
   if (wp) {  // one w-plane: rotate, add into the image
-    set_lds((const void*)passB_adj_w_kernel<R, M, NBB, NTB>, ldb);
-    ProfScope ps(p, s, "passB_adj_w", nvn + (double)g.n * g.n * sizeof(R) * (wp->first ? 1 : 2),
-                 (double)g.n * M);
-    hipLaunchKernelGGL((passB_adj_w_kernel<R, M, NBB, NTB>), dim3((M / 2) / NBB), dim3(NTB), ldb,
-                       s, g, (const cpx<R>*)p->H, image, (const cpx<R>*)p->twiddle,
-                       (const R*)p->corr, scale, *wp);
-    PC_LAUNCH_CHECK("passB_adj_w");
-    return;
+    if constexpr (sizeof(R) == 4) {
+      constexpr int NBW = nb_passB<R, M, 1>();
+      constexpr int NTW = nt_for<NBW * M / 16>();
+      const size_t ldw = (size_t)padded(NBW * M) * CB;
+      set_lds((const void*)passB_adj_w_kernel<R, M, NBW, NTW>, ldw);
+      ProfScope ps(p, s, "passB_adj_w", nvn + (double)g.n * g.n * sizeof(R) * (wp->first ? 1 : 2),
+                   (double)g.n * M);
+      hipLaunchKernelGGL((passB_adj_w_kernel<R, M, NBW, NTW>), dim3((M / 2) / NBW), dim3(NTW),
+                         ldw, s, g, (const cpx<R>*)p->H, image, (const cpx<R>*)p->twiddle,
+                         (const R*)p->corr, scale, *wp);
+      PC_LAUNCH_CHECK("passB_adj_w");
+      return;
+    }
+    fail(PC_ERR_UNSUPPORTED, "w-planes of an FP64 plan");
   }
   ProfScope ps(p, s, rows ? "passB_adj_rows" : "passB_adj",
                nvr + nr * g.n * sizeof(R), nr * M);
 #define PC_PASS_B(MASKED)                                                                       \
   set_lds((const void*)passB_adj_kernel<R, M, NBB, NTB, MASKED>, ldb);                          \
-  hipLaunchKernelGGL((passB_adj_kernel<R, M, NBB, NTB, MASKED>), dim3((M / 2) / NBB), dim3(NTB), \
+  hipLaunchKernelGGL((passB_adj_kernel<R, M, NBB, NTB, MASKED>), dim3((M / 4) / NBB), dim3(NTB), \
                      ldb, s, g, (const cpx<R>*)p->H, image, (const cpx<R>*)p->twiddle,          \
                      (const R*)p->corr, scale, rows ? nullptr : p->maxkey, p->max_positive, bits)
   if (rows) {
@@ -1781,13 +1980,14 @@ static void run_passes_fwd(pc_plan* p, const R* image, hipStream_t s,
   const GridGeom& g = p->g;
   const size_t lda = (size_t)padded(NBA * M) * CB, ldb = (size_t)padded(NBB * M) * CB;
   const uint32_t* bits = rows ? rows->bits : nullptr;
+  const uint32_t* cols = rows ? rows->pair_bits : nullptr;
   const double nr = rows ? (double)rows->count : (double)g.n;
   const double nvr = (double)g.nv * nr * CB;
   if (pass_b) {  // (else the caller has written the pass-A buffer's columns)
     ProfScope ps(p, s, rows ? "passB_fwd_rows" : "passB_fwd", nvr + nr * g.n * sizeof(R), nr * M);
 #define PC_PASS_BF(MASKED)                                                                      \
   set_lds((const void*)passB_fwd_kernel<R, M, NBB, NTB, MASKED>, ldb);                          \
-  hipLaunchKernelGGL((passB_fwd_kernel<R, M, NBB, NTB, MASKED>), dim3((M / 2) / NBB), dim3(NTB), \
+  hipLaunchKernelGGL((passB_fwd_kernel<R, M, NBB, NTB, MASKED>), dim3((M / 4) / NBB), dim3(NTB), \
                      ldb, s, g, image, (cpx<R>*)p->H, (const cpx<R>*)p->twiddle,                \
                      (const R*)p->corr, bits)
     if (rows) {
@@ -1804,7 +2004,7 @@ static void run_passes_fwd(pc_plan* p, const R* image, hipStream_t s,
   set_lds((const void*)passA_fwd_kernel<R, M, NBA, NTA, MASKED>, lda);                          \
   hipLaunchKernelGGL((passA_fwd_kernel<R, M, NBA, NTA, MASKED>), dim3((g.nv + NBA - 1) / NBA),  \
                      dim3(NTA), lda, s, g, (const cpx<R>*)p->H, (cpx<R>*)p->grid,               \
-                     (const cpx<R>*)p->twiddle, bits)
+                     (const cpx<R>*)p->twiddle, cols)
   if (rows) {
     PC_PASS_AF(true);
   } else {
@@ -1959,7 +2159,7 @@ void restricted_gradient_grid(pc_plan* p, const c32* vis, int64_t natoms, const 
   hipLaunchKernelGGL(atoms_to_set_kernel, dim3(ab), dim3(256), 0, s, natoms, dord, weight, w);
   PC_LAUNCH_CHECK("atoms_to_set");
   const AtomSet as{natoms, (const int32_t*)d, (const int3*)(d + o_rows), nrows,
-                   RowMask{(const uint32_t*)(d + o_mask), nrows}};
+                   RowMask{(const uint32_t*)(d + o_mask), nrows, (const uint32_t*)(d + o_mask)}};
   // r = V - Phi_S x in plan order, then Phi_S* r
   c32* vp = (c32*)(d + o_v);
   c32* r = (c32*)p->vis_scratch;
@@ -2081,7 +2281,7 @@ int passA_blocks(int M, int nv) {
 
 int passB_blocks(int M) {
   switch (M) {
-#define PC_M(m) case m: return (m / 2) / PassShape<m>::NBB;
+#define PC_M(m) case m: return (m / 4) / PassShape<m>::NBB;
     PC_M(32) PC_M(64) PC_M(128) PC_M(256) PC_M(512) PC_M(1024) PC_M(2048) PC_M(4096) PC_M(8192)
     PC_M(16384)
 #undef PC_M

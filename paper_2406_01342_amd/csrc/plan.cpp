@@ -195,6 +195,7 @@ struct Layout {
   std::vector<uint8_t> tile_flags;      // 1 if any footprint reaches the tile
   std::vector<InterpItem> interp;       // interpolation work list
   int64_t n_partials = 0;
+  int wraps = 0;                        // footprints cross the periodic grid's edge
   bool quads = false;                   // chunks grouped by workgroup (see SpreadChunk)
   std::vector<int32_t> group_work;      // per workgroup: its longest item's visibilities
 };
@@ -285,6 +286,7 @@ static Layout build_layout(const pc_geometry* geo, bool full) {
   std::vector<double> A(L), B(L);
   std::vector<int32_t> c0u(L), c0v(L);
   std::vector<double> su(L), sv(L);
+  std::vector<uint8_t> flipped(L, 0);
   int64_t lo_u = INT64_MAX, hi_u = INT64_MIN, lo_v = INT64_MAX, hi_v = INT64_MIN;
   for (int64_t k = 0; k < L; ++k) {
     const double a = geo->u[k] * scale * dl, b = geo->v[k] * scale * dl;
@@ -293,11 +295,13 @@ static Layout build_layout(const pc_geometry* geo, bool full) {
     // The gridded adjoint takes Re(h e^{+j2pi(ul + vm + wc)}) = Re(h* e^{+j2pi(-ul - vm - wc)}):
     // a visibility with w < 0 is gridded as its conjugate at (-u, -v, -w), so
     // that the w-planes need only cover [min |w|, max |w|].  The direct sums
-    // keep (A, B) as given.
-    const bool flip = with_w && geo->w[k] < 0;
-    const double ga = flip ? -a : a, gb = flip ? -b : b;
-    const double xu = M * (ga + 0.5 - std::floor(ga + 0.5));
-    const double xv = M * (gb + 0.5 - std::floor(gb + 0.5));
+    // keep (A, B) as given.  A coplanar plan takes the same identity (wc = 0)
+    // to grid the half plane v >= 0 alone: cells xv in [M/2, M], M being
+    // v = 1/2 turn per pixel, the same frequency as cell 0.
+    const double fa = a + 0.5 - std::floor(a + 0.5), fb = b + 0.5 - std::floor(b + 0.5);
+    const bool flip = with_w ? geo->w[k] < 0 : fb < 0.5;
+    if (!with_w) flipped[k] = flip;
+    const double xu = M * (flip ? 1.0 - fa : fa), xv = M * (flip ? 1.0 - fb : fb);
     const double mu = std::ceil(xu - 0.5 * W), mv = std::ceil(xv - 0.5 * W);
     c0u[k] = (int32_t)mu;
     c0v[k] = (int32_t)mv;
@@ -323,11 +327,20 @@ static Layout build_layout(const pc_geometry* geo, bool full) {
     return false;
   };
   const bool wu = band(lo_u, hi_u, g.u0, g.nu);
-  const bool wv = band(lo_v, hi_v, g.v0, g.nv);
-  g.wrap = (wu || wv) ? 1 : 0;
-  if (g.wrap) {  // one periodic mode for both axes keeps the kernels simple
-    g.u0 = g.v0 = 0;
-    g.nu = g.nv = M;
+  if (with_w) {
+    const bool wv = band(lo_v, hi_v, g.v0, g.nv);
+    g.wrap = g.wrapv = (wu || wv) ? 1 : 0;
+    if (g.wrap) {  // one periodic mode for both axes
+      g.u0 = g.v0 = 0;
+      g.nu = g.nv = M;
+    }
+    lay.wraps = g.wrap;
+  } else {
+    g.wrap = wu ? 1 : 0;
+    g.wrapv = 0;
+    g.v0 = (int32_t)(lo_v / T) * T;  // lo_v >= M/2 - W/2 >= 0
+    g.nv = (int32_t)((hi_v + 1 + T - 1) / T * T) - g.v0;
+    lay.wraps = (wu || hi_v > M - 1) ? 1 : 0;
   }
   g.ntu = g.nu / T;
   g.ntv = g.nv / T;
@@ -339,7 +352,7 @@ static Layout build_layout(const pc_geometry* geo, bool full) {
   // only, so that the sets {down, both}, {both, right}, {both} are ranges.
   std::vector<int64_t> key(L);
   for (int64_t k = 0; k < L; ++k) {
-    int32_t cu = ((c0u[k] % M) + M) % M, cv = ((c0v[k] % M) + M) % M;
+    int32_t cu = ((c0u[k] % M) + M) % M, cv = with_w ? ((c0v[k] % M) + M) % M : c0v[k];
     int32_t ru = cu - g.u0, rv = cv - g.v0;
     int32_t tu = ru / T, tv = rv / T;
     bool sr = (ru % T) > T - W, sd = (rv % T) > T - W;
@@ -401,19 +414,16 @@ static Layout build_layout(const pc_geometry* geo, bool full) {
       const int32_t k = lay.perm[s];
       lay.AB[2 * s] = A[k];
       lay.AB[2 * s + 1] = B[k];
-      lay.cell[s] = ((uint32_t)c0v[k] << 16) | (uint32_t)c0u[k];
+      lay.cell[s] = ((uint32_t)c0v[k] << 16) | (uint32_t)c0u[k] | (flipped[k] ? kFlip : 0u);
       lay.off[2 * s] = su[k];
       lay.off[2 * s + 1] = sv[k];
     }
   }
   // Work list.
   auto tid = [&](int tv, int tu) -> int64_t {
-    if (g.wrap) {
-      tv = (tv + ntv) % ntv;
-      tu = (tu + ntu) % ntu;
-    } else if (tv < 0 || tu < 0) {
-      return -1;
-    }
+    if (g.wrapv) tv = (tv + ntv) % ntv;
+    if (g.wrap) tu = (tu + ntu) % ntu;
+    if (tv < 0 || tu < 0) return -1;
     return (int64_t)tv * ntu + tu;
   };
   auto cls_beg = [&](int64_t t, int c) { return bstart[t * 4 + c]; };
@@ -433,7 +443,9 @@ static Layout build_layout(const pc_geometry* geo, bool full) {
       rb[2] = cls_beg(tup, 1);
       re[2] = cls_beg(tup, 3);
     }
-    if (tul >= 0 && tul != t) {  // upper-left neighbour: class both
+    // upper-left neighbour: class both (a band one tile wide that wraps along
+    // u has the upper tile there, whose range holds that class already)
+    if (tul >= 0 && tul != t && tul != tup) {
       rb[3] = cls_beg(tul, 2);
       re[3] = cls_beg(tul, 3);
     }
@@ -492,6 +504,11 @@ static Layout build_layout(const pc_geometry* geo, bool full) {
     // launch while the partial tiles to fold stay few.
     constexpr int G = kSpreadQuad;
     const int64_t min_groups = 1536;
+    // (a tile of at most 512 stays whole: two partial tiles and their fold
+    // cost more than the longer item)
+    auto chunks_of = [](int64_t total, int64_t kq) {
+      return total <= 512 ? int64_t(1) : (total + 4 * kq - 1) / (4 * kq);
+    };
     auto groups_for = [&](int64_t kq) {
       int64_t light = 0, heavy = 0;
       for (int64_t t = 0; t < ntiles; ++t) {
@@ -499,7 +516,7 @@ static Layout build_layout(const pc_geometry* geo, bool full) {
         if (totals[t] <= kq)
           ++light;
         else
-          heavy += (totals[t] + 4 * kq - 1) / (4 * kq);
+          heavy += chunks_of(totals[t], kq);
       }
       return heavy + (light + G - 1) / G;
     };
@@ -530,7 +547,7 @@ static Layout build_layout(const pc_geometry* geo, bool full) {
           light.push_back(c);
           continue;
         }
-        const int64_t nch = (total + 4 * kq - 1) / (4 * kq);
+        const int64_t nch = chunks_of(total, kq);
         if (nch > 1) {
           lay.fold.push_back(FoldItem{(int32_t)t, (int32_t)lay.n_partials, (int32_t)nch, 0});
         }
@@ -695,7 +712,7 @@ static size_t layout_bytes(const Layout& lay, int prec) {
   add((size_t)lay.n_partials * kTile * kTile * cb);
   add((size_t)twiddle_entries(g.M) * cb);    // twiddles
   add((size_t)g.n * rb);                     // correction
-  add(256 + 4 * kMaxRowWords);               // max key, row mask
+  add(256 + 8 * kMaxRowWords);               // max key, row mask and its row pairs
   add(lay.L * cb);                           // vis scratch
   if (lay.ws.nplanes > 0) {
     add(lay.L * 8);                          // w
@@ -738,6 +755,7 @@ extern "C" pc_status pc_plan_create_impl(const pc_geometry* geom, void* stream, 
     p->n_partials = lay.n_partials;
     p->n_fold = (int64_t)lay.fold.size();
     p->n_interp = (int64_t)lay.interp.size();
+    p->wraps = lay.wraps;
     p->spread_quads = lay.quads;
     p->chunk_work = lay.group_work;
     const GridGeom& g = lay.g;
@@ -758,7 +776,7 @@ extern "C" pc_status pc_plan_create_impl(const pc_geometry* geom, void* stream, 
     p->partials = dalloc(p, (size_t)lay.n_partials * kTile * kTile * cb);
     p->twiddle = dalloc(p, (size_t)twiddle_entries(g.M) * cb);
     p->corr = dalloc(p, (size_t)g.n * rb);
-    p->maxkey = (unsigned long long*)dalloc(p, 256 + 4 * kMaxRowWords);
+    p->maxkey = (unsigned long long*)dalloc(p, 256 + 8 * kMaxRowWords);
     p->rowmask = (uint32_t*)((unsigned char*)p->maxkey + 256);
     p->vis_scratch = dalloc(p, L * cb);
     p->ws = lay.ws;

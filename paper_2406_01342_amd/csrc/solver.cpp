@@ -404,7 +404,7 @@ struct Pfw {
     y.ensure(nS);
     g.ensure(nS);
     adj_partial.ensure(adjoint_partial_count(p, nS));
-    act_rows = RowMask{nullptr, 0};
+    act_rows = RowMask{nullptr, 0, nullptr};
     act_rowlist = nullptr;
     act_nrows = 0;
     if (nS == 0) return;
@@ -441,7 +441,8 @@ struct Pfw {
     PC_HIP(hipMemcpyAsync(act_blk.ptr, h, bytes, hipMemcpyHostToDevice, s));
     up_act.arm(s);
     k_activate(p, nS, act_blk.ptr, x.ptr, y.ptr, pix.ptr, atoms.ptr, s);
-    act_rows = RowMask{(const uint32_t*)((const unsigned char*)act_blk.ptr + moff), nrows};
+    const uint32_t* dmask = (const uint32_t*)((const unsigned char*)act_blk.ptr + moff);
+    act_rows = RowMask{dmask, nrows, dmask};
     act_rowlist = (const int3*)((const unsigned char*)act_blk.ptr + loff);
     act_nrows = nrows;
   }
