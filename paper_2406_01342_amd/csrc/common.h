@@ -65,7 +65,7 @@ using c64 = cpx<double>;
 constexpr int kTile = 32;
 constexpr int kMaxWidth = 16;
 
-// Spreading register window: a wave's lanes cover a spread_span(W)-wide
+// Spreading register window (FP64): a wave's lanes cover a spread_span(W)-wide
 // square of cells, the union of the footprints of all visibilities whose
 // first cell lies in one spread_block(W)-wide square block.  The plan sorts
 // visibilities by that block within each tile.
@@ -75,14 +75,11 @@ __host__ __device__ constexpr int spread_block(int W) { return spread_span(W) - 
 // One spreading work item: an output tile plus the (sub)ranges of sorted
 // visibilities that reach it from the tile itself and from its left, upper
 // and upper-left neighbours.  slot >= 0 means the tile is split across
-// several items and this item writes partial tile `slot`.  FP32 plans with
-// kernel widths up to 8 group items by kSpreadQuad, one workgroup of that many
-// waves per group: either independent items (combine = 0; tile = -1 marks an
-// empty one), or shares of one tile's visibilities (combine = 1, same tile and
-// slot) whose LDS tiles the workgroup adds in a fixed order before the single
-// write.  Two waves per workgroup (31 KB of LDS) let five workgroups share a
-// compute unit, ten waves against the eight that four-wave groups (62 KB)
-// allow.
+// several items and this item writes partial tile `slot`.  FP32 plans group
+// items by kSpreadQuad, one workgroup of that many waves per group: either
+// independent items (combine = 0; tile = -1 marks an empty one), or shares of
+// one tile's visibilities (combine = 1, same tile and slot) whose tiles the
+// workgroup adds in a fixed order before the single write.
 struct SpreadChunk {
   int32_t tile;
   int32_t slot;
@@ -91,7 +88,8 @@ struct SpreadChunk {
   int32_t combine;
   int32_t pad;
 };
-constexpr int kSpreadQuad = 2;  // waves (items) per workgroup of the grouped spread
+constexpr int kSpreadQuad = 4;     // waves (items) per workgroup of the grouped spread
+constexpr int kSpreadWaves = 4096;  // its waves resident on the device (LDS: 16 per compute unit)
 
 // Interpolation work item: the plan-order visibilities [beg, end) whose first
 // cells lie in `tile` (a tile's own visibilities, in chunks of at most
@@ -235,7 +233,7 @@ struct pc_plan {
   pc::GridGeom g{};
   int64_t n_chunks = 0, n_partials = 0, n_fold = 0, n_interp = 0;
   int wraps = 0;              // footprints cross the periodic grid's edge
-  bool spread_quads = false;  // work items grouped by workgroup (FP32, kernel width <= 8)
+  bool spread_quads = false;  // work items grouped by workgroup (FP32)
   size_t footprint = 0;
 
   // Per-visibility data in plan (tile-sorted) order.

@@ -147,6 +147,11 @@ __device__ __forceinline__ int chunk_index(int q, int c1, int c2, int c3, int b0
   return q + add;
 }
 
+// End (cumulative) of the range that position q of a work item falls in.
+__device__ __forceinline__ int range_end(int q, int c1, int c2, int c3, int total) {
+  return q < c1 ? c1 : (q < c2 ? c2 : (q < c3 ? c3 : total));
+}
+
 template <typename R>
 __device__ __forceinline__ VisIn<R> fetch_vis(int s, const uint32_t* __restrict__ cell,
                                               const R* __restrict__ off,
@@ -289,42 +294,35 @@ __device__ __forceinline__ void spread_body(
   }
 }
 
-// FP32 spreading for kernel widths up to 8, four visibilities per step.
+// FP32 spreading on the matrix cores.
 //
-// The wave's lanes again cover an 8 x 8 window of cells (lane = row a, column
-// b), the union of the footprints of the visibilities whose first cell lies
-// in one RB x RB block, and a run of visibilities sharing a block accumulates
-// in registers.  What differs is how a lane gets its factors.  Each lane
-// stages one visibility of a batch of 64 and writes its weights, already
-// shifted onto the window, into two transposed tables: wy[a][j] (rows), and
-// the column weights times the value as complex pairs, wx[b][j] =
-// (wx_j[b] Re v_j, wx_j[b] Im v_j).  Consecutive visibilities j of one table
-// row are adjacent, so 128-bit LDS reads hand a lane its factors for four
-// visibilities: three reads and eight FMAs per lane for four visibilities
-// (instead of two 32-bit weight reads, the broadcast value and key reads, a
-// multiply and two FMAs per visibility).  Run boundaries are found once per
-// batch (a ballot of "my block differs from my predecessor's"); a group of
-// four with no boundary takes the straight path, a group with one flushes
-// between its visibilities.  Table rows are padded (68 and 132 floats) so
-// that the eight distinct rows a wave reads in one instruction fall in
-// distinct banks; the staging writes one row at a time from all lanes.  The
-// LDS tile holds interleaved complex cells (one 64-bit read-add-write per
-// lane and flush).  Deterministic: each cell receives its terms in a fixed
-// order.
-// Groups of four visibilities whose LDS reads are issued together.
-constexpr int kGroupsAhead = 4;
+// A tile's sum over its visibilities, tile[y][x] = sum_k wy_k[y] (wx_k[x] v_k),
+// is a product of a 32 x K and a K x 64 matrix (re and im of each column): the
+// wave keeps the whole 32 x 32 complex tile in 2 x 4 accumulator blocks of 16
+// rows by 8 complex columns, and v_mfma_f32_16x16x4_f32 adds four
+// visibilities to one block.  Only the blocks that the footprints of a step's
+// visibilities reach are computed (about two of the eight: the plan sorts a
+// tile's visibilities by the blocks they reach), so sparse and dense tiles
+// cost the same per visibility, and nothing is flushed between visibilities.
+//
+// The factors are staged in LDS, BATCH visibilities at a time: the tables
+// wy[y][j] and wx[x][j], zero outside visibility j's W taps, and the values.
+// Lanes 0-31 evaluate the row weights of one visibility each, lanes 32-63 its
+// column weights, and write the W taps; after the batch they write zeros over
+// them.  The row stride of 34 floats makes the operand reads conflict-free.
+// Taps outside the tile (visibilities spilling from a neighbour) go to row 32,
+// which no operand reads.  FP32 products and sums; deterministic (each cell
+// receives its terms in a fixed order).
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-template <int W>
-struct SpreadG {
-  static constexpr int BS = 8;                  // window side
-  static constexpr int RB = BS - W + 1;         // block side (first cells)
-  static constexpr int S = kTile + 4;           // tile row stride (complex cells)
-  static constexpr int TR = 68;                 // row-weight table row stride (floats)
-  static constexpr int TRX = 132;               // column table row stride (floats)
-  static constexpr int TILE_F = 2 * kTile * S;  // floats
-  static constexpr int TAB_F = BS * (TR + TRX); // floats
-  static constexpr size_t wave_bytes = sizeof(float) * (TILE_F + TAB_F);
-  static constexpr size_t lds_bytes = kSpreadQuad * wave_bytes;
+struct SpreadM {
+  static constexpr int BATCH = 32;              // visibilities per staged batch
+  static constexpr int S = kTile + 2;           // tile row stride (complex cells)
+  static constexpr int RS = 34;                 // table row stride (floats)
+  static constexpr int TAB_F = kTile * RS + BATCH;  // floats per table, with the discard row
+  static constexpr int WAVE_F = 2 * TAB_F + 2 * BATCH;  // 9,216 bytes
+  static_assert(2 * kTile * S <= WAVE_F, "the finished tile overlays the tables");
+  static constexpr size_t lds_bytes = kSpreadQuad * sizeof(float) * WAVE_F;
 };
 
 // Exponential-of-semicircle weight of a tap at distance x (cells) from the
@@ -337,22 +335,32 @@ __device__ __forceinline__ float es_weight(float x, float R2, float c1, float c0
   return __builtin_amdgcn_exp2f(fmaf(c1, __builtin_amdgcn_sqrtf(q), -c0));
 }
 
-// Accumulates one work item into the wave's LDS region (its tile, then its
-// tables) and leaves the tile there; the caller writes it out.
+__device__ __forceinline__ void lds_order() {  // a wave's own LDS writes before its reads
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Accumulates one work item and leaves its tile in the wave's LDS region
+// (complex cells, row stride S); the caller writes it out.
 // perm: NULL when vals is in plan order, else the plan -> caller map.
 template <int W>
 __device__ __forceinline__ void spread_group_accumulate(
     const GridGeom& g, const SpreadChunk& ch, const uint32_t* __restrict__ cell,
     const float* __restrict__ off, const cpx<float>* __restrict__ vals,
-    const int32_t* __restrict__ perm, float* __restrict__ tile, int lane) {
-  using C = SpreadG<W>;
-  static_assert(W >= 2 && W <= 8, "group spreading covers widths 2..8");
-  float* tab = tile + C::TILE_F;        // wy [8][TR]
-  float* tabx = tab + C::BS * C::TR;    // wx v as complex pairs [8][TRX]
-  const int a = lane >> 3, b = lane & 7;
+    const int32_t* __restrict__ perm, float* __restrict__ region, int lane) {
+  using C = SpreadM;
+  static_assert(W >= 2 && W <= kMaxWidth, "kernel widths");
+  float* tab = region + (lane >= 32 ? C::TAB_F : 0);  // this lane's table: wy, wx [33][RS]
+  float* tval = region + 2 * C::TAB_F;                // Re v [32], Im v [32]
+  const int j = lane & 31;
+  const bool cols = lane >= 32;
   const int tv = ch.tile / g.ntu, tu = ch.tile - tv * g.ntu;
-  const int ov = g.v0 + tv * kTile, ou = g.u0 + tu * kTile;
-  const bool single_u = g.wrap && g.M == kTile, single_v = g.wrapv && g.M == kTile;
+  const int origin = cols ? g.u0 + tu * kTile : g.v0 + tv * kTile;
+  const int wrap = cols ? g.wrap : g.wrapv;
+  const bool single = g.M == kTile && wrap;  // the periodic grid is one tile wide
+  const bool periodic = (g.wrap | g.wrapv) != 0;
+  const int bside = cols ? 8 : 16;           // the axis's block side
   constexpr float R = 0.5f * (float)W;
   const float c0 = g.beta * 1.44269504088896341f;  // beta log2(e)
   const float c1 = c0 / R;
@@ -361,185 +369,169 @@ __device__ __forceinline__ void spread_group_accumulate(
   const int c3n = c2n + ch.end[2] - ch.beg[2];
   const int total = c3n + ch.end[3] - ch.beg[3];
   const int b0 = ch.beg[0], b1 = ch.beg[1] - c1n, b2 = ch.beg[2] - c2n, b3 = ch.beg[3] - c3n;
-  {
-    float4* t4 = reinterpret_cast<float4*>(tile);
-    for (int i = lane; i < C::TILE_F / 4; i += 64) t4[i] = make_float4(0.f, 0.f, 0.f, 0.f);
-  }
-  if (total <= 0) return;
+  f32x4 acc[2][4];
+#pragma unroll
+  for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) acc[rb][q] = f32x4{0.f, 0.f, 0.f, 0.f};
   // Loads run ahead through three record buffers (batch k uses buffer k mod 3).
-  // The cell, offsets and source index of batch k + 3 and the value of batch
+  // The cell, offset and source index of batch k + 3 and the value of batch
   // k + 2 are issued while batch k is staged and summed; the value of a
   // caller-order input needs its source index, which was issued a batch
   // earlier, so no load waits on one issued just before it.  Lanes past the
-  // end load the last record again (no branch around the loads, so that each
-  // wait covers exactly the batch it consumes).
+  // end load the last record again, and both ways of forming the index issue
+  // the same loads, so that each wait covers exactly the batch it consumes.
   struct Raw {
     uint32_t cell;
-    float2 off;
-    int32_t ld, sidx;  // the loaded index, and the record's plan position
+    float off;
+    uint32_t ld, sidx;  // the loaded index, and the record's plan position
     cpx<float> val;
   };
   // (for a plan-order input the index load reads the cell array instead and
   // is discarded, so that every path issues the same loads)
-  const int32_t* src_arr = perm ? perm : reinterpret_cast<const int32_t*>(cell);
-  auto load_pre = [&](Raw& rw, int q) {
-    const int sidx = chunk_index(q < total ? q : total - 1, c1n, c2n, c3n, b0, b1, b2, b3);
-    rw.cell = cell[sidx];
-    rw.off = reinterpret_cast<const float2*>(off)[sidx];
-    rw.ld = src_arr[sidx];
-    rw.sidx = sidx;
-  };
-  // (the choice between them is made here, a batch after the index load)
-  auto load_val = [&](Raw& rw) { rw.val = vals[perm ? rw.ld : rw.sidx]; };
-  Raw rb0, rb1, rb2;
-  load_pre(rb0, lane);
-  load_val(rb0);
-  load_pre(rb1, 64 + lane);
-  load_pre(rb2, 128 + lane);
-  load_val(rb1);
-  const float* rwy = tab + a * C::TR;
-  const float* rwx = tabx + b * C::TRX;
-  int ckey = kNoBlock;
-  float accr = 0.f, acci = 0.f;
-  auto flush = [&]() {
-    if (ckey != kNoBlock) {
-      int y = ((ckey >> 8) - 64) + a, x = ((ckey & 0xff) - 64) + b;
-      if (single_v) y &= kTile - 1;
-      if (single_u) x &= kTile - 1;
-      if ((unsigned)y < (unsigned)kTile && (unsigned)x < (unsigned)kTile) {
-        float2* cp = reinterpret_cast<float2*>(tile) + y * C::S + x;
-        float2 o = *cp;
-        o.x += accr;
-        o.y += acci;
-        *cp = o;
-      }
-    }
-    accr = 0.f;
-    acci = 0.f;
-  };
-  // One batch of 64: stage from rk (batch k), reload rk with batch k + 3 and
-  // the value of rk2 (batch k + 2), then sum.
-  auto batch = [&](int base, Raw& rk, Raw& rk2) {
-    const int q = base + lane;
-    const bool valid = q < total;
-    int key = kNoBlock, du = 0, dv = 0;
-    float fy[W], fx[W], vr = 0.f, vi = 0.f;
-    if (valid) {
-      const int cu = cell_u(rk.cell), cv = cell_v(rk.cell);
-      du = cu % C::RB;
-      dv = cv % C::RB;
-      key = block_key(tile_base(cu - du, ou, g.M, C::BS, g.wrap),
-                      tile_base(cv - dv, ov, g.M, C::BS, g.wrapv));
-      vr = rk.val.x;
-      vi = __uint_as_float(__float_as_uint(rk.val.y) ^ (rk.cell & kFlip));  // conjugate if flipped
-      // tap t lies x = s + t cells from the visibility, s in (-R, -R + 1],
-      // so |x| <= R (z = x / R in (-1, 1])
-#pragma unroll
-      for (int t = 0; t < W; ++t) {
-        fy[t] = es_weight(rk.off.y + (float)t, R * R, c1, c0);
-        fx[t] = es_weight(rk.off.x + (float)t, R * R, c1, c0);
-      }
+  const uint32_t* src_arr = perm ? reinterpret_cast<const uint32_t*>(perm) : cell;
+  const uint32_t j1 = (uint32_t)j, j2 = 2 * j1 + (cols ? 0u : 1u);
+  auto load_pre = [&](Raw& rw, int q0) {
+    // a batch inside one of the four ranges has a scalar base for all lanes
+    const int end = range_end(q0, c1n, c2n, c3n, total);
+    const uint32_t s0 = (uint32_t)chunk_index(q0, c1n, c2n, c3n, b0, b1, b2, b3);
+    if (q0 + C::BATCH <= end) {
+      rw.cell = (cell + s0)[j1];
+      rw.off = (off + 2 * (size_t)s0)[j2];
+      rw.ld = (src_arr + s0)[j1];
+      rw.sidx = s0 + j1;
     } else {
-#pragma unroll
-      for (int t = 0; t < W; ++t) fy[t] = fx[t] = 0.f;
+      const int q = q0 + j;
+      const uint32_t sidx =
+          (uint32_t)chunk_index(q < total ? q : total - 1, c1n, c2n, c3n, b0, b1, b2, b3);
+      rw.cell = cell[sidx];
+      rw.off = off[2 * (size_t)sidx + (j2 & 1u)];
+      rw.ld = src_arr[sidx];
+      rw.sidx = sidx;
     }
-    load_pre(rk, q + 192);
-    load_val(rk2);
-    // run starts: a valid visibility whose block differs from its predecessor's
-    const int prev = __shfl_up(key, 1, 64);
-    const bool start = valid && (lane == 0 ? key != ckey : key != prev);
-    const unsigned long long runs = __ballot(start);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    // Every lane writes the same table row at once (consecutive addresses, no
-    // bank conflicts): window row a holds tap a - dv of the footprint, or zero
-    // outside it, picked by selects over the RB possible shifts.
-#pragma unroll
-    for (int row = 0; row < C::BS; ++row) {
-      float wy = 0.f, wx = 0.f;
-#pragma unroll
-      for (int d = 0; d < C::RB; ++d) {
-        const int t = row - d;
-        if (t >= 0 && t < W) {
-          wy = dv == d ? fy[t] : wy;
-          wx = du == d ? fx[t] : wx;
-        }
-      }
-      tab[row * C::TR + lane] = wy;
-      *reinterpret_cast<float2*>(tabx + row * C::TRX + 2 * lane) = make_float2(wx * vr, wx * vi);
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const int ng = ((total - base < 64 ? total - base : 64) + 3) >> 2;  // groups of four
-#pragma unroll 1
-    for (int g4 = 0; g4 < ng; g4 += kGroupsAhead) {
-      float4 y[kGroupsAhead], xr[kGroupsAhead], xi[kGroupsAhead];
-#pragma unroll
-      for (int u = 0; u < kGroupsAhead; ++u) {  // every read of these groups first
-        y[u] = *reinterpret_cast<const float4*>(rwy + 4 * (g4 + u));
-        // (re, im) pairs of visibilities 4g, 4g + 1, then 4g + 2, 4g + 3
-        const float4 p01 = *reinterpret_cast<const float4*>(rwx + 8 * (g4 + u));
-        const float4 p23 = *reinterpret_cast<const float4*>(rwx + 8 * (g4 + u) + 4);
-        xr[u] = make_float4(p01.x, p01.z, p23.x, p23.z);
-        xi[u] = make_float4(p01.y, p01.w, p23.y, p23.w);
-      }
-#pragma unroll
-      for (int u = 0; u < kGroupsAhead; ++u) {
-        const unsigned bits = (unsigned)(runs >> (4 * (g4 + u))) & 0xfu;
-        if (bits == 0u) {  // the group continues the current run
-          accr = fmaf(y[u].x, xr[u].x, accr);
-          acci = fmaf(y[u].x, xi[u].x, acci);
-          accr = fmaf(y[u].y, xr[u].y, accr);
-          acci = fmaf(y[u].y, xi[u].y, acci);
-          accr = fmaf(y[u].z, xr[u].z, accr);
-          acci = fmaf(y[u].z, xi[u].z, acci);
-          accr = fmaf(y[u].w, xr[u].w, accr);
-          acci = fmaf(y[u].w, xi[u].w, acci);
-        } else {
-          const int j0 = 4 * (g4 + u);
-          if (bits & 1u) {
-            flush();
-            ckey = __builtin_amdgcn_readlane(key, j0);
-          }
-          accr = fmaf(y[u].x, xr[u].x, accr);
-          acci = fmaf(y[u].x, xi[u].x, acci);
-          if (bits & 2u) {
-            flush();
-            ckey = __builtin_amdgcn_readlane(key, j0 + 1);
-          }
-          accr = fmaf(y[u].y, xr[u].y, accr);
-          acci = fmaf(y[u].y, xi[u].y, acci);
-          if (bits & 4u) {
-            flush();
-            ckey = __builtin_amdgcn_readlane(key, j0 + 2);
-          }
-          accr = fmaf(y[u].z, xr[u].z, accr);
-          acci = fmaf(y[u].z, xi[u].z, acci);
-          if (bits & 8u) {
-            flush();
-            ckey = __builtin_amdgcn_readlane(key, j0 + 3);
-          }
-          accr = fmaf(y[u].w, xr[u].w, accr);
-          acci = fmaf(y[u].w, xi[u].w, acci);
-        }
-      }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   };
-  // the three batches of a step run unconditionally (the later ones may be
-  // empty: no valid lane, zero weights, no groups), so that the loads in
-  // flight are the same on every path and each wait covers just what it needs
+  // (the choice between them is made here, a batch after the index load; row
+  // lanes need no value: they read the first one rather than repeat the
+  // column lanes' gather)
+  auto load_val = [&](Raw& rw) { rw.val = vals[cols ? (perm ? rw.ld : rw.sidx) : 0u]; };
+  // Operand addresses of this lane: row (lane & 15) of a row block, column
+  // (lane & 15) / 2 of a column block and part (lane & 1) of the values.  The
+  // two products of a step of eight visibilities take its even and odd ones:
+  // lane group lane / 16 holds visibilities 2 (lane / 16) and the next.
+  const int k2 = 2 * (lane >> 4);
+  const float* pa = region + (lane & 15) * C::RS + k2;
+  const float* pb = region + C::TAB_F + ((lane & 15) >> 1) * C::RS + k2;
+  const float* pv = tval + (lane & 1) * C::BATCH + k2;
+  // One batch: stage from rk (batch k), reload rk with batch k + 3 and the
+  // value of rk2 (batch k + 2), then sum.
+  auto batch = [&](int base, Raw& rk, Raw& rk2) {
+    const bool valid = base + j < total;
+    int lo = (cols ? cell_u(rk.cell) : cell_v(rk.cell)) - origin;
+    if (periodic) lo = tile_base(lo, 0, g.M, W, wrap);
+    const int hi = lo + W - 1;
+    float w[W];
+#pragma unroll
+    for (int t = 0; t < W; ++t) w[t] = es_weight(rk.off + (float)t, R * R, c1, c0);
+    // lanes past the end stage values of zero and reach no block
+    const float vr = valid ? rk.val.x : 0.f;
+    const float vi = valid ? __uint_as_float(__float_as_uint(rk.val.y) ^ (rk.cell & kFlip)) : 0.f;
+    load_pre(rk, base + 3 * C::BATCH);
+    load_val(rk2);
+    // which of the batch's visibilities reach each block of 16 rows (lanes
+    // 0-31) or 8 columns (lanes 32-63): lo <= last cell and hi >= first cell
+    const int left = total - base;
+    const unsigned live = left >= C::BATCH ? ~0u : (left > 0 ? (1u << left) - 1u : 0u);
+    unsigned rows[2], cls[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const unsigned long long r =
+          __builtin_amdgcn_ballot_w64((unsigned)(hi - q * bside) < (unsigned)(W - 1 + bside)) |
+          (periodic && g.M == kTile ? ~0ull : 0ull);  // (one tile wide: taps wrap inside it)
+      if (q < 2) rows[q] = (unsigned)r & live;
+      cls[q] = (unsigned)(r >> 32) & live;
+    }
+    // taps inside the tile for the whole wave: constant strides
+    const bool inside = __builtin_amdgcn_ballot_w64((unsigned)lo > (unsigned)(kTile - W)) == 0;
+    auto stage = [&](auto value) {
+      if (inside) {
+        float* p = tab + lo * C::RS + j;
+#pragma unroll
+        for (int t = 0; t < W; ++t) p[t * C::RS] = value(t);
+      } else {
+        int l = lo;
+        asm volatile("" : "+v"(l));  // this path's addresses are formed here, not ahead of the branch
+#pragma unroll
+        for (int t = 0; t < W; ++t) {
+          unsigned r = (unsigned)(l + t);
+          if (single) r &= kTile - 1;
+          tab[(r < (unsigned)kTile ? r : (unsigned)kTile) * C::RS + j] = value(t);
+        }
+      }
+    };
+    stage([&](int t) { return w[t]; });
+    if (cols) {
+      tval[j] = vr;
+      tval[C::BATCH + j] = vi;
+    }
+    lds_order();
+#pragma unroll
+    for (int st = 0; st < C::BATCH / 8; ++st) {
+      const unsigned m = 0xffu << (8 * st);
+      const unsigned r0 = rows[0] & m, r1 = rows[1] & m;
+      const float2 a0 = *reinterpret_cast<const float2*>(pa + 8 * st);
+      const float2 a1 = *reinterpret_cast<const float2*>(pa + 16 * C::RS + 8 * st);
+      const float2 v = *reinterpret_cast<const float2*>(pv + 8 * st);
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (cls[q] & m) {
+          const float2 x = *reinterpret_cast<const float2*>(pb + 8 * q * C::RS + 8 * st);
+          const float bx = x.x * v.x, by = x.y * v.y;
+          if (r0) {
+            acc[0][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0.x, bx, acc[0][q], 0, 0, 0);
+            acc[0][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(a0.y, by, acc[0][q], 0, 0, 0);
+          }
+          if (r1) {
+            acc[1][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1.x, bx, acc[1][q], 0, 0, 0);
+            acc[1][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(a1.y, by, acc[1][q], 0, 0, 0);
+          }
+        }
+    }
+    lds_order();
+    stage([&](int) { return 0.f; });
+  };
+  if (total > 0) {
+    // (issued in the order of the loop's steady state)
+    Raw rb0, rb1, rb2;
+    load_pre(rb0, 0);
+    load_pre(rb1, C::BATCH);
+    {
+      float4* t4 = reinterpret_cast<float4*>(region);
+      for (int i = lane; i < C::WAVE_F / 4; i += 64) t4[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    lds_order();
+    load_val(rb0);
+    load_pre(rb2, 2 * C::BATCH);
+    load_val(rb1);
 #pragma unroll 1
-  for (int base = 0; base < total; base += 192) {
-    batch(base, rb0, rb2);
-    batch(base + 64, rb1, rb0);
-    batch(base + 128, rb2, rb1);
+    for (int base = 0;; base += 3 * C::BATCH) {
+      batch(base, rb0, rb2);
+      if (base + C::BATCH >= total) break;
+      batch(base + C::BATCH, rb1, rb0);
+      if (base + 2 * C::BATCH >= total) break;
+      batch(base + 2 * C::BATCH, rb2, rb1);
+      if (base + 3 * C::BATCH >= total) break;
+    }
+    lds_order();
   }
-  flush();
+  // accumulator r of block (rb, q) holds row 16 rb + 4 (lane / 16) + r, float
+  // 16 q + lane % 16 of the tile row
+#pragma unroll
+  for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        region[(16 * rb + 4 * (lane >> 4) + r) * 2 * C::S + 16 * q + (lane & 15)] = acc[rb][q][r];
 }
 
 // Output address of a work item's tile: the band tile itself, or its
@@ -566,21 +558,20 @@ __device__ __forceinline__ void spread_quad_body(
     const float* __restrict__ off, const cpx<float>* __restrict__ vals,
     const int32_t* __restrict__ perm, cpx<float>* __restrict__ grid,
     cpx<float>* __restrict__ partials) {
-  using C = SpreadG<W>;
-  constexpr int WAVE_F = C::TILE_F + C::TAB_F;
+  using C = SpreadM;
+  constexpr int WAVE_F = C::WAVE_F;
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  // (the wave's index as a scalar: its work item then sits in scalar registers)
+  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
   float* region = reinterpret_cast<float*>(smem_raw);
-  const SpreadChunk& ch = quad[w];
+  const SpreadChunk ch = quad[w];
   const bool combine = quad[0].combine != 0;  // the same for every wave
   if (ch.tile >= 0)
     spread_group_accumulate<W>(g, ch, cell, off, vals, perm, region + w * WAVE_F, lane);
   size_t stride;
   if (!combine) {
     if (ch.tile < 0) return;
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    lds_order();
     cpx<float>* dst = spread_dst(g, ch, grid, partials, stride);
     const float4* t4 = reinterpret_cast<const float4*>(region + w * WAVE_F);
     for (int i = lane; i < kTile * kTile / 2; i += 64) {  // two cells per lane and step
@@ -640,16 +631,6 @@ __global__ __launch_bounds__(64) void spread_kernel(
   // here rather than by a launch of its own; the pass runs later on the stream)
   if (blockIdx.x == 0 && threadIdx.x == 0) *maxkey = 0ull;
   spread_body<R, W>(g, chunks[blockIdx.x], cell, off, vals, perm, grid, partials);
-}
-
-// One launch over the work items of several plans: items[b] = (job, item).
-template <int W>
-__global__ __launch_bounds__(64) void spread_batch_kernel(const AdjJob* __restrict__ jobs,
-                                                          const int2* __restrict__ items) {
-  const int2 it = items[blockIdx.x];
-  const AdjJob& J = jobs[it.x];
-  if (it.y == 0 && threadIdx.x == 0) *J.maxkey = 0ull;  // every job has an item 0
-  spread_body<float, W>(J.g, J.chunks[it.y], J.cell, J.off, J.vals, J.perm, J.grid, J.partials);
 }
 
 // Fold of a split tile: 64 cells per workgroup, kFoldSub threads per cell
@@ -1792,9 +1773,9 @@ template <typename R, int W>
 static void launch_spread_w(pc_plan* p, const cpx<R>* vals, const int32_t* perm, hipStream_t s) {
   const double rb = sizeof(R);
   ProfScope ps(p, s, "spread", spread_bytes(p, rb), (double)p->L);
-  if constexpr (sizeof(R) == 4 && W <= 8) {
+  if constexpr (sizeof(R) == 4) {
     if (!p->spread_quads) fail(PC_ERR_DEVICE, "spread: the plan's work list is not grouped");
-    constexpr size_t lds = SpreadG<W>::lds_bytes;
+    constexpr size_t lds = SpreadM::lds_bytes;
     static_assert(lds <= 64 * 1024, "grouped spread LDS budget");
     hipLaunchKernelGGL((spread_quad_kernel<W>), dim3((unsigned)(p->n_chunks / kSpreadQuad)),
                        dim3(64 * kSpreadQuad), lds, s, p->g, p->chunks, p->cell,
@@ -2321,15 +2302,9 @@ void pass_batch(int M, bool passA, const AdjJob* jobs, const int2* items, int ni
 
 template <int W>
 void launch_spread_batch(const AdjJob* jobs, const int2* items, int nitems, hipStream_t s) {
-  if constexpr (W <= 8) {  // grouped work lists: items are (job, workgroup)
-    constexpr size_t lds = SpreadG<W>::lds_bytes;
-    hipLaunchKernelGGL((spread_quad_batch_kernel<W>), dim3(nitems), dim3(64 * kSpreadQuad), lds,
-                       s, jobs, items);
-  } else {
-    constexpr size_t lds = SpreadCfg<float, W>::lds_bytes;
-    set_lds((const void*)spread_batch_kernel<W>, lds);
-    hipLaunchKernelGGL((spread_batch_kernel<W>), dim3(nitems), dim3(64), lds, s, jobs, items);
-  }
+  // grouped work lists: items are (job, workgroup)
+  hipLaunchKernelGGL((spread_quad_batch_kernel<W>), dim3(nitems), dim3(64 * kSpreadQuad),
+                     SpreadM::lds_bytes, s, jobs, items);
   PC_LAUNCH_CHECK("spread_batch");
 }
 

@@ -350,37 +350,53 @@ static Layout build_layout(const pc_geometry* geo, bool full) {
   // Tile and spill class of each visibility.  Class order inside a tile:
   // 0 none, 1 spills down (+v) only, 2 spills both ways, 3 spills right (+u)
   // only, so that the sets {down, both}, {both, right}, {both} are ranges.
+  auto wrapped = [M](int32_t c) { return c < 0 ? c + M : (c >= M ? c - M : c); };
   std::vector<int64_t> key(L);
   for (int64_t k = 0; k < L; ++k) {
-    int32_t cu = ((c0u[k] % M) + M) % M, cv = with_w ? ((c0v[k] % M) + M) % M : c0v[k];
-    int32_t ru = cu - g.u0, rv = cv - g.v0;
+    int32_t cu = wrapped(c0u[k]), cv = with_w ? wrapped(c0v[k]) : c0v[k];
+    int32_t ru = cu - g.u0, rv = cv - g.v0;  // >= 0
     int32_t tu = ru / T, tv = rv / T;
-    bool sr = (ru % T) > T - W, sd = (rv % T) > T - W;
+    bool sr = (ru & (T - 1)) > T - W, sd = (rv & (T - 1)) > T - W;
     int cls = sd ? (sr ? 2 : 1) : (sr ? 3 : 0);
     key[k] = ((int64_t)tv * ntu + tu) * 4 + cls;
     c0u[k] = cu;
     c0v[k] = cv;
   }
-  // Sort by (tile, spill class, first-cell block within the tile): a stable
-  // counting sort on the block of the first cell (square blocks of
-  // spread_block(W) cells on the absolute fine grid, counted from the tile's
-  // first block), then a stable counting sort on (tile, class).  Visibilities
-  // sharing a block end up adjacent, which the spreading kernel exploits by
-  // accumulating them in registers over one window.
+  // Sort by (tile, spill class, place within the tile): a stable counting
+  // sort on the place, then a stable counting sort on (tile, class).
+  // FP32: the place is the set of 16-row and 8-column blocks of the tile that
+  // the footprint reaches (the accumulator blocks of the matrix-core spread),
+  // so that neighbours in the order share their blocks.
+  // FP64: the block of the first cell (square blocks of spread_block(W) cells
+  // on the absolute fine grid, counted from the tile's first block), which the
+  // spread accumulates in registers over one window.
+  lay.quads = geo->precision == PC_PREC_FP32;
   std::vector<int32_t> order(L);
-  {
+  auto by_place = [&](size_t places, auto place) {
+    std::vector<int64_t> c(places + 1, 0);
+    for (int64_t k = 0; k < L; ++k) c[place(k) + 1]++;
+    for (size_t i = 0; i + 1 < c.size(); ++i) c[i + 1] += c[i];
+    for (int64_t k = 0; k < L; ++k) order[c[place(k)]++] = (int32_t)k;
+  };
+  if (lay.quads) {
+    // (then by row, so that neighbouring lanes stage into the same table row,
+    // without bank conflicts)
+    int16_t row[kTile], col[kTile];  // place of a first cell along each axis
+    for (int x = 0; x < T; ++x) {
+      row[x] = (int16_t)(16 * 8 * (2 * (x >> 4) + ((x & 15) + W > 16 ? 1 : 0)) + (x & 15));
+      col[x] = (int16_t)(16 * (2 * (x >> 3) + ((x & 7) + W > 8 ? 1 : 0)));
+    }
+    // (u0 and v0 are multiples of the tile)
+    by_place(512, [&](int64_t k) { return (size_t)(row[c0v[k] & (T - 1)] + col[c0u[k] & (T - 1)]); });
+  } else {
     const int RB = spread_block(W);
     const int nbk = T / RB + 2;  // blocks a tile's first cells can fall in, per axis
-    std::vector<int64_t> c((size_t)nbk * nbk + 1, 0);
-    auto local = [&](int64_t k) {
+    by_place((size_t)nbk * nbk, [&](int64_t k) {
       const int32_t ou = g.u0 + ((c0u[k] - g.u0) / T) * T;
       const int32_t ov = g.v0 + ((c0v[k] - g.v0) / T) * T;
       const int32_t bu = c0u[k] / RB - ou / RB, bv = c0v[k] / RB - ov / RB;
-      return (int64_t)bv * nbk + bu;
-    };
-    for (int64_t k = 0; k < L; ++k) c[local(k) + 1]++;
-    for (size_t i = 0; i + 1 < c.size(); ++i) c[i + 1] += c[i];
-    for (int64_t k = 0; k < L; ++k) order[c[local(k)]++] = (int32_t)k;
+      return (size_t)bv * nbk + bu;
+    });
   }
   std::vector<int64_t> cnt(ntiles * 4 + 1, 0);
   for (int64_t k = 0; k < L; ++k) cnt[key[k] + 1]++;
@@ -492,40 +508,30 @@ static Layout build_layout(const pc_geometry* geo, bool full) {
                                                                    bstart[t * 4 + 4]),
                                         0});
     }
-  lay.quads = geo->precision == PC_PREC_FP32 && W <= 8;
   if (lay.quads) {
     // Grouped spread: workgroups of G = kSpreadQuad waves.  A tile with at
     // most kq visibilities is one wave's item, packed G to a workgroup with
     // items of similar length; a heavier tile is cut into chunks of at most
-    // 4 kq, each shared by the G waves of one workgroup (combine), which write
+    // G kq, each shared by the G waves of one workgroup (combine), which write
     // the tile itself when one chunk covers it and a partial tile otherwise.
-    // kq is the largest of 1024, 512, ..., 64 that still gives at least 1536
-    // workgroups, so that the longest work stays short against the whole
-    // launch while the partial tiles to fold stay few.
+    // The longest item is then kq, the largest power of two that is no more
+    // than an even share of all the work per resident wave (16 per compute
+    // unit), so that no wave outlasts the launch: at most 512, and at least
+    // 64 (32 on a band of few tiles), below which the partial tiles and their
+    // fold cost more than the shorter items give.
     constexpr int G = kSpreadQuad;
-    const int64_t min_groups = 1536;
-    // (a tile of at most 512 stays whole: two partial tiles and their fold
-    // cost more than the longer item)
-    auto chunks_of = [](int64_t total, int64_t kq) {
-      return total <= 512 ? int64_t(1) : (total + 4 * kq - 1) / (4 * kq);
+    int64_t events = 0, occupied = 0;
+    for (int64_t t = 0; t < ntiles; ++t) {
+      events += totals[t];
+      occupied += totals[t] > 0;
+    }
+    int64_t kq = occupied < 256 ? 32 : 64;
+    while (kq < 512 && 2 * kq * kSpreadWaves <= events) kq *= 2;
+    // wave w's share of [q0, q1) starts here: whole batches of 32 but the last
+    auto share = [](int64_t q0, int64_t q1, int w) {
+      const int64_t batches = (q1 - q0 + 31) / 32;
+      return std::min(q1, q0 + 32 * (batches * w / G));
     };
-    auto groups_for = [&](int64_t kq) {
-      int64_t light = 0, heavy = 0;
-      for (int64_t t = 0; t < ntiles; ++t) {
-        if (totals[t] == 0) continue;
-        if (totals[t] <= kq)
-          ++light;
-        else
-          heavy += chunks_of(totals[t], kq);
-      }
-      return heavy + (light + G - 1) / G;
-    };
-    int64_t kq = 64;
-    for (int64_t c = 1024; c >= 64; c /= 2)
-      if (groups_for(c) >= min_groups) {
-        kq = c;
-        break;
-      }
     struct Group {
       int64_t work;
       SpreadChunk c[G];
@@ -547,12 +553,13 @@ static Layout build_layout(const pc_geometry* geo, bool full) {
           light.push_back(c);
           continue;
         }
-        const int64_t nch = chunks_of(total, kq);
+        const int64_t nch = (total + G * kq - 1) / (G * kq);
         if (nch > 1) {
           lay.fold.push_back(FoldItem{(int32_t)t, (int32_t)lay.n_partials, (int32_t)nch, 0});
         }
         for (int64_t c = 0; c < nch; ++c) {
-          const int64_t q0 = total * c / nch, q1 = total * (c + 1) / nch;
+          const int64_t q0 = total * c / nch / 32 * 32;
+          const int64_t q1 = c + 1 < nch ? total * (c + 1) / nch / 32 * 32 : total;
           Group gr{};
           gr.work = 0;
           for (int w = 0; w < G; ++w) {
@@ -560,7 +567,7 @@ static Layout build_layout(const pc_geometry* geo, bool full) {
             ch.tile = (int32_t)t;
             ch.slot = nch > 1 ? (int32_t)(lay.n_partials + c) : -1;
             ch.combine = 1;
-            sub_ranges(rb, re, q0 + (q1 - q0) * w / G, q0 + (q1 - q0) * (w + 1) / G, ch);
+            sub_ranges(rb, re, share(q0, q1, w), share(q0, q1, w + 1), ch);
             gr.work = std::max(gr.work, work(ch));
           }
           groups.push_back(gr);
@@ -595,7 +602,7 @@ static Layout build_layout(const pc_geometry* geo, bool full) {
     }
     return lay;
   }
-  // One wave per item (FP64 plans, kernel widths above 8).  Split tiles whose
+  // One wave per item (FP64 plans).  Split tiles whose
   // gathered count exceeds kChunk: 256 visibilities keeps the longest item
   // short when few items exist (the spread is then bound by its longest work
   // item); with many items the spread is throughput-bound, and 512 halves the
