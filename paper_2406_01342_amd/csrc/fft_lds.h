@@ -299,4 +299,85 @@ __device__ __forceinline__ void lds_fft(cpx<R>* buf, const cpx<R>* tw) {
   fft_stages<R, M, NB, NT, SIGN, 1>(buf, tw);
 }
 
+// ---------------------------------------------------------------------------
+// Register-held transforms of length M = 4096 S (S = 1, 2, 4) whose input
+// lies in a window of 4096 consecutive slots centred on M / 2 (any 4096 slots
+// are the whole input for S = 1), FP32, one sequence per 256 threads.
+//
+// The outputs f = S k + s of one residue s are a 4096-point transform of the
+// input with its own twiddles, X[S k + s] = sum_m x_m w^(m (S k + s)),
+// w = exp(SIGN 2 pi i / M): thread t holds the inputs of slots t + 256 r (mod
+// 4096), r < 16, in registers for all residues, and three radix-16 stages with
+// twiddles u_1 = w^(256 s), u_2 = w^(16 (S k_1 + s)), u_3 = w^(S (k_1 + 16
+// k_2) + s) (folded into the DFTs, see dft_tw) give k = k_1 + 16 k_2 + 256 k_3;
+// the zero input slots cost nothing, no full-length buffer is needed, and two
+// LDS exchanges per residue replace the four of a padded length-M transform.
+// Slots at or above M / 2 (r < 8) carry w^(4096 S/2 s), those below
+// w^(4096 (S/2 - 1) s): quarter or half turns known at compile time.
+// 35 KB of LDS and 256 threads: four workgroups per compute unit, whose
+// barriers are independent.
+constexpr int kRegN = 4096, kRegT = 256;
+constexpr int kRegBuf = 4352;  // exchange buffer (elements): 256 x 17 and 16 x 272
+
+// v exp(SIGN 2 pi i q / S) for constants S in {1, 2, 4} and q.
+template <int S, int Q, int SIGN>
+__device__ __forceinline__ cpx<float> turn_const(cpx<float> v) {
+  constexpr int q = ((Q * (4 / S)) & 3) * (SIGN > 0 ? 1 : 3) & 3;
+  if constexpr (q == 0) return v;
+  if constexpr (q == 1) return {-v.y, v.x};
+  if constexpr (q == 2) return {-v.x, -v.y};
+  return {v.y, -v.x};
+}
+
+// exp(SIGN 2 pi i K / 64), K = 0..3
+template <int K, int SIGN>
+__device__ __forceinline__ cpx<float> root64() {
+  static_assert(K >= 0 && K < 4, "first-stage twiddles");
+  constexpr double c[4] = {1.0, 0.99518472667219688624, 0.98078528040323044913,
+                           0.95694033573220886494};
+  constexpr double sn[4] = {0.0, 0.09801714032956060199, 0.19509032201612826785,
+                            0.29028467725446236764};
+  return {(float)c[K], SIGN > 0 ? (float)sn[K] : (float)-sn[K]};
+}
+
+// Residue s: y[k3] = X[S (t + 256 k3) + s] from the inputs x[r] of slots
+// t + 256 r.  buf is free on entry (every earlier read of it behind a
+// barrier); its last reads, of residue s, are not followed by one.
+template <int S, int s, int SIGN>
+__device__ __forceinline__ void reg_fft(const cpx<float> (&x)[16], cpx<float> (&y)[16],
+                                        cpx<float>* __restrict__ buf,
+                                        const cpx<float>* __restrict__ tws) {
+  constexpr int M = kRegN * S;
+  const int t = (int)threadIdx.x, lo = t & 15, hi = t >> 4;
+#pragma unroll
+  for (int r = 0; r < 16; ++r)
+    y[r] = r < 8 ? turn_const<S, s*(S / 2), SIGN>(x[r])
+                 : turn_const<S, s*(S > 1 ? S / 2 - 1 : 0), SIGN>(x[r]);
+  if constexpr (s == 0)
+    dft<float, 16, SIGN>(y);
+  else
+    dft_tw<float, 16, SIGN>(y, root64<s * 4 / S, SIGN>());
+#pragma unroll
+  for (int k = 0; k < 16; ++k) buf[17 * t + k] = y[k];
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < 16; ++r) y[r] = buf[17 * (hi + 16 * r) + lo];
+  {
+    cpx<float> u = twiddle<float, M>(tws, 16 * (S * lo + s));
+    if (SIGN < 0) u.y = -u.y;
+    dft_tw<float, 16, SIGN>(y, u);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 16; ++k) buf[272 * hi + lo + 16 * k] = y[k];
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < 16; ++r) y[r] = buf[272 * r + t];
+  {
+    cpx<float> u = twiddle<float, M>(tws, S * t + s);
+    if (SIGN < 0) u.y = -u.y;
+    dft_tw<float, 16, SIGN>(y, u);
+  }
+}
+
 }  // namespace pc

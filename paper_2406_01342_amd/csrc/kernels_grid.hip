@@ -25,6 +25,7 @@
 #include <algorithm>
 #include <cstring>
 #include <memory>
+#include <type_traits>
 
 #include "common.h"
 #include "fft_lds.h"
@@ -716,16 +717,26 @@ __device__ __forceinline__ cpx<R> turns_pos(cpx<R> v, int q) {
 }
 
 // Pass-A output layout: columns grouped in blocks of KHB, each block stored
-// row-major over the band rows, so that a pass-B workgroup reading KHB (or
-// fewer) adjacent columns reads one contiguous stretch.
-constexpr int kHBLarge = 4;  // block width at fine grids of 8192 and more
+// row-major over the band rows; h_col is the element of a column at band row
+// 0, its rows are KHB apart.  Columns 2k and 2k + 1 stay adjacent (pass B reads
+// them together).  At the 16384 fine grid, whose pass A stores a thread's
+// columns 4k, 4k + 1 and 4k + 2, 4k + 3 at different times, the pairs of each
+// kind are grouped apart, so that neighbouring lanes fill a block's row at
+// once.
+constexpr int kSplitGrid = 16384;
 template <int M>
 constexpr int khb_for() {
-  return M >= 8192 ? kHBLarge : 8;
+  return M == kSplitGrid ? 4 : 8;
 }
-template <int KHB>
+template <int M>
+__device__ __forceinline__ size_t h_col(int col, int nv) {
+  constexpr int KHB = khb_for<M>();
+  const int c = M == kSplitGrid ? ((col >> 1) & 1) * (M / 4) + ((col >> 2) << 1) + (col & 1) : col;
+  return (size_t)(c / KHB) * nv * KHB + (c % KHB);
+}
+template <int M>
 __device__ __forceinline__ size_t h_index(int row, int col, int nv) {
-  return ((size_t)(col / KHB) * nv + row) * KHB + (col % KHB);
+  return h_col<M>(col, nv) + (size_t)row * khb_for<M>();
 }
 
 // Fills the padded LDS buffer from global memory: element idx (< TOTAL) goes
@@ -879,7 +890,7 @@ __device__ __forceinline__ void passA_adj_body(const GridGeom& g, const cpx<R>* 
   auto store = [&](int b, int f, cpx<R> v) {
     const int row = row0 + b;
     const int i = f < n / 2 ? f + n / 2 : f - M + n / 2;
-    if (row < g.nv && (!rows || row_set(smask, i))) H[h_index<khb_for<M>()>(row, i, g.nv)] = v;
+    if (row < g.nv && (!rows || row_set(smask, i))) H[h_index<M>(row, i, g.nv)] = v;
   };
   // a last-stage butterfly j (outputs j + r M/16) keeps the columns
   // i = j + t M/16, t = 0..7: with a row mask, one whose eight columns are all
@@ -909,6 +920,98 @@ __global__ __launch_bounds__(NT) void passA_adj_kernel(GridGeom g, const cpx<R>*
                                                         const uint32_t* __restrict__ rows) {
   passA_adj_body<R, M, NB, NT>(g, grid, tile_flags, H, tw, xcd_local(blockIdx.x, gridDim.x),
                                rows);
+}
+
+// Two adjacent columns of the pass-A buffer at one band row.
+template <typename R>
+struct alignas(4 * sizeof(R)) cpair {
+  cpx<R> a, b;
+};
+
+// Pass A of the adjoint by register-held transforms (FP32, M = 4096 S): one
+// band row per workgroup, the band within the window of 4096 slots centred on
+// M / 2 (reg_window).  Outputs f = S t + s + 256 S k3 are the columns
+// i = S t + s + 256 S q, q = (k3 + 4) mod 16 < 8; the S residues of a thread
+// are adjacent columns, written two at a time.
+__host__ __device__ constexpr bool reg_window(int M, int lo, int hi) {  // slots [lo, hi)
+  return M == kRegN ||
+         (M > kRegN && M <= 4 * kRegN && lo >= M / 2 - kRegN / 2 && hi <= M / 2 + kRegN / 2);
+}
+
+template <int S>
+__device__ __forceinline__ void passA_reg_body(const GridGeom& g, const c32* __restrict__ grid,
+                                               const uint8_t* __restrict__ tile_flags,
+                                               c32* __restrict__ H, const c32* __restrict__ tw,
+                                               int row, const uint32_t* __restrict__ rows) {
+  constexpr int M = kRegN * S;
+  static_assert(S * kRegN == M && (S == 1 || S == 2 || S == 4), "register-held pass sizes");
+  __shared__ c32 buf[kRegBuf];
+  __shared__ c32 tws[tw_count(M)];
+  __shared__ uint8_t sflag[kMaxTileCols];
+  __shared__ uint32_t smask[kMaxRowWords];
+  const int t = (int)threadIdx.x;
+  rows_to_lds<kRegT>(smask, rows, g.n);
+  for (int c = t; c < g.ntu; c += kRegT) sflag[c] = tile_flags[(row / kTile) * g.ntu + c];
+  load_twiddles<float, M, kRegT>(tws, tw);  // ends with a barrier
+  c32 x[16];
+  bool ok[16];
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    const int c = t + kRegT * r;
+    const int rel = (S == 1 ? c : M / 2 + (r < 8 ? c : c - kRegN)) - g.u0;
+    ok[r] = (unsigned)rel < (unsigned)g.nu && sflag[rel / kTile] != 0;
+    x[r] = grid[ok[r] ? (size_t)row * g.nu + rel : 0];
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r)
+    if (!ok[r]) x[r] = {0.f, 0.f};
+  constexpr int KHB = khb_for<M>();
+  auto set = [&](int i) { return !rows || row_set(smask, i); };
+  if constexpr (S == 1) {
+    c32 y[16];
+    reg_fft<1, 0, +1>(x, y, buf, tws);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int i = t + kRegT * q;
+      if (set(i)) H[h_index<M>(row, i, g.nv)] = y[(q + 12) & 15];
+    }
+  } else {
+    auto pair = [&](auto s0) {
+      c32 y0[16], y1[16];
+      if constexpr (s0 > 0) __syncthreads();
+      reg_fft<S, s0, +1>(x, y0, buf, tws);
+      __syncthreads();
+      reg_fft<S, s0 + 1, +1>(x, y1, buf, tws);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const int i = S * (t + kRegT * q) + s0, k3 = (q + 12) & 15;
+        c32* h = H + h_index<M>(row, i, g.nv);  // columns i, i + 1: 16 bytes
+        if (!rows)
+          *reinterpret_cast<cpair<float>*>(h) = cpair<float>{y0[k3], y1[k3]};
+        else {
+          if (row_set(smask, i)) h[0] = y0[k3];
+          if (row_set(smask, i + 1)) h[1] = y1[k3];
+        }
+      }
+    };
+    pair(std::integral_constant<int, 0>{});
+    if constexpr (S == 4) pair(std::integral_constant<int, 2>{});
+  }
+}
+
+template <int S, bool MASKED>
+__global__ __launch_bounds__(kRegT, S == 4 ? 3 : 4) void passA_adj_reg_kernel(
+    GridGeom g, const c32* __restrict__ grid, const uint8_t* __restrict__ tile_flags,
+    c32* __restrict__ H, const c32* __restrict__ tw, const uint32_t* __restrict__ rows) {
+  passA_reg_body<S>(g, grid, tile_flags, H, tw, xcd_local(blockIdx.x, gridDim.x), rows);
+}
+
+template <int S>
+__global__ __launch_bounds__(kRegT, S == 4 ? 3 : 4) void passA_reg_batch_kernel(const AdjJob* __restrict__ jobs,
+                                                                   const int2* __restrict__ items) {
+  const int2 it = items[xcd_local(blockIdx.x, gridDim.x)];
+  const AdjJob& J = jobs[it.x];
+  passA_reg_body<S>(J.g, J.grid, J.flags, J.H, J.tw, it.y, J.rows);
 }
 
 template <int M, int NB, int NT>
@@ -953,7 +1056,7 @@ __device__ __forceinline__ void passB_adj_w_body(const GridGeom& g, const cpx<R>
   const int b = (int)threadIdx.x & (NB - 1), m0 = (int)threadIdx.x / NB;
   const int col = i0 + b;
   constexpr int KHB = khb_for<M>();
-  const cpx<R>* hcol = H + (size_t)(col / KHB) * g.nv * KHB + (col % KHB);
+  const cpx<R>* hcol = H + h_col<M>(col, g.nv);
   // Input pruning: with a first radix of 2 or 4 and a band no longer than
   // M / radix, each first-stage butterfly (inputs j + r M / radix) holds at
   // most one band row, so the stage is applied while loading: output s of
@@ -1034,12 +1137,6 @@ __device__ __forceinline__ void passB_adj_w_body(const GridGeom& g, const cpx<R>
     lds_fft_store<R, M, NB, NT, +1>(buf, tws, keep, store);
   }
 }
-
-// Two adjacent columns of the pass-A buffer at one band row.
-template <typename R>
-struct alignas(4 * sizeof(R)) cpair {
-  cpx<R> a, b;
-};
 
 // The half plane's Hermitian completion.  Coplanar plans hold the band rows
 // v >= 0 (and the kernel's reach below), H_i(c) for cells c = v0 + rel; image
@@ -1125,7 +1222,7 @@ __device__ __forceinline__ void passB_adj_body(const GridGeom& g, const cpx<R>* 
   const int b = (int)threadIdx.x & (NB - 1), m0 = (int)threadIdx.x / NB;
   const int col = i0 + 2 * b;
   constexpr int KHB = khb_for<M>();
-  const cpx<R>* hcol = H + (size_t)(col / KHB) * g.nv * KHB + (col % KHB);
+  const cpx<R>* hcol = H + h_col<M>(col, g.nv);
   auto load = [&](int rel) {
     return *reinterpret_cast<const cpair<R>*>(hcol + (size_t)rel * KHB);
   };
@@ -1269,6 +1366,160 @@ __global__ __launch_bounds__(NT) void passB_adj_kernel(GridGeom g, const cpx<R>*
                                                         const uint32_t* __restrict__ rows) {
   passB_adj_body<R, M, NB, NT>(g, H, image, tw, corr, scale, maxkey, positive,
                                xcd_local(blockIdx.x, gridDim.x), rows);
+}
+
+// Pass B of the adjoint by register-held transforms (FP32, M = 4096 S): one
+// pair of image rows per workgroup, the completed column within the window of
+// 4096 slots centred on M / 2.  Thread t holds the pixels j = S t + s + 256 S q
+// (q < 8), two adjacent ones per store.
+template <int S>
+__device__ __forceinline__ void passB_reg_body(const GridGeom& g, const c32* __restrict__ H,
+                                               float* __restrict__ image,
+                                               const c32* __restrict__ tw,
+                                               const float* __restrict__ corr, float scale,
+                                               unsigned long long* __restrict__ maxkey,
+                                               int positive, int pairno,
+                                               const uint32_t* __restrict__ rows) {
+  constexpr int M = kRegN * S, n = M / 2;
+  __shared__ c32 buf[kRegBuf];
+  __shared__ c32 tws[tw_count(M)];
+  const int t = (int)threadIdx.x, i0 = 2 * pairno;
+  // with a row mask: pairs without a row set return at once, the others
+  // store only their rows that are set
+  const bool set0 = !rows || row_set(rows, i0), set1 = !rows || row_set(rows, i0 + 1);
+  if (!set0 && !set1) return;  // the whole workgroup
+  load_twiddles<float, M, kRegT>(tws, tw);
+  constexpr int KHB = khb_for<M>();
+  const c32* hcol = H + h_col<M>(i0, g.nv);
+  auto load = [&](int rel) {
+    return *reinterpret_cast<const cpair<float>*>(hcol + (size_t)rel * KHB);
+  };
+  const PairGeom pg{M, g.v0, g.nv};
+  c32 x[16];
+  {
+    cpair<float> h[16];
+    auto cell = [&](int r) {  // the slot's cell in [0, M)
+      const int c = t + kRegT * r;
+      return S == 1 ? c : M / 2 + (r < 8 ? c : c - kRegN);
+    };
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      bool conj, ok;
+      const int rel = pair_main(pg, cell(r), conj, ok);
+      h[r] = load(ok ? rel : 0);
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      bool conj, ok;
+      pair_main(pg, cell(r), conj, ok);
+      x[r] = pair_z<float>(h[r], conj);
+      if (!ok) x[r] = {0.f, 0.f};
+      if (pair_edge(pg, cell(r))) {
+        const c32 e = pair_rest<float>(pg, cell(r), load);
+        x[r] = {x[r].x + e.x, x[r].y + e.y};
+      }
+    }
+  }
+  // the largest |eta| (by its bits, so that a NaN wins) of each row and its j,
+  // lowest on ties: pixels come in ascending j within a residue pair
+  unsigned best[2];
+  int at[2];
+  auto begin = [&](int s0) {  // (an all-zero row reports its first pixel)
+    best[0] = best[1] = 0u;
+    at[0] = at[1] = S * t + s0;
+  };
+  unsigned long long key = 0;
+  const float dl = (float)g.dl;
+  const float l0 = (float)(i0 - n / 2) * dl, l1 = (float)(i0 + 1 - n / 2) * dl;
+  const float ci0 = corr[i0] * (0.5f * scale), ci1 = corr[i0 + 1] * (0.5f * scale);
+  auto pixel = [&](c32 v, int j, float cj, float& p0, float& p1) {
+    const float mm = (float)(j - n / 2) * dl;
+    p0 = v.x * ci0 * cj * __builtin_amdgcn_rsqf(1.0f - l0 * l0 - mm * mm);
+    p1 = v.y * ci1 * cj * __builtin_amdgcn_rsqf(1.0f - l1 * l1 - mm * mm);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const float p = h ? p1 : p0;
+      // positive part: +0 for every value <= 0 (never -0, whose bits would win)
+      const unsigned b = __float_as_uint(positive ? (p > 0.f ? p : 0.0f) : fabsf(p));
+      const bool up = b > best[h];
+      best[h] = up ? b : best[h];
+      at[h] = up ? j : at[h];
+    }
+  };
+  auto fold = [&]() {  // the rows' maxima so far into the key (only rows stored count)
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const unsigned long long k = max_key(__uint_as_float(best[h]), (i0 + h) * n + at[h]);
+      if ((h ? set1 : set0) && k > key) key = k;
+    }
+  };
+  float* row0 = image + (size_t)i0 * n;
+  float* row1 = row0 + n;
+  if constexpr (S == 1) {
+    c32 y[16];
+    reg_fft<1, 0, +1>(x, y, buf, tws);
+    begin(0);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int j = t + kRegT * q;
+      float p0, p1;
+      pixel(y[(q + 12) & 15], j, corr[j], p0, p1);
+      if (set0) row0[j] = p0;
+      if (set1) row1[j] = p1;
+    }
+    fold();
+  } else {
+    auto pair = [&](auto s0) {
+      c32 y0[16], y1[16];
+      if constexpr (s0 > 0) __syncthreads();
+      reg_fft<S, s0, +1>(x, y0, buf, tws);
+      __syncthreads();
+      reg_fft<S, s0 + 1, +1>(x, y1, buf, tws);
+      begin(s0);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const int j = S * (t + kRegT * q) + s0, k3 = (q + 12) & 15;
+        const float2 cj = *reinterpret_cast<const float2*>(corr + j);
+        float2 p0, p1;
+        pixel(y0[k3], j, cj.x, p0.x, p1.x);
+        pixel(y1[k3], j + 1, cj.y, p0.y, p1.y);
+        if (set0) *reinterpret_cast<float2*>(row0 + j) = p0;
+        if (set1) *reinterpret_cast<float2*>(row1 + j) = p1;
+      }
+      fold();
+    };
+    pair(std::integral_constant<int, 0>{});
+    if constexpr (S == 4) pair(std::integral_constant<int, 2>{});
+  }
+  for (int o = 32; o > 0; o >>= 1) {
+    const unsigned long long other = __shfl_xor(key, o, 64);
+    key = other > key ? other : key;
+  }
+  __shared__ unsigned long long wbest[kRegT / 64];
+  if ((t & 63) == 0) wbest[t >> 6] = key;
+  __syncthreads();
+  if (t == 0 && maxkey) {
+    unsigned long long m = 0;
+    for (int w = 0; w < kRegT / 64; ++w) m = wbest[w] > m ? wbest[w] : m;
+    atomicMax(maxkey, m);
+  }
+}
+
+template <int S, bool MASKED>
+__global__ __launch_bounds__(kRegT, S == 4 ? 3 : 4) void passB_adj_reg_kernel(
+    GridGeom g, const c32* __restrict__ H, float* __restrict__ image, const c32* __restrict__ tw,
+    const float* __restrict__ corr, float scale, unsigned long long* __restrict__ maxkey,
+    int positive, const uint32_t* __restrict__ rows) {
+  passB_reg_body<S>(g, H, image, tw, corr, scale, maxkey, positive,
+                    xcd_local(blockIdx.x, gridDim.x), rows);
+}
+
+template <int S>
+__global__ __launch_bounds__(kRegT, S == 4 ? 3 : 4) void passB_reg_batch_kernel(const AdjJob* __restrict__ jobs,
+                                                                   const int2* __restrict__ items) {
+  const int2 it = items[xcd_local(blockIdx.x, gridDim.x)];
+  const AdjJob& J = jobs[it.x];
+  passB_reg_body<S>(J.g, J.H, J.image, J.tw, J.corr, J.scale, J.maxkey, J.positive, it.y, J.rows);
 }
 
 template <typename R, int M, int NB, int NT>
@@ -1481,7 +1732,7 @@ __device__ __forceinline__ void passB_fwd_body(const GridGeom& g, const R* __res
     const int c = v0 + rel;
     const cpx<R> z = buf[pidx(b * M + (c & (M - 1)))];
     const cpx<R> w = buf[pidx(b * M + ((M - c) & (M - 1)))];
-    *reinterpret_cast<cpair<R>*>(H + h_index<KHB>(rel, i0 + 2 * b, nv)) =
+    *reinterpret_cast<cpair<R>*>(H + h_index<M>(rel, i0 + 2 * b, nv)) =
         cpair<R>{{R(0.5) * (z.x + w.x), R(0.5) * (z.y - w.y)},
                  {R(0.5) * (z.y + w.y), R(0.5) * (w.x - z.x)}};
   }
@@ -1518,7 +1769,7 @@ __global__ __launch_bounds__(NT) void passA_fwd_kernel(GridGeom g, const cpx<R>*
     // H column c is image row c: zero, and not read, when the mask clears it;
     // rows past the band (last workgroup) read row 0 and are never stored
     if (rows && !row_set(smask, c)) return {R(0), R(0)};
-    return H[h_index<KHB>(row < nv ? row : 0, c, nv)];
+    return H[h_index<M>(row < nv ? row : 0, c, nv)];
   });
   __syncthreads();
   const int u0 = g.u0, nu = g.nu;
@@ -1706,7 +1957,7 @@ __device__ __forceinline__ float inv_n_f32(const GridGeom& g, int i, int j) {
 // Forward: H[band row][i] = sum over the atoms of row i of c e^{-2 pi i f q / M}
 // for each occupied row i (rowlist: row, first atom, end), atoms sorted by
 // pixel with FP64 weights w.
-template <int KHB>
+template <int M>
 __global__ __launch_bounds__(256) void rows_fwd_direct_kernel(GridGeom g,
                                                               const int3* __restrict__ rowlist,
                                                               const int32_t* __restrict__ pix,
@@ -1726,14 +1977,14 @@ __global__ __launch_bounds__(256) void rows_fwd_direct_kernel(GridGeom g,
       hx += c * __builtin_amdgcn_cosf(tt);
       hy -= c * __builtin_amdgcn_sinf(tt);
     }
-    H[h_index<KHB>(rel, i, g.nv)] = {hx, hy};
+    H[h_index<M>(rel, i, g.nv)] = {hx, hy};
   }
 }
 
 // Adjoint at the atoms: one 256-thread workgroup per atom, g = Re(sum over
 // band rows of H[band row][i] e^{+2 pi i f q / M}) times the corrections, in
 // FP64 out (thread sums combined in a fixed order).
-template <int KHB>
+template <int M>
 __global__ __launch_bounds__(256) void atoms_adj_direct_kernel(GridGeom g,
                                                                const int32_t* __restrict__ pix,
                                                                const c32* __restrict__ H,
@@ -1745,7 +1996,7 @@ __global__ __launch_bounds__(256) void atoms_adj_direct_kernel(GridGeom g,
   float acc = 0.f;
   for (int rel = t; rel < g.nv; rel += 256) {
     const float tt = turns_mod(j - n / 2, g.v0 + rel, g.M);
-    const c32 h = H[h_index<KHB>(rel, i, g.nv)];
+    const c32 h = H[h_index<M>(rel, i, g.nv)];
     acc += h.x * __builtin_amdgcn_cosf(tt) - h.y * __builtin_amdgcn_sinf(tt);
   }
   double d = acc;
@@ -1883,6 +2134,19 @@ constexpr int nt_for() {
   return TOTAL_BUTTERFLIES >= 1024 ? 1024 : (TOTAL_BUTTERFLIES >= 512 ? 512 : 256);
 }
 
+// The register-held passes take FP32 plans of fine grids 4096 ... 16384 whose
+// band (pass A), or completed column (pass B), fits their window; wider bands
+// and the other sizes go through the full-length LDS transforms.
+constexpr bool reg_size(int M) { return M == kRegN || M == 2 * kRegN || M == 4 * kRegN; }
+static bool reg_passA(const GridGeom& g) {
+  return reg_size(g.M) && reg_window(g.M, g.u0, g.u0 + g.nu);
+}
+static bool reg_passB(const GridGeom& g) {
+  const int hi = g.v0 + g.nv;  // cells [v0, hi) and their mirror images M - c
+  const int lo = std::min(g.v0, g.M + 1 - hi);
+  return reg_size(g.M) && reg_window(g.M, lo, g.M + 1 - lo);
+}
+
 template <typename R, int M>
 static void run_passes_adj(pc_plan* p, R* image, R scale, hipStream_t s,
                            const WPlane* wp = nullptr, const RowMask* rows = nullptr,
@@ -1904,8 +2168,24 @@ static void run_passes_adj(pc_plan* p, R* image, R scale, hipStream_t s,
   {
     ProfScope ps(p, s, rows ? "passA_adj_rows" : "passA_adj", (double)g.nv * g.nu * CB + nvr,
                  (double)g.nv * M);
+    bool passA_done = false;
+    if constexpr (sizeof(R) == 4 && reg_size(M)) {
+      if (reg_passA(g)) {
+        constexpr int S = M / kRegN;
+        if (rows)
+          hipLaunchKernelGGL((passA_adj_reg_kernel<S, true>), dim3(g.nv), dim3(kRegT), 0, s, g,
+                             (const c32*)p->grid, p->tile_flags, (c32*)p->H,
+                             (const c32*)p->twiddle, cols);
+        else
+          hipLaunchKernelGGL((passA_adj_reg_kernel<S, false>), dim3(g.nv), dim3(kRegT), 0, s, g,
+                             (const c32*)p->grid, p->tile_flags, (c32*)p->H,
+                             (const c32*)p->twiddle, nullptr);
+        passA_done = true;
+      }
+    }
+    if (!passA_done) {
 #define PC_PASS_A(MASKED)                                                                      \
-  set_lds((const void*)passA_adj_kernel<R, M, NBA, NTA, MASKED>, lda);                         \
+      set_lds((const void*)passA_adj_kernel<R, M, NBA, NTA, MASKED>, lda);                         \
   hipLaunchKernelGGL((passA_adj_kernel<R, M, NBA, NTA, MASKED>), dim3((g.nv + NBA - 1) / NBA), \
                      dim3(NTA), lda, s, g, (const cpx<R>*)p->grid, p->tile_flags,              \
                      (cpx<R>*)p->H, (const cpx<R>*)p->twiddle, cols)
@@ -1915,6 +2195,7 @@ static void run_passes_adj(pc_plan* p, R* image, R scale, hipStream_t s,
       PC_PASS_A(false);
     }
 #undef PC_PASS_A
+    }
     PC_LAUNCH_CHECK("passA_adj");
   }
   if (!pass_b) return;  // (the caller evaluates pass B itself)
@@ -1936,6 +2217,21 @@ static void run_passes_adj(pc_plan* p, R* image, R scale, hipStream_t s,
   }
   ProfScope ps(p, s, rows ? "passB_adj_rows" : "passB_adj",
                nvr + nr * g.n * sizeof(R), nr * M);
+  if constexpr (sizeof(R) == 4 && reg_size(M)) {
+    if (reg_passB(g)) {
+      constexpr int S = M / kRegN;
+      if (rows)
+        hipLaunchKernelGGL((passB_adj_reg_kernel<S, true>), dim3(g.n / 2), dim3(kRegT), 0, s, g,
+                           (const c32*)p->H, image, (const c32*)p->twiddle, (const float*)p->corr,
+                           scale, nullptr, p->max_positive, bits);
+      else
+        hipLaunchKernelGGL((passB_adj_reg_kernel<S, false>), dim3(g.n / 2), dim3(kRegT), 0, s, g,
+                           (const c32*)p->H, image, (const c32*)p->twiddle, (const float*)p->corr,
+                           scale, p->maxkey, p->max_positive, nullptr);
+      PC_LAUNCH_CHECK("passB_adj");
+      return;
+    }
+  }
 #define PC_PASS_B(MASKED)                                                                       \
   set_lds((const void*)passB_adj_kernel<R, M, NBB, NTB, MASKED>, ldb);                          \
   hipLaunchKernelGGL((passB_adj_kernel<R, M, NBB, NTB, MASKED>), dim3((M / 4) / NBB), dim3(NTB), \
@@ -2034,11 +2330,11 @@ void forward_grid_set(pc_plan* p, const AtomSet& as, const double* w, const c32*
     ProfScope ps(p, s, "passB_fwd_set", 8.0 * g.nv * as.rows.count + 12.0 * as.nS,
                  (double)g.nv * as.nS);
     const dim3 grid((unsigned)((g.nv + 255) / 256), (unsigned)as.nrows);
-    if (g.M >= 8192)
-      hipLaunchKernelGGL((rows_fwd_direct_kernel<khb_for<8192>()>), grid, dim3(256), 0, s, g,
+    if (g.M == kSplitGrid)  // (the other sizes share one layout)
+      hipLaunchKernelGGL((rows_fwd_direct_kernel<kSplitGrid>), grid, dim3(256), 0, s, g,
                          as.rowlist, as.pix, w, (const float*)p->corr, (c32*)p->H);
     else
-      hipLaunchKernelGGL((rows_fwd_direct_kernel<khb_for<4096>()>), grid, dim3(256), 0, s, g,
+      hipLaunchKernelGGL((rows_fwd_direct_kernel<kSplitGrid / 2>), grid, dim3(256), 0, s, g,
                          as.rowlist, as.pix, w, (const float*)p->corr, (c32*)p->H);
     PC_LAUNCH_CHECK("rows_fwd_direct");
   }
@@ -2055,11 +2351,11 @@ void adjoint_grid_set(pc_plan* p, const c32* vis, const AtomSet& as, double* gou
   dispatch_M<float>(p, true, nullptr, nullptr, 1.0f, s, nullptr, &as.rows, false);
   ProfScope ps(p, s, "passB_adj_set", 8.0 * g.nv * as.rows.count + 12.0 * as.nS,
                (double)g.nv * as.nS);
-  if (g.M >= 8192)
-    hipLaunchKernelGGL((atoms_adj_direct_kernel<khb_for<8192>()>), dim3((unsigned)as.nS),
+  if (g.M == kSplitGrid)  // (the other sizes share one layout)
+    hipLaunchKernelGGL((atoms_adj_direct_kernel<kSplitGrid>), dim3((unsigned)as.nS),
                        dim3(256), 0, s, g, as.pix, (const c32*)p->H, (const float*)p->corr, gout);
   else
-    hipLaunchKernelGGL((atoms_adj_direct_kernel<khb_for<4096>()>), dim3((unsigned)as.nS),
+    hipLaunchKernelGGL((atoms_adj_direct_kernel<kSplitGrid / 2>), dim3((unsigned)as.nS),
                        dim3(256), 0, s, g, as.pix, (const c32*)p->H, (const float*)p->corr, gout);
   PC_LAUNCH_CHECK("atoms_adj_direct");
 }
@@ -2289,8 +2585,23 @@ void launch_pass_batch(bool passA, const AdjJob* jobs, const int2* items, int ni
   }
 }
 
-void pass_batch(int M, bool passA, const AdjJob* jobs, const int2* items, int nitems,
+template <int S>
+void launch_pass_reg_batch(bool passA, const AdjJob* jobs, const int2* items, int nitems,
+                           hipStream_t s) {
+  if (passA)
+    hipLaunchKernelGGL((passA_reg_batch_kernel<S>), dim3(nitems), dim3(kRegT), 0, s, jobs, items);
+  else
+    hipLaunchKernelGGL((passB_reg_batch_kernel<S>), dim3(nitems), dim3(kRegT), 0, s, jobs, items);
+  PC_LAUNCH_CHECK("pass_reg_batch");
+}
+
+void pass_batch(int M, bool reg, bool passA, const AdjJob* jobs, const int2* items, int nitems,
                 hipStream_t s) {
+  if (reg) switch (M) {
+      case kRegN: launch_pass_reg_batch<1>(passA, jobs, items, nitems, s); return;
+      case 2 * kRegN: launch_pass_reg_batch<2>(passA, jobs, items, nitems, s); return;
+      case 4 * kRegN: launch_pass_reg_batch<4>(passA, jobs, items, nitems, s); return;
+    }
   switch (M) {
 #define PC_M(m) case m: launch_pass_batch<m>(passA, jobs, items, nitems, s); return;
     PC_M(32) PC_M(64) PC_M(128) PC_M(256) PC_M(512) PC_M(1024) PC_M(2048) PC_M(4096) PC_M(8192)
@@ -2371,7 +2682,7 @@ void adjoint_grid_batch(BatchCtx& ctx, pc_plan* const* plans, const c32* const* 
   std::vector<AdjJob> jobs(n);
   std::vector<std::pair<int32_t, int2>> sitems;  // (work, (job, chunk))
   std::vector<int2> fitems;
-  std::vector<int> Ms, Ws;
+  std::vector<int> Ms, Ws;  // (Ms: fine grids of any plan)
   for (int j = 0; j < n; ++j) {
     pc_plan* p = plans[j];
     PC_REQUIRE(p && p->precision == PC_PREC_FP32, "batched adjoint needs FP32 plans");
@@ -2417,20 +2728,26 @@ void adjoint_grid_batch(BatchCtx& ctx, pc_plan* const* plans, const c32* const* 
     n_spread[w] = it.size();
   }
   const size_t o_fold = blob.put(fitems);
-  std::vector<size_t> oA(Ms.size()), nA(Ms.size()), oB(Ms.size()), nB(Ms.size());
-  for (size_t m = 0; m < Ms.size(); ++m) {
-    std::vector<int2> a, b;
-    for (int j = 0; j < n; ++j) {
-      if (plans[j]->g.M != Ms[m]) continue;
-      const int na = passA_blocks(Ms[m], plans[j]->g.nv), nbk = passB_blocks(Ms[m]);
-      for (int r = 0; r < na; ++r) a.push_back(make_int2(j, r));
-      for (int r = 0; r < nbk; ++r) b.push_back(make_int2(j, r));
-    }
-    oA[m] = blob.put(a);
-    nA[m] = a.size();
-    oB[m] = blob.put(b);
-    nB[m] = b.size();
-  }
+  // pass items per fine grid, those of the register-held passes apart
+  struct PassItems {
+    int M;
+    bool reg, first;
+    size_t off, count;
+  };
+  std::vector<PassItems> passes;
+  for (const bool first : {true, false})
+    for (const int M : Ms)
+      for (const bool reg : {false, true}) {
+        std::vector<int2> it;
+        for (int j = 0; j < n; ++j) {
+          const GridGeom& g = plans[j]->g;
+          if (g.M != M || (first ? reg_passA(g) : reg_passB(g)) != reg) continue;
+          const int blocks = reg ? (first ? g.nv : g.n / 2)
+                                 : (first ? passA_blocks(M, g.nv) : passB_blocks(M));
+          for (int r = 0; r < blocks; ++r) it.push_back(make_int2(j, r));
+        }
+        if (!it.empty()) passes.push_back({M, reg, first, blob.put(it), it.size()});
+      }
   const size_t bytes = blob.bytes.size();
   if (ctx.host_bytes < bytes) {
     if (ctx.host) (void)hipHostFree(ctx.host);
@@ -2457,10 +2774,8 @@ void adjoint_grid_batch(BatchCtx& ctx, pc_plan* const* plans, const c32* const* 
                        dim3(64 * kFoldSub), 0, s, djobs, (const int2*)(ctx.dev + o_fold));
     PC_LAUNCH_CHECK("fold_batch");
   }
-  for (size_t m = 0; m < Ms.size(); ++m)
-    if (nA[m]) pass_batch(Ms[m], true, djobs, (const int2*)(ctx.dev + oA[m]), (int)nA[m], s);
-  for (size_t m = 0; m < Ms.size(); ++m)
-    if (nB[m]) pass_batch(Ms[m], false, djobs, (const int2*)(ctx.dev + oB[m]), (int)nB[m], s);
+  for (const PassItems& ps : passes)  // every first pass, then every second
+    pass_batch(ps.M, ps.reg, ps.first, djobs, (const int2*)(ctx.dev + ps.off), (int)ps.count, s);
   PC_HIP(hipEventRecord(ctx.done, s));
   ctx.pending = true;
 }

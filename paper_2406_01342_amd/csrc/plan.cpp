@@ -516,7 +516,7 @@ static Layout build_layout(const pc_geometry* geo, bool full) {
     // the tile itself when one chunk covers it and a partial tile otherwise.
     // The longest item is then kq, the largest power of two that is no more
     // than an even share of all the work per resident wave (16 per compute
-    // unit), so that no wave outlasts the launch: at most 512, and at least
+    // unit), so that no wave outlasts the launch: at most 1024, and at least
     // 64 (32 on a band of few tiles), below which the partial tiles and their
     // fold cost more than the shorter items give.
     constexpr int G = kSpreadQuad;
@@ -526,7 +526,7 @@ static Layout build_layout(const pc_geometry* geo, bool full) {
       occupied += totals[t] > 0;
     }
     int64_t kq = occupied < 256 ? 32 : 64;
-    while (kq < 512 && 2 * kq * kSpreadWaves <= events) kq *= 2;
+    while (kq < 1024 && 2 * kq * kSpreadWaves <= events) kq *= 2;
     // wave w's share of [q0, q1) starts here: whole batches of 32 but the last
     auto share = [](int64_t q0, int64_t q1, int w) {
       const int64_t batches = (q1 - q0 + 31) / 32;
