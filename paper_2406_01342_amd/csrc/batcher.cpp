@@ -133,9 +133,10 @@ struct pc_batcher {
       adjoint_grid_batch(ctx, plans.data(), vis.data(), flags.get(), images.data(), scales.data(),
                          n, stream);
       PC_HIP(hipEventRecord(e1, stream));
+      std::vector<Readback> rb(n);
       for (int j = 0; j < n; ++j)
-        PC_HIP(hipMemcpyAsync(keys + j, plans[j]->maxkey, sizeof(unsigned long long),
-                              hipMemcpyDeviceToHost, stream));
+        rb[j] = Readback{plans[j]->maxkey, keys + j, sizeof(unsigned long long)};
+      readback(rb.data(), n, stream);
     }
     PC_HIP(hipStreamSynchronize(stream));
     if (n > 0) PC_HIP(hipEventElapsedTime(&ms, e0, e1));

@@ -276,10 +276,7 @@ pc_status pc_adjoint_grid_batch(pc_plan* const* plans, const void* const* vis,
     adjoint_grid_batch(g_batch_ctx[dev], plans, (const c32* const*)vis, sorted.get(), images,
                        nullptr, njobs, s);
     for (int j = 0; j < njobs; ++j) plan_touch(plans[j], s);
-    if (max_abs || argmax) {
-      for (int j = 0; j < njobs; ++j)
-        maxkey_read(plans[j], s, max_abs ? max_abs + j : nullptr, argmax ? argmax + j : nullptr);
-    }
+    if (max_abs || argmax) maxkey_read(plans, njobs, s, max_abs, argmax);
     return PC_OK;
   });
 }

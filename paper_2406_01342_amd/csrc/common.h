@@ -259,6 +259,7 @@ struct pc_plan {
   uint32_t* rowmask = nullptr;  // a caller's row mask and its row pairs (after the max key)
   int max_positive = 0;  // the key holds max(x, 0) in place of |x| (positivity-constrained solve)
   void* vis_scratch = nullptr;  // complex [L] in plan order (residual etc.)
+  unsigned long long* key_host = nullptr;  // pinned slot that maxkey_read reads back into
   pc::WStack ws;                // w-stacking planes (nplanes 0: coplanar)
   void* wvals = nullptr;        // complex [L]: one plane's weighted visibilities
   double* wquad = nullptr;      // [2 nquad] doubles: Psi's Chebyshev series (kPsiCheb terms)
@@ -307,6 +308,11 @@ void* pool_alloc(int device, size_t bytes, size_t* got);
 void pool_release(int device, void* ptr, size_t bytes);
 size_t pool_class(size_t bytes);
 size_t pool_trim(int device);
+// Pinned host slots of eight bytes for small readbacks (allocated in pages that
+// all plans share; pc_device_pool_trim frees them when none is in use).
+unsigned long long* pinned_slot();
+void pinned_slot_release(unsigned long long* slot);
+void pinned_slots_trim();
 // Work of a plan's entry points is followed by an event on the call's stream
 // (one per stream the plan has seen); destroying the plan waits for these
 // events only.
@@ -395,6 +401,17 @@ void adjoint_grid_set(pc_plan* p, const c32* vis, const AtomSet& as, double* gou
 void restricted_gradient_grid(pc_plan* p, const c32* vis, int64_t natoms, const int32_t* pix,
                               const float* weight, double* grad, c32* resid, hipStream_t s);
 void maxkey_read(pc_plan* p, hipStream_t s, double* max_abs, int64_t* argmax);
+// The same for several plans: one readback, one wait.
+void maxkey_read(pc_plan* const* plans, int n, hipStream_t s, double* max_abs, int64_t* argmax);
+// Copies small device buffers to pinned host memory by one kernel on the
+// stream (a copy call each costs the host more than the launch, and the device
+// a launch each).  bytes: a multiple of 4.  The caller waits for the stream.
+struct Readback {
+  const void* src;
+  void* dst;
+  uint32_t bytes;
+};
+void readback(const Readback* r, int n, hipStream_t s);
 // Launch tables of the batched adjoint (device copy and pinned staging),
 // reused from call to call.
 struct BatchCtx {

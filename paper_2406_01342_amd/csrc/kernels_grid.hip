@@ -2453,11 +2453,42 @@ void restricted_gradient_grid(pc_plan* p, const c32* vis, int64_t natoms, const 
   PC_HIP(hipStreamSynchronize(s));  // the host staging above goes out of scope
 }
 
-void maxkey_read(pc_plan* p, hipStream_t s, double* max_abs, int64_t* argmax) {
-  unsigned long long key = 0;
-  PC_HIP(hipMemcpyAsync(&key, p->maxkey, sizeof(key), hipMemcpyDeviceToHost, s));
+struct ReadbackArgs {
+  static constexpr int kMax = 32;
+  Readback r[kMax];
+};
+__global__ __launch_bounds__(256) void readback_kernel(ReadbackArgs a) {
+  const Readback r = a.r[blockIdx.x];
+  const uint32_t* src = (const uint32_t*)r.src;
+  uint32_t* dst = (uint32_t*)r.dst;
+  for (uint32_t i = threadIdx.x; i < r.bytes / 4; i += 256) dst[i] = src[i];
+}
+
+void readback(const Readback* r, int n, hipStream_t s) {
+  for (int i = 0; i < n; i += ReadbackArgs::kMax) {
+    ReadbackArgs a{};
+    const int m = std::min(n - i, ReadbackArgs::kMax);
+    std::copy(r + i, r + i + m, a.r);
+    hipLaunchKernelGGL(readback_kernel, dim3((unsigned)m), dim3(256), 0, s, a);
+    PC_LAUNCH_CHECK("readback");
+  }
+}
+
+void maxkey_read(pc_plan* const* plans, int n, hipStream_t s, double* max_abs, int64_t* argmax) {
+  std::vector<Readback> r((size_t)n);
+  for (int j = 0; j < n; ++j) {
+    if (!plans[j]->key_host) plans[j]->key_host = pinned_slot();
+    r[j] = Readback{plans[j]->maxkey, plans[j]->key_host, sizeof(unsigned long long)};
+  }
+  readback(r.data(), n, s);
   PC_HIP(hipStreamSynchronize(s));
-  maxkey_decode(key, max_abs, argmax);
+  for (int j = 0; j < n; ++j)
+    maxkey_decode(*plans[j]->key_host, max_abs ? max_abs + j : nullptr,
+                  argmax ? argmax + j : nullptr);
+}
+
+void maxkey_read(pc_plan* p, hipStream_t s, double* max_abs, int64_t* argmax) {
+  maxkey_read(&p, 1, s, max_abs, argmax);
 }
 
 void maxkey_decode(unsigned long long key, double* max_abs, int64_t* argmax) {
@@ -2526,17 +2557,6 @@ void forward_grid(pc_plan* p, const R* image, cpx<R>* vis_out, bool out_sorted, 
 // Batched adjoint across plans
 // ----------------------------------------------------------------------------
 namespace {
-struct Blob {
-  std::vector<unsigned char> bytes;
-  template <typename T>
-  size_t put(const std::vector<T>& v) {
-    size_t off = (bytes.size() + 255) & ~size_t(255);
-    bytes.resize(off + v.size() * sizeof(T));
-    if (!v.empty()) std::memcpy(bytes.data() + off, v.data(), v.size() * sizeof(T));
-    return off;
-  }
-};
-
 template <int M>
 struct PassShape {
   static constexpr int CB = sizeof(c32);
@@ -2680,9 +2700,7 @@ void adjoint_grid_batch(BatchCtx& ctx, pc_plan* const* plans, const c32* const* 
   if (ctx.pending) PC_HIP(hipEventSynchronize(ctx.done));
   // job descriptors and work lists
   std::vector<AdjJob> jobs(n);
-  std::vector<std::pair<int32_t, int2>> sitems;  // (work, (job, chunk))
-  std::vector<int2> fitems;
-  std::vector<int> Ms, Ws;  // (Ms: fine grids of any plan)
+  std::vector<int> Ms, Ws;
   for (int j = 0; j < n; ++j) {
     pc_plan* p = plans[j];
     PC_REQUIRE(p && p->precision == PC_PREC_FP32, "batched adjoint needs FP32 plans");
@@ -2705,50 +2723,47 @@ void adjoint_grid_batch(BatchCtx& ctx, pc_plan* const* plans, const c32* const* 
     J.maxkey = p->maxkey;
     J.positive = p->max_positive;
     J.rows = nullptr;
-    // one entry per workgroup: a group of four items, or one item
-    for (size_t c = 0; c < p->chunk_work.size(); ++c)
-      sitems.push_back({p->chunk_work[c], make_int2(j, (int)c)});
-    for (int64_t f = 0; f < p->n_fold; ++f) fitems.push_back(make_int2(j, (int)f));
     if (std::find(Ms.begin(), Ms.end(), p->g.M) == Ms.end()) Ms.push_back(p->g.M);
     if (std::find(Ws.begin(), Ws.end(), p->g.W) == Ws.end()) Ws.push_back(p->g.W);
   }
-  // longest spreading items first across all plans
-  std::stable_sort(sitems.begin(), sitems.end(),
-                   [](const std::pair<int32_t, int2>& a, const std::pair<int32_t, int2>& b) {
-                     return a.first > b.first;
-                   });
-  Blob blob;
-  const size_t o_jobs = blob.put(jobs);
-  std::vector<size_t> o_spread(Ws.size()), n_spread(Ws.size());
-  for (size_t w = 0; w < Ws.size(); ++w) {
-    std::vector<int2> it;
-    for (auto& e : sitems)
-      if (plans[e.second.x]->g.W == Ws[w]) it.push_back(e.second);
-    o_spread[w] = blob.put(it);
-    n_spread[w] = it.size();
-  }
-  const size_t o_fold = blob.put(fitems);
-  // pass items per fine grid, those of the register-held passes apart
+  // Table sizes, then the tables themselves, written straight into the pinned
+  // staging: the jobs, the spreading workgroups per kernel width, the folded
+  // tiles, and the pass items per fine grid (those of the register-held passes
+  // apart, every first pass ahead of every second).
   struct PassItems {
     int M;
     bool reg, first;
     size_t off, count;
   };
+  size_t bytes = 0;
+  auto reserve = [&](size_t count, size_t size) {
+    const size_t off = (bytes + 255) & ~size_t(255);
+    bytes = off + count * size;
+    return off;
+  };
+  auto blocks_of = [&](int j, int M, bool reg, bool first) -> int {
+    const GridGeom& g = plans[j]->g;
+    if (g.M != M || (first ? reg_passA(g) : reg_passB(g)) != reg) return 0;
+    return reg ? (first ? g.nv : g.n / 2) : (first ? passA_blocks(M, g.nv) : passB_blocks(M));
+  };
+  const size_t o_jobs = reserve(n, sizeof(AdjJob));
+  std::vector<size_t> o_spread(Ws.size()), n_spread(Ws.size(), 0);
+  for (size_t w = 0; w < Ws.size(); ++w) {
+    for (int j = 0; j < n; ++j)
+      if (plans[j]->g.W == Ws[w]) n_spread[w] += plans[j]->chunk_work.size();
+    o_spread[w] = reserve(n_spread[w], sizeof(int2));
+  }
+  size_t n_fold = 0;
+  for (int j = 0; j < n; ++j) n_fold += (size_t)plans[j]->n_fold;
+  const size_t o_fold = reserve(n_fold, sizeof(int2));
   std::vector<PassItems> passes;
   for (const bool first : {true, false})
     for (const int M : Ms)
       for (const bool reg : {false, true}) {
-        std::vector<int2> it;
-        for (int j = 0; j < n; ++j) {
-          const GridGeom& g = plans[j]->g;
-          if (g.M != M || (first ? reg_passA(g) : reg_passB(g)) != reg) continue;
-          const int blocks = reg ? (first ? g.nv : g.n / 2)
-                                 : (first ? passA_blocks(M, g.nv) : passB_blocks(M));
-          for (int r = 0; r < blocks; ++r) it.push_back(make_int2(j, r));
-        }
-        if (!it.empty()) passes.push_back({M, reg, first, blob.put(it), it.size()});
+        size_t count = 0;
+        for (int j = 0; j < n; ++j) count += (size_t)blocks_of(j, M, reg, first);
+        if (count) passes.push_back({M, reg, first, reserve(count, sizeof(int2)), count});
       }
-  const size_t bytes = blob.bytes.size();
   if (ctx.host_bytes < bytes) {
     if (ctx.host) (void)hipHostFree(ctx.host);
     ctx.host = nullptr;
@@ -2763,14 +2778,42 @@ void adjoint_grid_batch(BatchCtx& ctx, pc_plan* const* plans, const c32* const* 
     PC_HIP(hipMalloc((void**)&ctx.dev, bytes * 2));
     ctx.dev_bytes = bytes * 2;
   }
-  std::memcpy(ctx.host, blob.bytes.data(), bytes);
+  std::memcpy(ctx.host + o_jobs, jobs.data(), n * sizeof(AdjJob));
+  for (size_t w = 0; w < Ws.size(); ++w) {
+    // Longest spreading workgroups first across all plans, to a factor of two:
+    // each plan lists its own longest first, so the classes of work above 512,
+    // 256, ... are taken from the plans in turn.
+    int2* it = (int2*)(ctx.host + o_spread[w]);
+    std::vector<size_t> at(n, 0);
+    for (int32_t above = 512;; above = above > 16 ? above / 2 : -1) {
+      for (int j = 0; j < n; ++j) {
+        const pc_plan* p = plans[j];
+        if (p->g.W != Ws[w]) continue;
+        while (at[j] < p->chunk_work.size() && p->chunk_work[at[j]] > above)
+          *it++ = make_int2(j, (int)at[j]++);
+      }
+      if (above < 0) break;
+    }
+  }
+  {
+    int2* it = (int2*)(ctx.host + o_fold);
+    for (int j = 0; j < n; ++j)
+      for (int64_t f = 0; f < plans[j]->n_fold; ++f) *it++ = make_int2(j, (int)f);
+  }
+  for (const PassItems& ps : passes) {
+    int2* it = (int2*)(ctx.host + ps.off);
+    for (int j = 0; j < n; ++j) {
+      const int blocks = blocks_of(j, ps.M, ps.reg, ps.first);
+      for (int r = 0; r < blocks; ++r) *it++ = make_int2(j, r);
+    }
+  }
   PC_HIP(hipMemcpyAsync(ctx.dev, ctx.host, bytes, hipMemcpyHostToDevice, s));
   const AdjJob* djobs = (const AdjJob*)(ctx.dev + o_jobs);
   for (size_t w = 0; w < Ws.size(); ++w)
     if (n_spread[w])
       spread_batch(Ws[w], djobs, (const int2*)(ctx.dev + o_spread[w]), (int)n_spread[w], s);
-  if (!fitems.empty()) {
-    hipLaunchKernelGGL(fold_batch_kernel, dim3((unsigned)fitems.size(), kTile * kTile / 64),
+  if (n_fold) {
+    hipLaunchKernelGGL(fold_batch_kernel, dim3((unsigned)n_fold, kTile * kTile / 64),
                        dim3(64 * kFoldSub), 0, s, djobs, (const int2*)(ctx.dev + o_fold));
     PC_LAUNCH_CHECK("fold_batch");
   }

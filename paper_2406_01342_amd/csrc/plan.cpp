@@ -101,6 +101,44 @@ size_t pool_trim(int device) {
   return n;
 }
 
+namespace {
+constexpr size_t kSlotPage = 4096;
+std::mutex g_slots_mu;
+std::vector<void*> g_slot_pages;
+std::vector<unsigned long long*> g_slots;  // free ones
+}  // namespace
+
+unsigned long long* pinned_slot() {
+  std::lock_guard<std::mutex> lk(g_slots_mu);
+  if (g_slots.empty()) {
+    void* page = nullptr;
+    PC_HIP(hipHostMalloc(&page, kSlotPage, hipHostMallocPortable));
+    g_slot_pages.push_back(page);
+    for (size_t i = 0; i < kSlotPage / sizeof(unsigned long long); ++i)
+      g_slots.push_back(static_cast<unsigned long long*>(page) + i);
+  }
+  unsigned long long* s = g_slots.back();
+  g_slots.pop_back();
+  return s;
+}
+
+void pinned_slot_release(unsigned long long* slot) {
+  if (!slot) return;
+  std::lock_guard<std::mutex> lk(g_slots_mu);
+  g_slots.push_back(slot);
+}
+
+void pinned_slots_trim() {
+  std::vector<void*> pages;
+  {
+    std::lock_guard<std::mutex> lk(g_slots_mu);
+    if (g_slots.size() < g_slot_pages.size() * (kSlotPage / sizeof(unsigned long long))) return;
+    g_slots.clear();
+    pages.swap(g_slot_pages);
+  }
+  for (void* p : pages) (void)hipHostFree(p);
+}
+
 void plan_touch(pc_plan* p, hipStream_t s) {
   for (auto& t : p->touched)
     if (t.first == s) {
@@ -130,6 +168,8 @@ void plan_release(pc_plan* p) {
     (void)hipEventDestroy(t.second);
   }
   p->touched.clear();
+  pinned_slot_release(p->key_host);
+  p->key_host = nullptr;
   for (auto& b : p->owned) pool_release(p->device, b.ptr, b.bytes);
   p->owned.clear();
   if (p->ev_a) (void)hipEventDestroy(p->ev_a);
@@ -736,6 +776,7 @@ using namespace pc;
 extern "C" pc_status pc_device_pool_trim_impl(int32_t device, size_t* released) {
   PC_REQUIRE(device >= 0, "device must be >= 0");
   const size_t n = pool_trim(device);
+  pinned_slots_trim();
   if (released) *released = n;
   return PC_OK;
 }

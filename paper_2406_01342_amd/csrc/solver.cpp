@@ -341,10 +341,11 @@ struct Pfw {
                       cand_count.ptr, cand.ptr, cand.cap, s);
     const int64_t first = std::min<int64_t>(kFirstCandidates, cand.cap);
     unsigned char* h = (unsigned char*)down.get(28 + first * 4);
-    PC_HIP(hipMemcpyAsync(h, p->maxkey, 8, hipMemcpyDeviceToHost, s));
-    PC_HIP(hipMemcpyAsync(h + 8, scal.ptr + kScalResid, 16, hipMemcpyDeviceToHost, s));
-    PC_HIP(hipMemcpyAsync(h + 24, cand_count.ptr, 4, hipMemcpyDeviceToHost, s));
-    PC_HIP(hipMemcpyAsync(h + 28, cand.ptr, first * 4, hipMemcpyDeviceToHost, s));
+    const Readback rb[4] = {{p->maxkey, h, 8},
+                            {scal.ptr + kScalResid, h + 8, 16},
+                            {cand_count.ptr, h + 24, 4},
+                            {cand.ptr, h + 28, (uint32_t)(first * 4)}};
+    readback(rb, 4, s);
     PC_HIP(hipStreamSynchronize(s));
     unsigned long long key;
     double st[2];
