@@ -383,7 +383,8 @@ void forward_grid(pc_plan* p, const R* image, cpx<R>* vis_out, bool out_sorted,
 // (rowlist: row, first atom, end; nrows) and their mask.  Pass B is
 // evaluated directly at those rows (forward) or atoms (adjoint), pass A with
 // the mask.  forward_grid_set: out (plan order) = base - Phi_S w (Phi_S w
-// without base), stats as forward_grid's.  adjoint_grid_set: gout[q] =
+// without base; base in plan order when base_sorted, else in caller order),
+// stats as forward_grid's.  adjoint_grid_set: gout[q] =
 // (Phi* vis)[pix[q]] in FP64, vis in plan order.
 struct AtomSet {
   int64_t nS;
@@ -393,7 +394,7 @@ struct AtomSet {
   RowMask rows;
 };
 void forward_grid_set(pc_plan* p, const AtomSet& as, const double* w, const c32* base,
-                      double* stats, c32* out, hipStream_t s);
+                      bool base_sorted, double* stats, c32* out, hipStream_t s);
 void adjoint_grid_set(pc_plan* p, const c32* vis, const AtomSet& as, double* gout,
                       hipStream_t s);
 // Phi_S* (V - Phi_S x) by the set operators above, atoms in caller order

@@ -1830,9 +1830,12 @@ __global__ __launch_bounds__(256) void interp_kernel(GridGeom g, int64_t L,
 // visibilities' footprints reach, into LDS (cells outside the band as zeros;
 // with a periodic band, wrapped), then each thread sums the W x W taps of one
 // visibility at a time from there, rows of taps in the same order as
-// interp_kernel.  With base (plan order, plan-order output), the output is
-// base - Phi x: the residual, in the same FP32 subtraction a separate pass
-// would do; with stats as well, each work item also writes its sums of
+// interp_kernel.  With base (plan-order output), the output is base - Phi x:
+// the residual, in the same FP32 subtraction a separate pass would do.  base is
+// in plan order, or with base_perm in caller order: the gather is a load per
+// visibility issued ahead of its taps and hides behind them (as a pass of its
+// own it was bound by its random 64-byte sectors, 145 us for 8,372,224
+// visibilities).  With stats as well, each work item also writes its sums of
 // |r|^2 and Re(conj(base) r) in FP64 to stats[2 item], [2 item + 1] (threads
 // combined in a fixed order).
 constexpr int kInterpThreads = 256;
@@ -1850,6 +1853,7 @@ __global__ __launch_bounds__(kInterpThreads) void interp_lds_kernel(GridGeom g,
                                                         const c32* __restrict__ grid,
                                                         const int32_t* __restrict__ perm,
                                                         const c32* __restrict__ base,
+                                                        const int32_t* __restrict__ base_perm,
                                                         c32* __restrict__ out,
                                                         double* __restrict__ stats) {
   using C = InterpCfg<W>;
@@ -1876,8 +1880,13 @@ __global__ __launch_bounds__(kInterpThreads) void interp_lds_kernel(GridGeom g,
   const float c1 = c0 / R;
   const int ou = g.u0 + ru0, ov = g.v0 + rv0;
   double r2 = 0.0, vr = 0.0;
+  // a caller-order base's source index one visibility ahead of its use
+  int src = base_perm && it.beg + tid < it.end ? base_perm[it.beg + tid] : 0;
   for (int sidx = it.beg + tid; sidx < it.end; sidx += kInterpThreads) {
     const uint32_t c = cell[sidx];
+    c32 v{0.f, 0.f};
+    if (base) v = base[base_perm ? src : sidx];
+    if (base_perm && sidx + kInterpThreads < it.end) src = base_perm[sidx + kInterpThreads];
     const int x = cell_u(c) - ou, y = cell_v(c) - ov;  // in [0, kTile)
     const float2 o = reinterpret_cast<const float2*>(off)[sidx];
     float ku[W];
@@ -1900,7 +1909,6 @@ __global__ __launch_bounds__(kInterpThreads) void interp_lds_kernel(GridGeom g,
     }
     ay = __uint_as_float(__float_as_uint(ay) ^ (c & kFlip));  // conjugate if flipped
     if (base) {
-      const c32 v = base[sidx];
       const c32 r = {v.x - ax, v.y - ay};
       out[sidx] = r;
       r2 += (double)r.x * r.x + (double)r.y * r.y;
@@ -2071,7 +2079,7 @@ static void launch_spread(pc_plan* p, const cpx<R>* vals, const int32_t* perm, h
 
 template <typename R, int W>
 static void launch_interp_w(pc_plan* p, const int32_t* perm, cpx<R>* out, hipStream_t s,
-                            const cpx<R>* base, double* stats) {
+                            const cpx<R>* base, const int32_t* base_perm, double* stats) {
   const double rb = sizeof(R);
   ProfScope ps(p, s, "interp", p->L * (4 + 4 * rb + (base ? 2 * rb : 0)) +
                                    2 * rb * p->g.nu * p->g.nv, (double)p->L);
@@ -2079,7 +2087,7 @@ static void launch_interp_w(pc_plan* p, const int32_t* perm, cpx<R>* out, hipStr
     hipLaunchKernelGGL((interp_lds_kernel<W>), dim3((unsigned)p->n_interp), dim3(kInterpThreads),
                        0, s, p->g,
                        p->interp, p->cell, (const float*)p->off, (const c32*)p->grid, perm,
-                       (const c32*)base, (c32*)out, base ? stats : nullptr);
+                       (const c32*)base, base_perm, (c32*)out, base ? stats : nullptr);
   } else {
     if (base) fail(PC_ERR_UNSUPPORTED, "FP64 interpolation with a base");
     const unsigned nb = (unsigned)((p->L + 255) / 256);
@@ -2091,11 +2099,12 @@ static void launch_interp_w(pc_plan* p, const int32_t* perm, cpx<R>* out, hipStr
 
 template <typename R>
 static void launch_interp(pc_plan* p, const int32_t* perm, cpx<R>* out, hipStream_t s,
-                          const cpx<R>* base = nullptr, double* stats = nullptr) {
+                          const cpx<R>* base = nullptr, const int32_t* base_perm = nullptr,
+                          double* stats = nullptr) {
   switch (p->g.W) {
 #define PC_W(w) \
   case w:       \
-    launch_interp_w<R, w>(p, perm, out, s, base, stats); \
+    launch_interp_w<R, w>(p, perm, out, s, base, base_perm, stats); \
     break;
     PC_W(2) PC_W(3) PC_W(4) PC_W(5) PC_W(6) PC_W(7) PC_W(8) PC_W(9) PC_W(10) PC_W(11) PC_W(12)
     PC_W(13) PC_W(14) PC_W(15) PC_W(16)
@@ -2322,7 +2331,7 @@ static void dispatch_M(pc_plan* p, bool adjoint, R* img_out, const R* img_in, R 
 
 
 void forward_grid_set(pc_plan* p, const AtomSet& as, const double* w, const c32* base,
-                      double* stats, c32* out, hipStream_t s) {
+                      bool base_sorted, double* stats, c32* out, hipStream_t s) {
   if (p->Cw || p->precision != PC_PREC_FP32)
     fail(PC_ERR_UNSUPPORTED, "gridded set operators need a coplanar FP32 plan");
   const GridGeom& g = p->g;
@@ -2339,7 +2348,7 @@ void forward_grid_set(pc_plan* p, const AtomSet& as, const double* w, const c32*
     PC_LAUNCH_CHECK("rows_fwd_direct");
   }
   dispatch_M<float>(p, false, nullptr, nullptr, 1.0f, s, nullptr, &as.rows, false);
-  launch_interp<float>(p, nullptr, out, s, base, stats);
+  launch_interp<float>(p, nullptr, out, s, base, base && !base_sorted ? p->perm : nullptr, stats);
 }
 
 void adjoint_grid_set(pc_plan* p, const c32* vis, const AtomSet& as, double* gout,
@@ -2362,7 +2371,7 @@ void adjoint_grid_set(pc_plan* p, const c32* vis, const AtomSet& as, double* gou
 
 // Small moves of the gridded restricted gradient: caller-order atoms into
 // pixel order (weights widened to FP64), the gradient back, and visibilities
-// between caller and plan order.
+// from plan to caller order.
 __global__ void atoms_to_set_kernel(int64_t nS, const int32_t* __restrict__ order,
                                     const float* __restrict__ weight, double* __restrict__ w) {
   const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -2372,11 +2381,6 @@ __global__ void set_to_atoms_kernel(int64_t nS, const int32_t* __restrict__ orde
                                     const double* __restrict__ g, double* __restrict__ grad) {
   const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (q < nS) grad[order[q]] = g[q];
-}
-__global__ void vis_to_plan_kernel(int64_t L, const int32_t* __restrict__ perm,
-                                   const c32* __restrict__ in, c32* __restrict__ out) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < L) out[k] = in[perm[k]];
 }
 __global__ void vis_to_caller_kernel(int64_t L, const int32_t* __restrict__ perm,
                                      const c32* __restrict__ in, c32* __restrict__ out) {
@@ -2416,12 +2420,12 @@ void restricted_gradient_grid(pc_plan* p, const c32* vis, int64_t natoms, const 
     mask[i >> 5] |= 1u << (i & 31);
   }
   const int64_t nrows = (int64_t)rl.size() / 3;
-  // device scratch: [pixel-order pix | order | rows | mask | w | g | V in plan order]
+  // device scratch: [pixel-order pix | order | rows | mask | w | g]
   auto al = [](size_t b) { return (b + 255) / 256 * 256; };
   const size_t o_ord = al(natoms * 4), o_rows = o_ord + al(natoms * 4);
   const size_t o_mask = o_rows + al(nrows * 12), o_w = o_mask + al(words * 4);
-  const size_t o_g = o_w + al(natoms * 8), o_v = o_g + al(natoms * 8);
-  const size_t total = o_v + al(L * sizeof(c32));
+  const size_t o_g = o_w + al(natoms * 8);
+  const size_t total = o_g + al(natoms * 8);
   unsigned char* d = (unsigned char*)ensure_atom_scratch(p, total);
   std::vector<unsigned char> up(o_w);
   for (int64_t q = 0; q < natoms; ++q) ((int32_t*)up.data())[q] = hp[order[q]];
@@ -2438,11 +2442,8 @@ void restricted_gradient_grid(pc_plan* p, const c32* vis, int64_t natoms, const 
   const AtomSet as{natoms, (const int32_t*)d, (const int3*)(d + o_rows), nrows,
                    RowMask{(const uint32_t*)(d + o_mask), nrows, (const uint32_t*)(d + o_mask)}};
   // r = V - Phi_S x in plan order, then Phi_S* r
-  c32* vp = (c32*)(d + o_v);
   c32* r = (c32*)p->vis_scratch;
-  hipLaunchKernelGGL(vis_to_plan_kernel, dim3(lb), dim3(256), 0, s, L, p->perm, vis, vp);
-  PC_LAUNCH_CHECK("vis_to_plan");
-  forward_grid_set(p, as, w, vp, nullptr, r, s);
+  forward_grid_set(p, as, w, vis, false, nullptr, r, s);
   adjoint_grid_set(p, r, as, g, s);
   hipLaunchKernelGGL(set_to_atoms_kernel, dim3(ab), dim3(256), 0, s, natoms, dord, g, grad);
   PC_LAUNCH_CHECK("set_to_atoms");
@@ -2550,7 +2551,7 @@ void forward_grid(pc_plan* p, const R* image, cpx<R>* vis_out, bool out_sorted, 
          "the gridded forward operator needs a coplanar plan (w = 0); the direct sums take w");
   if (base && !out_sorted) fail(PC_ERR_INVALID_ARG, "forward_grid: a base needs plan order");
   dispatch_M<R>(p, false, nullptr, image, R(1), s, nullptr, rows);
-  launch_interp<R>(p, out_sorted ? nullptr : p->perm, vis_out, s, base, stats);
+  launch_interp<R>(p, out_sorted ? nullptr : p->perm, vis_out, s, base, nullptr, stats);
 }
 
 // ----------------------------------------------------------------------------

@@ -495,7 +495,7 @@ struct Pfw {
       k_fill(p, N, 0.0f, dimg.ptr, s);
     } else {  // (the residual and its statistics formed by the interpolation itself)
       if (base) red_partial.ensure(2 * std::max<int64_t>(k_resid_blocks(L), p->n_interp));
-      forward_grid_set(p, atom_set(nS), w, base ? V.ptr : nullptr,
+      forward_grid_set(p, atom_set(nS), w, base ? V.ptr : nullptr, true,
                        base ? red_partial.ptr : nullptr, out, s);
       resid_parts = base ? p->n_interp : 0;
       return;
