@@ -340,8 +340,8 @@ __device__ __forceinline__ cpx<float> root64() {
   return {(float)c[K], SIGN > 0 ? (float)sn[K] : (float)-sn[K]};
 }
 
-// Residue s: y[k3] = X[S (t + 256 k3) + s] from the inputs x[r] of slots
-// t + 256 r.  buf is free on entry (every earlier read of it behind a
+// Residue s: y[k3] = X[S (t + 256 k3) + s], k3 < 4 or k3 >= 12 (the central
+// frequencies), from the inputs x[r] of slots t + 256 r.  buf is free on entry (every earlier read of it behind a
 // barrier); its last reads, of residue s, are not followed by one.
 template <int S, int s, int SIGN>
 __device__ __forceinline__ void reg_fft(const cpx<float> (&x)[16], cpx<float> (&y)[16],
@@ -378,6 +378,105 @@ __device__ __forceinline__ void reg_fft(const cpx<float> (&x)[16], cpx<float> (&
     if (SIGN < 0) u.y = -u.y;
     dft_tw<float, 16, SIGN>(y, u);
   }
+  // (the central outputs are formed here, not sunk into the caller's
+  // conditional stores with all their inputs alive until then)
+#pragma unroll
+  for (int k = 0; k < 16; ++k)
+    if (k < 4 || k >= 12) asm volatile("" : "+v"(y[k].x), "+v"(y[k].y));
+}
+
+// exp(SIGN 2 pi i K / 64), any K >= 0
+template <int K, int SIGN>
+__device__ __forceinline__ cpx<float> root64_any() {
+  constexpr double c[17] = {1.0, 0.99518472667219688624, 0.98078528040323044913,
+                            0.95694033573220886494, 0.92387953251128675613,
+                            0.88192126434835502971, 0.83146961230254523708,
+                            0.77301045336273696081, 0.70710678118654752440,
+                            0.63439328416364549822, 0.55557023301960222474,
+                            0.47139673682599764856, 0.38268343236508977173,
+                            0.29028467725446236764, 0.19509032201612826785,
+                            0.09801714032956060199, 0.0};
+  constexpr int q = K & 63, h = q >> 4, r = q & 15;
+  constexpr double a = c[r], b = c[16 - r];  // cos, sin of the angle within its quadrant
+  constexpr double x = h == 0 ? a : (h == 1 ? -b : (h == 2 ? -a : b));
+  constexpr double y = h == 0 ? b : (h == 1 ? a : (h == 2 ? -b : -a));
+  return {(float)x, (float)(SIGN > 0 ? y : -y)};
+}
+
+// The transposed transform: input on the n = 2048 S central frequencies
+// c = S k + s of a length-M sequence, outputs in the window of 4096 slots
+// centred on M / 2.  X[f] = sum_s w^(s f) Y_s[f mod 4096], Y_s the 4096-point
+// transform of residue s, whose input holds k = t + 256 r (mod 4096) for
+// r < 4 and r >= 12: thread t passes x[q] of k + 1024 = t + 256 q, q < 8.
+// Adds residue s into acc[k3], the output of slot t + 256 k3.
+template <int SIGN>
+__device__ __forceinline__ void dft16_central(const cpx<float> (&x)[8], cpx<float> (&y)[16]) {
+  // inputs r = 0..3 are x[4..7], r = 12..15 x[0..3], the others zero: one
+  // decimation step leaves two 8-point transforms
+  cpx<float> p[8], m[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const cpx<float> v = i < 4 ? x[i + 4] : x[i - 4];
+    p[i] = v;
+    m[i] = rot<float, 16, SIGN>(i < 4 ? v : cpx<float>{-v.x, -v.y}, i);
+  }
+  dft<float, 8, SIGN>(p);
+  dft<float, 8, SIGN>(m);
+#pragma unroll
+  for (int f = 0; f < 8; ++f) {
+    y[2 * f] = p[f];
+    y[2 * f + 1] = m[f];
+  }
+}
+
+template <int S, int s, int SIGN, int K3>
+__device__ __forceinline__ void reg_accumulate(cpx<float> (&acc)[16], const cpx<float> (&y)[16],
+                                               cpx<float> u) {
+  if constexpr (K3 < 16) {
+    if constexpr (s == 0) {
+      acc[K3] = y[K3];
+    } else {
+      // w^(s f): f = t + 256 k3 + 4096 m, m = S / 2 at or above M / 2, else one less
+      constexpr int m = K3 < 8 ? S / 2 : S / 2 - 1;
+      const cpx<float> w = cmul(u, root64_any<(4 * s / S) * K3 + 64 * s * m / S, SIGN>());
+      acc[K3].x = fmar(-w.y, y[K3].y, fmar(w.x, y[K3].x, acc[K3].x));
+      acc[K3].y = fmar(w.y, y[K3].x, fmar(w.x, y[K3].y, acc[K3].y));
+    }
+    reg_accumulate<S, s, SIGN, K3 + 1>(acc, y, u);
+  }
+}
+
+template <int S, int s, int SIGN>
+__device__ __forceinline__ void reg_fft_central(const cpx<float> (&x)[8], cpx<float> (&acc)[16],
+                                                cpx<float>* __restrict__ buf,
+                                                const cpx<float>* __restrict__ tws) {
+  constexpr int M = kRegN * S;
+  const int t = (int)threadIdx.x, lo = t & 15, hi = t >> 4;
+  cpx<float> y[16];
+  auto tw = [&](int k) {
+    cpx<float> u = twiddle<float, M>(tws, k);
+    if (SIGN < 0) u.y = -u.y;
+    return u;
+  };
+  dft16_central<SIGN>(x, y);
+#pragma unroll
+  for (int k = 0; k < 16; ++k) buf[17 * t + k] = y[k];
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < 16; ++r) y[r] = buf[17 * (hi + 16 * r) + lo];
+  dft_tw<float, 16, SIGN>(y, tw(16 * S * lo));
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 16; ++k) buf[272 * hi + lo + 16 * k] = y[k];
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < 16; ++r) y[r] = buf[272 * r + t];
+  dft_tw<float, 16, SIGN>(y, tw(S * t));
+  reg_accumulate<S, s, SIGN, 0>(acc, y, s == 0 ? cpx<float>{1.f, 0.f} : tw(s * t));
+  // (the sums are formed here, not sunk into a caller's conditional stores with
+  // every residue's outputs alive until then)
+#pragma unroll
+  for (int k = 0; k < 16; ++k) asm volatile("" : "+v"(acc[k].x), "+v"(acc[k].y));
 }
 
 }  // namespace pc

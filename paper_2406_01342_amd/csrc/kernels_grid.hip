@@ -1000,14 +1000,14 @@ __device__ __forceinline__ void passA_reg_body(const GridGeom& g, const c32* __r
 }
 
 template <int S, bool MASKED>
-__global__ __launch_bounds__(kRegT, S == 4 ? 3 : 4) void passA_adj_reg_kernel(
+__global__ __launch_bounds__(kRegT, 4) void passA_adj_reg_kernel(
     GridGeom g, const c32* __restrict__ grid, const uint8_t* __restrict__ tile_flags,
     c32* __restrict__ H, const c32* __restrict__ tw, const uint32_t* __restrict__ rows) {
   passA_reg_body<S>(g, grid, tile_flags, H, tw, xcd_local(blockIdx.x, gridDim.x), rows);
 }
 
 template <int S>
-__global__ __launch_bounds__(kRegT, S == 4 ? 3 : 4) void passA_reg_batch_kernel(const AdjJob* __restrict__ jobs,
+__global__ __launch_bounds__(kRegT, 4) void passA_reg_batch_kernel(const AdjJob* __restrict__ jobs,
                                                                    const int2* __restrict__ items) {
   const int2 it = items[xcd_local(blockIdx.x, gridDim.x)];
   const AdjJob& J = jobs[it.x];
@@ -1506,7 +1506,7 @@ __device__ __forceinline__ void passB_reg_body(const GridGeom& g, const c32* __r
 }
 
 template <int S, bool MASKED>
-__global__ __launch_bounds__(kRegT, S == 4 ? 3 : 4) void passB_adj_reg_kernel(
+__global__ __launch_bounds__(kRegT, 4) void passB_adj_reg_kernel(
     GridGeom g, const c32* __restrict__ H, float* __restrict__ image, const c32* __restrict__ tw,
     const float* __restrict__ corr, float scale, unsigned long long* __restrict__ maxkey,
     int positive, const uint32_t* __restrict__ rows) {
@@ -1515,7 +1515,7 @@ __global__ __launch_bounds__(kRegT, S == 4 ? 3 : 4) void passB_adj_reg_kernel(
 }
 
 template <int S>
-__global__ __launch_bounds__(kRegT, S == 4 ? 3 : 4) void passB_reg_batch_kernel(const AdjJob* __restrict__ jobs,
+__global__ __launch_bounds__(kRegT, 4) void passB_reg_batch_kernel(const AdjJob* __restrict__ jobs,
                                                                    const int2* __restrict__ items) {
   const int2 it = items[xcd_local(blockIdx.x, gridDim.x)];
   const AdjJob& J = jobs[it.x];
@@ -1779,6 +1779,128 @@ __global__ __launch_bounds__(NT) void passA_fwd_kernel(GridGeom g, const cpx<R>*
     if (row < nv) grid[(size_t)row * nu + (f - u0)] = v;
   };
   lds_fft_store<R, M, NB, NT, -1, first_radix(M)>(buf, tws, keep, store);
+}
+
+// The forward passes by register-held transforms (FP32, M = 4096 S), for the
+// bands of the adjoint's: pass B^T one pair of image rows per workgroup, its
+// completed spectrum taken apart through LDS; pass A^T one band row.
+template <int S, int E, typename Load>  // E residues at a time; x[e][q]: residue
+__device__ __forceinline__ void reg_central_all(  // s0 + e of k + 1024 = t + 256 q
+    c32 (&acc)[16], c32* __restrict__ buf, const c32* __restrict__ tws, Load load) {
+  auto group = [&](auto s0) {
+    c32 x[E][8];
+    load(x, (int)s0);
+    if constexpr (s0 > 0) __syncthreads();
+    reg_fft_central<S, s0, -1>(x[0], acc, buf, tws);
+    if constexpr (E == 2) {
+      __syncthreads();
+      reg_fft_central<S, s0 + 1, -1>(x[1], acc, buf, tws);
+    }
+  };
+  group(std::integral_constant<int, 0>{});
+  if constexpr (S > 1 && E == 1) group(std::integral_constant<int, 1>{});
+  if constexpr (S == 4) group(std::integral_constant<int, 2>{});
+  if constexpr (S == 4 && E == 1) group(std::integral_constant<int, 3>{});
+}
+
+template <int S, bool MASKED>
+__global__ __launch_bounds__(kRegT, 4) void passB_fwd_reg_kernel(
+    GridGeom g, const float* __restrict__ image, c32* __restrict__ H, const c32* __restrict__ tw,
+    const float* __restrict__ corr, const uint32_t* __restrict__ rows) {
+  constexpr int M = kRegN * S, n = M / 2;
+  __shared__ c32 buf[kRegBuf];
+  __shared__ c32 tws[tw_count(M)];
+  const int t = (int)threadIdx.x, i0 = 2 * xcd_local(blockIdx.x, gridDim.x);
+  // with a row mask, pairs of zero rows write nothing (pass A reads those
+  // columns of H as zeros), and the rows cleared are not read
+  const bool set0 = !rows || row_set(rows, i0), set1 = !rows || row_set(rows, i0 + 1);
+  if (!set0 && !set1) return;  // the whole workgroup
+  load_twiddles<float, M, kRegT>(tws, tw);
+  const float dl = (float)g.dl;
+  const float l0 = (float)(i0 - n / 2) * dl, l1 = (float)(i0 + 1 - n / 2) * dl;
+  const float c0 = corr[i0], c1 = corr[i0 + 1];
+  const float* row0 = image + (size_t)i0 * n;
+  const float* row1 = row0 + n;
+  auto pixel = [&](float a, float b, float cj, int j) {
+    const float mm = (float)(j - n / 2) * dl;
+    return c32{a * c0 * cj * __builtin_amdgcn_rsqf(1.0f - l0 * l0 - mm * mm),
+               b * c1 * cj * __builtin_amdgcn_rsqf(1.0f - l1 * l1 - mm * mm)};
+  };
+  c32 acc[16];
+  constexpr int E = S == 1 ? 1 : 2;
+  reg_central_all<S, E>(acc, buf, tws, [&](c32 (&x)[E][8], int s0) {
+    float2 a[8], b[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int j = S * (t + kRegT * q) + s0;
+      a[q] = b[q] = make_float2(0.f, 0.f);
+      if constexpr (S == 1) {
+        if (set0) a[q].x = row0[j];
+        if (set1) b[q].x = row1[j];
+      } else {
+        if (set0) a[q] = *reinterpret_cast<const float2*>(row0 + j);
+        if (set1) b[q] = *reinterpret_cast<const float2*>(row1 + j);
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int j = S * (t + kRegT * q) + s0;
+      x[0][q] = pixel(a[q].x, b[q].x, corr[j], j);
+      if constexpr (S > 1) x[1][q] = pixel(a[q].y, b[q].y, corr[j + 1], j + 1);
+    }
+  });
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 16; ++k) buf[pidx(t + kRegT * k)] = acc[k];
+  __syncthreads();
+  c32* hcol = H + h_col<M>(i0, g.nv);
+  for (int rel = t; rel < g.nv; rel += kRegT) {
+    const int c = g.v0 + rel;
+    const c32 z = buf[pidx(c & (kRegN - 1))], w = buf[pidx(-c & (kRegN - 1))];
+    *reinterpret_cast<cpair<float>*>(hcol + (size_t)rel * khb_for<M>()) =
+        cpair<float>{{0.5f * (z.x + w.x), 0.5f * (z.y - w.y)},
+                     {0.5f * (z.y + w.y), 0.5f * (w.x - z.x)}};
+  }
+}
+
+template <int S, bool MASKED>
+__global__ __launch_bounds__(kRegT, 4) void passA_fwd_reg_kernel(
+    GridGeom g, const c32* __restrict__ H, c32* __restrict__ grid, const c32* __restrict__ tw,
+    const uint32_t* __restrict__ rows) {
+  constexpr int M = kRegN * S;
+  __shared__ c32 buf[kRegBuf];
+  __shared__ c32 tws[tw_count(M)];
+  __shared__ uint32_t smask[kMaxRowWords];
+  rows_to_lds<kRegT>(smask, rows, g.n);
+  load_twiddles<float, M, kRegT>(tws, tw);  // (its barrier also covers the mask)
+  const int t = (int)threadIdx.x, row = xcd_local(blockIdx.x, gridDim.x), nv = g.nv;
+  // H column i is image row i: zero, and not read, when the mask clears it
+  auto set = [&](int i) { return !rows || row_set(smask, i); };
+  c32 acc[16];
+  reg_central_all<S, 1>(acc, buf, tws, [&](c32 (&x)[1][8], int s0) {
+    // columns 256 S apart are a constant stride apart.  One residue at a time,
+    // and (opaque) its loads behind the transforms of the one before: more in
+    // flight leaves too few registers.
+    const c32* col = H;
+    asm volatile("" : "+s"(col));
+    const size_t lane = h_index<M>(row, S * t + s0, nv), step = (size_t)(S == 1 ? 256 : 512) * nv;
+    bool ok[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      ok[q] = set(S * (t + kRegT * q) + s0);
+      x[0][q] = col[ok[q] ? lane + q * step : 0];
+    }
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      if (!ok[q]) x[0][q] = {0.f, 0.f};
+  });
+  const int u0 = g.u0, nu = g.nu;
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    const int c = t + kRegT * k;
+    const int rel = (S == 1 ? c : M / 2 + (k < 8 ? c : c - kRegN)) - u0;
+    if ((unsigned)rel < (unsigned)nu) grid[(size_t)row * nu + rel] = acc[k];
+  }
 }
 
 // Interpolation: V_k = sum of w x w taps of the fine grid (type-2 gather).
@@ -2271,6 +2393,22 @@ static void run_passes_fwd(pc_plan* p, const R* image, hipStream_t s,
   const double nvr = (double)g.nv * nr * CB;
   if (pass_b) {  // (else the caller has written the pass-A buffer's columns)
     ProfScope ps(p, s, rows ? "passB_fwd_rows" : "passB_fwd", nvr + nr * g.n * sizeof(R), nr * M);
+    bool done = false;
+    if constexpr (sizeof(R) == 4 && reg_size(M)) {
+      if (reg_passB(g)) {
+        constexpr int S = M / kRegN;
+        if (rows)
+          hipLaunchKernelGGL((passB_fwd_reg_kernel<S, true>), dim3(g.n / 2), dim3(kRegT), 0, s, g,
+                             image, (c32*)p->H, (const c32*)p->twiddle, (const float*)p->corr,
+                             bits);
+        else
+          hipLaunchKernelGGL((passB_fwd_reg_kernel<S, false>), dim3(g.n / 2), dim3(kRegT), 0, s, g,
+                             image, (c32*)p->H, (const c32*)p->twiddle, (const float*)p->corr,
+                             nullptr);
+        done = true;
+      }
+    }
+    if (!done) {
 #define PC_PASS_BF(MASKED)                                                                      \
   set_lds((const void*)passB_fwd_kernel<R, M, NBB, NTB, MASKED>, ldb);                          \
   hipLaunchKernelGGL((passB_fwd_kernel<R, M, NBB, NTB, MASKED>), dim3((M / 4) / NBB), dim3(NTB), \
@@ -2282,10 +2420,25 @@ static void run_passes_fwd(pc_plan* p, const R* image, hipStream_t s,
       PC_PASS_BF(false);
     }
 #undef PC_PASS_BF
+    }
     PC_LAUNCH_CHECK("passB_fwd");
   }
   ProfScope ps(p, s, rows ? "passA_fwd_rows" : "passA_fwd", (double)g.nv * g.nu * CB + nvr,
                (double)g.nv * M);
+  bool done = false;
+  if constexpr (sizeof(R) == 4 && reg_size(M)) {
+    if (reg_passA(g)) {
+      constexpr int S = M / kRegN;
+      if (rows)
+        hipLaunchKernelGGL((passA_fwd_reg_kernel<S, true>), dim3(g.nv), dim3(kRegT), 0, s, g,
+                           (const c32*)p->H, (c32*)p->grid, (const c32*)p->twiddle, cols);
+      else
+        hipLaunchKernelGGL((passA_fwd_reg_kernel<S, false>), dim3(g.nv), dim3(kRegT), 0, s, g,
+                           (const c32*)p->H, (c32*)p->grid, (const c32*)p->twiddle, nullptr);
+      done = true;
+    }
+  }
+  if (!done) {
 #define PC_PASS_AF(MASKED)                                                                      \
   set_lds((const void*)passA_fwd_kernel<R, M, NBA, NTA, MASKED>, lda);                          \
   hipLaunchKernelGGL((passA_fwd_kernel<R, M, NBA, NTA, MASKED>), dim3((g.nv + NBA - 1) / NBA),  \
@@ -2297,6 +2450,7 @@ static void run_passes_fwd(pc_plan* p, const R* image, hipStream_t s,
     PC_PASS_AF(false);
   }
 #undef PC_PASS_AF
+  }
   PC_LAUNCH_CHECK("passA_fwd");
 }
 
