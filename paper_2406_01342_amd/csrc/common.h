@@ -343,8 +343,12 @@ DictSpec make_dict(int n_scales, const double* sigma, const double* gamma);
 // out[s][i][j] = sum_{a,b} g_s[a][b] img[i + a][j + b] (zero outside), the
 // adjoint of the cropped synthesis, with the fused maximum key of |out| (of
 // max(out, 0) with positive) over the flat index s n^2 + i n + j in *key.
+// done >= 0: that scale's image is written already (img is then its own place
+// in out) and *key holds its maximum, indices from its first pixel.
 void dict_analysis(pc_plan* p, const DictSpec& D, const float* img, float* out, bool positive,
-                   unsigned long long* key, hipStream_t s);
+                   unsigned long long* key, hipStream_t s, int done = -1);
+// The first scale that is the image itself (sigma = 0, gamma = 1), or -1.
+int dict_identity_scale(const DictSpec& D);
 // img += sum_q w_q g_{s_q} centred on p_q (atoms[q] = s_q n^2 + p_q), cropped.
 void dict_synthesis(pc_plan* p, const DictSpec& D, int64_t nS, const int32_t* atoms,
                     const double* w, float* img, hipStream_t s);
