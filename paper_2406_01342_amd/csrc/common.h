@@ -170,6 +170,9 @@ __host__ __device__ inline double n_minus_one(double l, double m) {
 // the band the kernel is designed for at upsampling 2.
 struct WStack {
   int nplanes = 0;  // 0: coplanar plan
+  // Planes worked on together, each with its own band, pass-A buffer and
+  // partial tiles: a plane's kernels alone leave most of the device idle.
+  int together = 1;
   double w0 = 0, dw = 0;
   double cmid = 0;
   int nquad = 0;    // Gauss-Legendre nodes on [0, 1] of the Psi integral
@@ -261,7 +264,7 @@ struct pc_plan {
   void* vis_scratch = nullptr;  // complex [L] in plan order (residual etc.)
   unsigned long long* key_host = nullptr;  // pinned slot that maxkey_read reads back into
   pc::WStack ws;                // w-stacking planes (nplanes 0: coplanar)
-  void* wvals = nullptr;        // complex [L]: one plane's weighted visibilities
+  void* wvals = nullptr;        // complex [together][L]: the planes' weighted visibilities
   double* wquad = nullptr;      // [2 nquad] doubles: Psi's Chebyshev series (kPsiCheb terms)
   void* atom_scratch = nullptr; // per-atom staging
   size_t atom_capacity = 0;

@@ -599,16 +599,24 @@ __device__ __forceinline__ void spread_quad_body(
   }
 }
 
+// Element strides between the buffers of w-planes worked on together
+// (blockIdx.y, or blockIdx.z of the fold, is the plane; one plane otherwise).
+struct PlaneStride {
+  size_t vals, grid, partials, H;
+};
+
 template <int W>
 __global__ __launch_bounds__(64 * kSpreadQuad) void spread_quad_kernel(
     GridGeom g, const SpreadChunk* __restrict__ chunks, const uint32_t* __restrict__ cell,
     const float* __restrict__ off, const cpx<float>* __restrict__ vals,
     const int32_t* __restrict__ perm, cpx<float>* __restrict__ grid,
-    cpx<float>* __restrict__ partials, unsigned long long* __restrict__ maxkey) {
+    cpx<float>* __restrict__ partials, unsigned long long* __restrict__ maxkey,
+    PlaneStride ps) {
   // the image maximum that the last pass accumulates starts from zero
-  if (blockIdx.x == 0 && threadIdx.x == 0) *maxkey = 0ull;
-  spread_quad_body<W>(g, chunks + (size_t)kSpreadQuad * blockIdx.x, cell, off, vals, perm, grid,
-                      partials);
+  if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *maxkey = 0ull;
+  spread_quad_body<W>(g, chunks + (size_t)kSpreadQuad * blockIdx.x, cell, off,
+                      vals + blockIdx.y * ps.vals, perm, grid + blockIdx.y * ps.grid,
+                      partials + blockIdx.y * ps.partials);
 }
 
 // One launch over the workgroups of several plans: items[b] = (job, group).
@@ -686,8 +694,10 @@ template <typename R>
 __global__ __launch_bounds__(64 * kFoldSub) void fold_kernel(GridGeom g,
                                                            const FoldItem* __restrict__ items,
                                                            const cpx<R>* __restrict__ partials,
-                                                           cpx<R>* __restrict__ grid) {
-  fold_body<R>(g, items[blockIdx.x], partials, grid);
+                                                           cpx<R>* __restrict__ grid,
+                                                           PlaneStride ps) {
+  fold_body<R>(g, items[blockIdx.x], partials + blockIdx.z * ps.partials,
+               grid + blockIdx.z * ps.grid);
 }
 
 __global__ __launch_bounds__(64 * kFoldSub) void fold_batch_kernel(
@@ -917,9 +927,10 @@ __global__ __launch_bounds__(NT) void passA_adj_kernel(GridGeom g, const cpx<R>*
                                                         const uint8_t* __restrict__ tile_flags,
                                                         cpx<R>* __restrict__ H,
                                                         const cpx<R>* __restrict__ tw,
-                                                        const uint32_t* __restrict__ rows) {
-  passA_adj_body<R, M, NB, NT>(g, grid, tile_flags, H, tw, xcd_local(blockIdx.x, gridDim.x),
-                               rows);
+                                                        const uint32_t* __restrict__ rows,
+                                                        PlaneStride ps) {
+  passA_adj_body<R, M, NB, NT>(g, grid + blockIdx.y * ps.grid, tile_flags, H + blockIdx.y * ps.H,
+                               tw, xcd_local(blockIdx.x, gridDim.x), rows);
 }
 
 // Two adjacent columns of the pass-A buffer at one band row.
@@ -1002,8 +1013,10 @@ __device__ __forceinline__ void passA_reg_body(const GridGeom& g, const c32* __r
 template <int S, bool MASKED>
 __global__ __launch_bounds__(kRegT, 4) void passA_adj_reg_kernel(
     GridGeom g, const c32* __restrict__ grid, const uint8_t* __restrict__ tile_flags,
-    c32* __restrict__ H, const c32* __restrict__ tw, const uint32_t* __restrict__ rows) {
-  passA_reg_body<S>(g, grid, tile_flags, H, tw, xcd_local(blockIdx.x, gridDim.x), rows);
+    c32* __restrict__ H, const c32* __restrict__ tw, const uint32_t* __restrict__ rows,
+    PlaneStride ps) {
+  passA_reg_body<S>(g, grid + blockIdx.y * ps.grid, tile_flags, H + blockIdx.y * ps.H, tw,
+                    xcd_local(blockIdx.x, gridDim.x), rows);
 }
 
 template <int S>
@@ -1026,28 +1039,23 @@ __device__ __forceinline__ unsigned long long max_key(float a, int idx) {
   return ((unsigned long long)__float_as_uint(a) << 32) | (unsigned long long)(0xffffffffu - (unsigned)idx);
 }
 
-// One w-plane of the w-stacked adjoint: its position, the phase reference
-// c_mid, and whether it is the first plane (which writes instead of adding).
+// Consecutive w-planes of the w-stacked adjoint: the position of the first,
+// the spacing, the phase reference c_mid, their number, the stride of their
+// pass-A buffers, and whether the first of them is the first of all (which
+// writes instead of adding).
 struct WPlane {
-  double wj, cmid;
-  int first;
+  double w0, dw, cmid;
+  int first, count;
+  size_t H;
 };
 
-// Pass B of a w-plane: NB image rows i; FFT along v of H[:, i] (the whole
-// plane: the rotation makes the transform's outputs complex), correction,
-// rotation by the plane's phase, and the real part added into the image rows.
 template <typename R, int M, int NB, int NT>
-__device__ __forceinline__ void passB_adj_w_body(const GridGeom& g, const cpx<R>* __restrict__ H,
-                                                 R* __restrict__ image,
-                                                 const cpx<R>* __restrict__ tw,
-                                                 const R* __restrict__ corr, R scale, int iblock,
-                                                 WPlane wp) {
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  cpx<R>* buf = reinterpret_cast<cpx<R>*>(smem_raw);
-  __shared__ cpx<R> tws[tw_count(M)];
+__device__ __forceinline__ void passB_adj_w_plane(const GridGeom& g, const cpx<R>* __restrict__ H,
+                                                  R* __restrict__ image, cpx<R>* buf,
+                                                  const cpx<R>* tws, const R* __restrict__ corr,
+                                                  R scale, int i0, double wj, double cmid,
+                                                  bool first) {
   constexpr int n = M / 2;
-  const int i0 = iblock * NB;
-  load_twiddles<R, M, NT>(tws, tw);
   // element (m, b): band row m - v0 of column i0 + b of the pass-A buffer,
   // whose KHB-wide column blocks are row-major over the band rows
   static_assert((NB & (NB - 1)) == 0 && NT % NB == 0, "pass-B layout");
@@ -1120,13 +1128,13 @@ __device__ __forceinline__ void passB_adj_w_body(const GridGeom& g, const cpx<R>
     const int j = f < n / 2 ? f + n / 2 : f - M + n / 2;
     const R l = (R)(i - n / 2) * dl, mm = (R)(j - n / 2) * dl;
     const R inv_n = __builtin_amdgcn_rsqf(R(1) - l * l - mm * mm);
-    double th = wp.wj * (n_minus_one((double)(i - n / 2) * g.dl, (double)(j - n / 2) * g.dl) -
-                         wp.cmid);
+    double th = wj * (n_minus_one((double)(i - n / 2) * g.dl, (double)(j - n / 2) * g.dl) -
+                         cmid);
     th -= rint(th);
     const R sn = (R)__builtin_amdgcn_sinf((float)th), cs = (R)__builtin_amdgcn_cosf((float)th);
     const R val = (v.x * cs - v.y * sn) * (corr[i] * scale) * corr[j] * inv_n;
     R* dst = image + (size_t)i * n + j;
-    *dst = wp.first ? val : *dst + val;
+    *dst = first ? val : *dst + val;
   };
   if constexpr (RAD0 <= 4) {
     if (pruned)
@@ -1135,6 +1143,29 @@ __device__ __forceinline__ void passB_adj_w_body(const GridGeom& g, const cpx<R>
       lds_fft_store<R, M, NB, NT, +1>(buf, tws, keep, store);
   } else {
     lds_fft_store<R, M, NB, NT, +1>(buf, tws, keep, store);
+  }
+}
+
+// Pass B of w-planes: NB image rows i; for each plane in order, FFT along v of
+// H[:, i] (the whole plane: the rotation makes the transform's outputs
+// complex), correction, rotation by the plane's phase, and the real part added
+// into the image rows (by the same thread each time).
+template <typename R, int M, int NB, int NT>
+__device__ __forceinline__ void passB_adj_w_body(const GridGeom& g, const cpx<R>* __restrict__ H,
+                                                 R* __restrict__ image,
+                                                 const cpx<R>* __restrict__ tw,
+                                                 const R* __restrict__ corr, R scale, int iblock,
+                                                 WPlane wp) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  cpx<R>* buf = reinterpret_cast<cpx<R>*>(smem_raw);
+  __shared__ cpx<R> tws[tw_count(M)];
+  constexpr int n = M / 2;
+  const int i0 = iblock * NB;
+  load_twiddles<R, M, NT>(tws, tw);
+  for (int plane = 0; plane < wp.count; ++plane) {
+    if (plane > 0) __syncthreads();  // the last plane's reads of the buffer
+    passB_adj_w_plane<R, M, NB, NT>(g, H + plane * wp.H, image, buf, tws, corr, scale, i0,
+                                    wp.w0 + plane * wp.dw, wp.cmid, wp.first && plane == 0);
   }
 }
 
@@ -1532,32 +1563,41 @@ __global__ __launch_bounds__(NT) void passB_adj_w_kernel(GridGeom g, const cpx<R
                                  xcd_local(blockIdx.x, gridDim.x), wp);
 }
 
-// Visibility weights of w-plane w_j (plan order): h_k exp(2 pi i w_k c_mid)
-// psi((w_k - w_j) / dw) within the kernel's reach |w_k - w_j| <= (W/2) dw,
-// zero beyond it; a visibility with w_k < 0 enters as its conjugate at -w_k
-// (the plan grids it at (-u, -v)).  perm: NULL when h is in plan order.
+// Visibility weights of the w-planes w_j = w0 + j dw, j < count (plan order):
+// h_k exp(2 pi i w_k c_mid) psi((w_k - w_j) / dw) within the kernel's reach
+// |w_k - w_j| <= (W/2) dw, zero beyond it; a visibility with w_k < 0 enters as
+// its conjugate at -w_k (the plan grids it at (-u, -v)).  perm: NULL when h is
+// in plan order.  One thread forms a visibility's values for every plane.
 __global__ __launch_bounds__(256) void wplane_kernel(int64_t L, const double* __restrict__ Cw,
                                                      const cpx<float>* __restrict__ h,
-                                                     const int32_t* __restrict__ perm, double wj,
-                                                     double inv_dw, double cmid, float R2,
-                                                     float c1, float c0,
+                                                     const int32_t* __restrict__ perm, WPlane wp,
+                                                     double inv_dw, float R2, float c1, float c0,
                                                      cpx<float>* __restrict__ out) {
   const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= L) return;
   const double wk = fabs(Cw[k]);
-  const float t = (float)((wk - wj) * inv_dw);
-  cpx<float> o{0.f, 0.f};
-  if (t * t <= R2) {
-    cpx<float> v = h[perm ? perm[k] : k];
-    if (Cw[k] < 0.0) v.y = -v.y;
-    double ph = wk * cmid;
+  const float t0 = (float)((wk - wp.w0) * inv_dw);
+  cpx<float> v{0.f, 0.f};
+  // (a margin for the rounding of the plane's own distance below)
+  const float reach = __builtin_amdgcn_sqrtf(R2) + 1e-3f;
+  if (t0 >= -reach && t0 <= (float)(wp.count - 1) + reach) {
+    const cpx<float> x = h[perm ? perm[k] : k];
+    const float y = Cw[k] < 0.0 ? -x.y : x.y;
+    double ph = wk * wp.cmid;
     ph -= rint(ph);
     const float sn = __builtin_amdgcn_sinf((float)ph), cs = __builtin_amdgcn_cosf((float)ph);
-    const float q = fmaxf(fmaf(-t, t, R2), 0.0f);
-    const float psi = __builtin_amdgcn_exp2f(fmaf(c1, __builtin_amdgcn_sqrtf(q), -c0));
-    o = {psi * (v.x * cs - v.y * sn), psi * (v.x * sn + v.y * cs)};
+    v = {x.x * cs - y * sn, x.x * sn + y * cs};
   }
-  out[k] = o;
+  for (int j = 0; j < wp.count; ++j) {
+    const float t = (float)((wk - (wp.w0 + j * wp.dw)) * inv_dw);
+    cpx<float> o{0.f, 0.f};
+    if (t * t <= R2) {
+      const float q = fmaxf(fmaf(-t, t, R2), 0.0f);
+      const float psi = __builtin_amdgcn_exp2f(fmaf(c1, __builtin_amdgcn_sqrtf(q), -c0));
+      o = {psi * v.x, psi * v.y};
+    }
+    out[(size_t)j * L + k] = o;
+  }
 }
 
 // Last step of the w-stacked adjoint: image /= Psi(dw c') per pixel, and
@@ -2150,18 +2190,25 @@ static double spread_bytes(const pc_plan* p, double rb) {
   return p->L * 4.0 * rb + 2.0 * rb * p->g.nu * p->g.nv;
 }
 
+static PlaneStride plane_stride(const pc_plan* p) {
+  const GridGeom& g = p->g;
+  return PlaneStride{(size_t)p->L, (size_t)g.nu * g.nv, (size_t)p->n_partials * kTile * kTile,
+                     (size_t)g.nv * g.n};
+}
+
 template <typename R, int W>
-static void launch_spread_w(pc_plan* p, const cpx<R>* vals, const int32_t* perm, hipStream_t s) {
+static void launch_spread_w(pc_plan* p, const cpx<R>* vals, const int32_t* perm, hipStream_t s,
+                            int planes) {
   const double rb = sizeof(R);
-  ProfScope ps(p, s, "spread", spread_bytes(p, rb), (double)p->L);
+  ProfScope ps(p, s, "spread", planes * spread_bytes(p, rb), planes * (double)p->L);
   if constexpr (sizeof(R) == 4) {
     if (!p->spread_quads) fail(PC_ERR_DEVICE, "spread: the plan's work list is not grouped");
     constexpr size_t lds = SpreadM::lds_bytes;
     static_assert(lds <= 64 * 1024, "grouped spread LDS budget");
-    hipLaunchKernelGGL((spread_quad_kernel<W>), dim3((unsigned)(p->n_chunks / kSpreadQuad)),
+    hipLaunchKernelGGL((spread_quad_kernel<W>), dim3((unsigned)(p->n_chunks / kSpreadQuad), (unsigned)planes),
                        dim3(64 * kSpreadQuad), lds, s, p->g, p->chunks, p->cell,
                        (const float*)p->off, vals, perm, (c32*)p->grid, (c32*)p->partials,
-                       p->maxkey);
+                       p->maxkey, plane_stride(p));
   } else {
     constexpr size_t lds = SpreadCfg<R, W>::lds_bytes;
     static_assert(lds <= 160 * 1024, "spread LDS budget");
@@ -2177,11 +2224,12 @@ static void launch_spread_w(pc_plan* p, const cpx<R>* vals, const int32_t* perm,
 }
 
 template <typename R>
-static void launch_spread(pc_plan* p, const cpx<R>* vals, const int32_t* perm, hipStream_t s) {
+static void launch_spread(pc_plan* p, const cpx<R>* vals, const int32_t* perm, hipStream_t s,
+                          int planes = 1) {
   switch (p->g.W) {
 #define PC_W(w) \
   case w:       \
-    launch_spread_w<R, w>(p, vals, perm, s); \
+    launch_spread_w<R, w>(p, vals, perm, s, planes); \
     break;
     PC_W(2) PC_W(3) PC_W(4) PC_W(5) PC_W(6) PC_W(7) PC_W(8) PC_W(9) PC_W(10) PC_W(11) PC_W(12)
     PC_W(13) PC_W(14) PC_W(15) PC_W(16)
@@ -2191,10 +2239,12 @@ static void launch_spread(pc_plan* p, const cpx<R>* vals, const int32_t* perm, h
   }
   if (p->n_fold > 0) {
     const double tb = 2.0 * sizeof(R) * kTile * kTile;
-    ProfScope ps(p, s, "fold", tb * (p->n_partials + p->n_fold), (double)p->n_partials);
-    hipLaunchKernelGGL((fold_kernel<R>), dim3((unsigned)p->n_fold, kTile * kTile / 64),
+    ProfScope ps(p, s, "fold", planes * tb * (p->n_partials + p->n_fold),
+                 planes * (double)p->n_partials);
+    hipLaunchKernelGGL((fold_kernel<R>),
+                       dim3((unsigned)p->n_fold, kTile * kTile / 64, (unsigned)planes),
                        dim3(64 * kFoldSub), 0, s, p->g, p->fold,
-                       (const cpx<R>*)p->partials, (cpx<R>*)p->grid);
+                       (const cpx<R>*)p->partials, (cpx<R>*)p->grid, plane_stride(p));
     PC_LAUNCH_CHECK("fold");
   }
 }
@@ -2297,8 +2347,9 @@ static void run_passes_adj(pc_plan* p, R* image, R scale, hipStream_t s,
   const double nr = rows ? (double)rows->count : (double)g.n;
   const double nvr = (double)g.nv * nr * CB;
   {
-    ProfScope ps(p, s, rows ? "passA_adj_rows" : "passA_adj", (double)g.nv * g.nu * CB + nvr,
-                 (double)g.nv * M);
+    const unsigned planes = wp ? (unsigned)wp->count : 1u;
+    ProfScope ps(p, s, rows ? "passA_adj_rows" : "passA_adj",
+                 planes * ((double)g.nv * g.nu * CB + nvr), planes * (double)g.nv * M);
     bool passA_done = false;
     if constexpr (sizeof(R) == 4 && reg_size(M)) {
       if (reg_passA(g)) {
@@ -2306,20 +2357,20 @@ static void run_passes_adj(pc_plan* p, R* image, R scale, hipStream_t s,
         if (rows)
           hipLaunchKernelGGL((passA_adj_reg_kernel<S, true>), dim3(g.nv), dim3(kRegT), 0, s, g,
                              (const c32*)p->grid, p->tile_flags, (c32*)p->H,
-                             (const c32*)p->twiddle, cols);
+                             (const c32*)p->twiddle, cols, plane_stride(p));
         else
-          hipLaunchKernelGGL((passA_adj_reg_kernel<S, false>), dim3(g.nv), dim3(kRegT), 0, s, g,
-                             (const c32*)p->grid, p->tile_flags, (c32*)p->H,
-                             (const c32*)p->twiddle, nullptr);
+          hipLaunchKernelGGL((passA_adj_reg_kernel<S, false>), dim3(g.nv, planes), dim3(kRegT), 0,
+                             s, g, (const c32*)p->grid, p->tile_flags, (c32*)p->H,
+                             (const c32*)p->twiddle, nullptr, plane_stride(p));
         passA_done = true;
       }
     }
     if (!passA_done) {
 #define PC_PASS_A(MASKED)                                                                      \
       set_lds((const void*)passA_adj_kernel<R, M, NBA, NTA, MASKED>, lda);                         \
-  hipLaunchKernelGGL((passA_adj_kernel<R, M, NBA, NTA, MASKED>), dim3((g.nv + NBA - 1) / NBA), \
+  hipLaunchKernelGGL((passA_adj_kernel<R, M, NBA, NTA, MASKED>), dim3((g.nv + NBA - 1) / NBA, planes), \
                      dim3(NTA), lda, s, g, (const cpx<R>*)p->grid, p->tile_flags,              \
-                     (cpx<R>*)p->H, (const cpx<R>*)p->twiddle, cols)
+                     (cpx<R>*)p->H, (const cpx<R>*)p->twiddle, cols, plane_stride(p))
     if (rows) {
       PC_PASS_A(true);
     } else {
@@ -2336,8 +2387,9 @@ static void run_passes_adj(pc_plan* p, R* image, R scale, hipStream_t s,
       constexpr int NTW = nt_for<NBW * M / 16>();
       const size_t ldw = (size_t)padded(NBW * M) * CB;
       set_lds((const void*)passB_adj_w_kernel<R, M, NBW, NTW>, ldw);
-      ProfScope ps(p, s, "passB_adj_w", nvn + (double)g.n * g.n * sizeof(R) * (wp->first ? 1 : 2),
-                   (double)g.n * M);
+      ProfScope ps(p, s, "passB_adj_w",
+                   wp->count * nvn + (double)g.n * g.n * sizeof(R) * (wp->first ? 1 : 2),
+                   wp->count * (double)g.n * M);
       hipLaunchKernelGGL((passB_adj_w_kernel<R, M, NBW, NTW>), dim3((M / 2) / NBW), dim3(NTW),
                          ldw, s, g, (const cpx<R>*)p->H, image, (const cpx<R>*)p->twiddle,
                          (const R*)p->corr, scale, *wp);
@@ -2662,16 +2714,17 @@ static void adjoint_grid_w(pc_plan* p, const c32* vis, bool vis_sorted, float* i
   const float R = 0.5f * (float)p->g.W;
   const float c0 = (float)(p->g.beta64 * 1.4426950408889634);  // beta log2(e)
   const unsigned nb = (unsigned)((p->L + 255) / 256);
-  for (int j = 0; j < ws.nplanes; ++j) {
-    const WPlane wp{ws.w0 + j * ws.dw, ws.cmid, j == 0 ? 1 : 0};
+  for (int j = 0; j < ws.nplanes; j += ws.together) {
+    const int count = std::min(ws.together, ws.nplanes - j);
+    const WPlane wp{ws.w0 + j * ws.dw, ws.dw, ws.cmid, j == 0 ? 1 : 0, count, plane_stride(p).H};
     {
-      ProfScope ps(p, s, "wplane", p->L * 24.0, (double)p->L);
+      ProfScope ps(p, s, "wplane", p->L * (16.0 + 8.0 * count), (double)p->L * count);
       hipLaunchKernelGGL(wplane_kernel, dim3(nb), dim3(256), 0, s, p->L, p->Cw, vis,
-                         vis_sorted ? nullptr : p->perm, wp.wj, 1.0 / ws.dw, ws.cmid, R * R,
-                         c0 / R, c0, (c32*)p->wvals);
+                         vis_sorted ? nullptr : p->perm, wp, 1.0 / ws.dw, R * R, c0 / R, c0,
+                         (c32*)p->wvals);
       PC_LAUNCH_CHECK("wplane");
     }
-    launch_spread<float>(p, (const c32*)p->wvals, nullptr, s);  // also clears the max key
+    launch_spread<float>(p, (const c32*)p->wvals, nullptr, s, count);  // also clears the max key
     dispatch_M<float>(p, true, image, nullptr, scale, s, &wp);
   }
   const int64_t N = (int64_t)p->g.n * p->g.n;

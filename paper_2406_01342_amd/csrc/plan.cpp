@@ -240,6 +240,8 @@ struct Layout {
   std::vector<int32_t> group_work;      // per workgroup: its longest item's visibilities
 };
 
+static int planes_together(const Layout& lay);
+
 static double kernel_beta(int W) { return 2.30 * W; }
 
 // Entries of the FFT's two-level twiddle table (matches the kernels' layout).
@@ -640,6 +642,7 @@ static Layout build_layout(const pc_geometry* geo, bool full) {
       for (int w = 0; w < G; ++w) lay.chunks.push_back(gr.c[w]);
       lay.group_work.push_back((int32_t)gr.work);
     }
+    if (lay.ws.nplanes > 0) lay.ws.together = planes_together(lay);
     return lay;
   }
   // One wave per item (FP64 plans).  Split tiles whose
@@ -741,6 +744,19 @@ static std::vector<double> correction_table(const GridGeom& g) {
   return c;
 }
 
+// Planes of a w-stacked adjoint worked on together: at most eight (the
+// launches are full by then), in groups of even size, and no more than
+// kWGroupBytes of per-plane buffers.
+constexpr size_t kWGroupBytes = size_t(512) << 20;
+static int planes_together(const Layout& lay) {
+  const GridGeom& g = lay.g;
+  const size_t each = 8 * ((size_t)g.nu * g.nv + (size_t)g.nv * g.n + (size_t)lay.L +
+                           (size_t)lay.n_partials * kTile * kTile);
+  const int most = (int)std::max<size_t>(1, std::min<size_t>(8, kWGroupBytes / each));
+  const int groups = (lay.ws.nplanes + most - 1) / most;
+  return (lay.ws.nplanes + groups - 1) / groups;
+}
+
 static size_t layout_bytes(const Layout& lay, int prec) {
   const GridGeom& g = lay.g;
   const size_t cb = prec == PC_PREC_FP64 ? 16 : 8, rb = cb / 2;
@@ -754,16 +770,17 @@ static size_t layout_bytes(const Layout& lay, int prec) {
   add(lay.fold.size() * sizeof(FoldItem));
   add(lay.tile_flags.size());
   add(lay.interp.size() * sizeof(InterpItem));
-  add((size_t)g.nu * g.nv * cb);             // grid band
-  add((size_t)g.nv * g.n * cb);              // H
-  add((size_t)lay.n_partials * kTile * kTile * cb);
+  const size_t planes = (size_t)lay.ws.together;
+  add(planes * g.nu * g.nv * cb);            // grid band
+  add(planes * g.nv * g.n * cb);             // H
+  add(planes * lay.n_partials * kTile * kTile * cb);
   add((size_t)twiddle_entries(g.M) * cb);    // twiddles
   add((size_t)g.n * rb);                     // correction
   add(256 + 8 * kMaxRowWords);               // max key, row mask and its row pairs
   add(lay.L * cb);                           // vis scratch
   if (lay.ws.nplanes > 0) {
     add(lay.L * 8);                          // w
-    add(lay.L * cb);                         // one plane's weighted visibilities
+    add(planes * lay.L * cb);                // the planes' weighted visibilities
     add((size_t)lay.ws.nquad * 16);          // Psi quadrature
   }
   return b;
@@ -819,9 +836,10 @@ extern "C" pc_status pc_plan_create_impl(const pc_geometry* geom, void* stream, 
     p->fold = (FoldItem*)dalloc(p, lay.fold.size() * sizeof(FoldItem));
     p->tile_flags = (uint8_t*)dalloc(p, lay.tile_flags.size());
     p->interp = (InterpItem*)dalloc(p, lay.interp.size() * sizeof(InterpItem));
-    p->grid = dalloc(p, (size_t)g.nu * g.nv * cb);
-    p->H = dalloc(p, (size_t)g.nv * g.n * cb);
-    p->partials = dalloc(p, (size_t)lay.n_partials * kTile * kTile * cb);
+    const size_t planes = (size_t)lay.ws.together;
+    p->grid = dalloc(p, planes * g.nu * g.nv * cb);
+    p->H = dalloc(p, planes * g.nv * g.n * cb);
+    p->partials = dalloc(p, planes * lay.n_partials * kTile * kTile * cb);
     p->twiddle = dalloc(p, (size_t)twiddle_entries(g.M) * cb);
     p->corr = dalloc(p, (size_t)g.n * rb);
     p->maxkey = (unsigned long long*)dalloc(p, 256 + 8 * kMaxRowWords);
@@ -830,7 +848,7 @@ extern "C" pc_status pc_plan_create_impl(const pc_geometry* geom, void* stream, 
     p->ws = lay.ws;
     if (lay.ws.nplanes > 0) {
       p->Cw = (double*)dalloc(p, L * 8);
-      p->wvals = dalloc(p, L * cb);
+      p->wvals = dalloc(p, planes * L * cb);
       p->wquad = (double*)dalloc(p, (size_t)lay.ws.nquad * 16);
     }
 
