@@ -291,14 +291,6 @@ __device__ __forceinline__ void lds_fft_store(cpx<R>* buf, const cpx<R>* tw, Kee
   fft_stages_store<R, M, NB, NT, SIGN, NS>(buf, tw, keep, store, need);
 }
 
-// In-place FFT of NB sequences of length M stored contiguously in LDS, with
-// the twiddle table `tw` in LDS (see load_twiddles).  Must be called by all
-// NT threads of the block; ends with a barrier.
-template <typename R, int M, int NB, int NT, int SIGN>
-__device__ __forceinline__ void lds_fft(cpx<R>* buf, const cpx<R>* tw) {
-  fft_stages<R, M, NB, NT, SIGN, 1>(buf, tw);
-}
-
 // ---------------------------------------------------------------------------
 // Register-held transforms of length M = 4096 S (S = 1, 2, 4) whose input
 // lies in a window of 4096 consecutive slots centred on M / 2 (any 4096 slots

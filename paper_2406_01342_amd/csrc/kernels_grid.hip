@@ -2,26 +2,32 @@
 // forward as type-1 / type-2 non-uniform FFTs).
 //
 // Adjoint (Eq. adjoint-phi) as four launches:
-//   spread   sorted visibilities -> fine-grid band, one workgroup per output
-//            tile (kTile x kTile cells) accumulating in LDS; every band tile is
-//            written exactly once (no global atomics, no zero-fill pass).  Hot
-//            tiles are split into several work items writing partial tiles.
+//   spread   sorted visibilities -> fine-grid band, one wave per work item
+//            and output tile (kTile x kTile cells), accumulated in registers
+//            by matrix instructions in FP32 (SpreadM) and in LDS in FP64
+//            (SpreadCfg); every band tile is written exactly once (no global
+//            atomics, no zero-fill pass).  Hot tiles are split into several
+//            work items writing partial tiles.
 //   fold     sums the partial tiles of split tiles, in a fixed order.
-//   pass A   per band row: inverse FFT of length M along u in LDS, keeping the
-//            n central frequencies (input pruned to the band, output pruned).
-//   pass B   per group of NB image rows: inverse FFT along v in LDS of the
-//            pass-A columns, keeping n frequencies, then the apodisation and
+//   pass A   per band row: inverse FFT of length M along u, keeping the n
+//            central frequencies (input pruned to the band, output pruned).
+//   pass B   per pair of image rows: inverse FFT along v of the pass-A
+//            columns, keeping n frequencies, then the apodisation and
 //            1/n(l, m) correction, the image write and a fused max |eta|.
+// Coplanar plans hold the half plane v >= 0 of the band only, and two real
+// image rows come out of one complex transform (PairGeom).  The transforms
+// run through LDS (fft_lds.h), or, at fine grids 4096 ... 16384 in FP32, in
+// registers (reg_passA, reg_passB).
 // Forward by interpolation (type-2): the same passes transposed with the
 // opposite sign, then a w x w gather per visibility.
 //
 // Non-coplanar baselines (Sect. 2.1, Eq. phi-plane): the adjoint is
-// w-stacked (planes and their kernel in the WStack comment).  Per plane, one
-// small kernel weights the visibilities by the plane's kernel value (zero
-// beyond its reach), the spread and pass A run unchanged, and pass B rotates
-// each output pixel by the plane's phase exp(2 pi i w_j c') and adds the real
-// part into the image; a last kernel divides by Psi(dw c') and takes the
-// maximum.
+// w-stacked (planes and their kernel in the WStack comment), a group of
+// planes at a time.  One small kernel weights the visibilities by the planes'
+// kernel values (zero beyond their reach), the spread, fold and pass A run on
+// all planes of the group in one launch each, and pass B rotates each output
+// pixel by the planes' phases exp(2 pi i w_j c') and adds the real parts into
+// the image; a last kernel divides by Psi(dw c') and takes the maximum.
 #include <algorithm>
 #include <cstring>
 #include <memory>
@@ -747,33 +753,6 @@ __device__ __forceinline__ size_t h_col(int col, int nv) {
 template <int M>
 __device__ __forceinline__ size_t h_index(int row, int col, int nv) {
   return h_col<M>(col, nv) + (size_t)row * khb_for<M>();
-}
-
-// Fills the padded LDS buffer from global memory: element idx (< TOTAL) goes
-// to buf[pidx(lpos(idx))] and is src[addr(idx)], or zero when addr returns a
-// negative value.  Every load of the thread is issued before any result is
-// used (masked elements read a fixed valid address and are zeroed by a
-// select), so the loads are in flight together instead of one round trip per
-// element.
-template <typename R, int TOTAL, int NT, typename A, typename P>
-__device__ __forceinline__ void gather_to_lds(cpx<R>* buf, const cpx<R>* __restrict__ src,
-                                              A addr, P lpos) {
-  constexpr int IT = (TOTAL + NT - 1) / NT;
-  cpx<R> t[IT];
-  int64_t a[IT];
-#pragma unroll
-  for (int it = 0; it < IT; ++it) {
-    const int idx = (int)threadIdx.x + it * NT;
-    a[it] = (TOTAL % NT == 0 || idx < TOTAL) ? addr(idx) : -1;
-  }
-#pragma unroll
-  for (int it = 0; it < IT; ++it) t[it] = src[a[it] >= 0 ? a[it] : 0];
-#pragma unroll
-  for (int it = 0; it < IT; ++it) {
-    const int idx = (int)threadIdx.x + it * NT;
-    if (TOTAL % NT == 0 || idx < TOTAL)
-      buf[pidx(lpos(idx))] = a[it] >= 0 ? t[it] : cpx<R>{R(0), R(0)};
-  }
 }
 
 // Workgroups are dispatched to the 8 XCDs (each with its own L2) in turn:
@@ -2319,6 +2298,9 @@ constexpr int nt_for() {
 // band (pass A), or completed column (pass B), fits their window; wider bands
 // and the other sizes go through the full-length LDS transforms.
 constexpr bool reg_size(int M) { return M == kRegN || M == 2 * kRegN || M == 4 * kRegN; }
+// Fine grid 4096 fits its window whole: FP32 plans need no other passes there.
+template <typename R, int M>
+constexpr bool reg_always = sizeof(R) == 4 && M == kRegN;
 static bool reg_passA(const GridGeom& g) {
   return reg_size(g.M) && reg_window(g.M, g.u0, g.u0 + g.nu);
 }
@@ -2365,17 +2347,19 @@ static void run_passes_adj(pc_plan* p, R* image, R scale, hipStream_t s,
         passA_done = true;
       }
     }
-    if (!passA_done) {
-#define PC_PASS_A(MASKED)                                                                      \
-      set_lds((const void*)passA_adj_kernel<R, M, NBA, NTA, MASKED>, lda);                         \
-  hipLaunchKernelGGL((passA_adj_kernel<R, M, NBA, NTA, MASKED>), dim3((g.nv + NBA - 1) / NBA, planes), \
-                     dim3(NTA), lda, s, g, (const cpx<R>*)p->grid, p->tile_flags,              \
-                     (cpx<R>*)p->H, (const cpx<R>*)p->twiddle, cols, plane_stride(p))
-    if (rows) {
-      PC_PASS_A(true);
-    } else {
-      PC_PASS_A(false);
-    }
+    if constexpr (!reg_always<R, M>) {
+#define PC_PASS_A(MASKED)                                                                     \
+  set_lds((const void*)passA_adj_kernel<R, M, NBA, NTA, MASKED>, lda);                        \
+  hipLaunchKernelGGL((passA_adj_kernel<R, M, NBA, NTA, MASKED>),                              \
+                     dim3((g.nv + NBA - 1) / NBA, planes), dim3(NTA), lda, s, g,              \
+                     (const cpx<R>*)p->grid, p->tile_flags, (cpx<R>*)p->H,                    \
+                     (const cpx<R>*)p->twiddle, cols, plane_stride(p))
+      if (passA_done) {
+      } else if (rows) {
+        PC_PASS_A(true);
+      } else {
+        PC_PASS_A(false);
+      }
 #undef PC_PASS_A
     }
     PC_LAUNCH_CHECK("passA_adj");
@@ -2420,13 +2404,15 @@ static void run_passes_adj(pc_plan* p, R* image, R scale, hipStream_t s,
   hipLaunchKernelGGL((passB_adj_kernel<R, M, NBB, NTB, MASKED>), dim3((M / 4) / NBB), dim3(NTB), \
                      ldb, s, g, (const cpx<R>*)p->H, image, (const cpx<R>*)p->twiddle,          \
                      (const R*)p->corr, scale, rows ? nullptr : p->maxkey, p->max_positive, bits)
-  if (rows) {
-    PC_PASS_B(true);
-  } else {
-    PC_PASS_B(false);
+  if constexpr (!reg_always<R, M>) {
+    if (rows) {
+      PC_PASS_B(true);
+    } else {
+      PC_PASS_B(false);
+    }
+    PC_LAUNCH_CHECK("passB_adj");
   }
 #undef PC_PASS_B
-  PC_LAUNCH_CHECK("passB_adj");
 }
 
 template <typename R, int M>
@@ -2460,17 +2446,18 @@ static void run_passes_fwd(pc_plan* p, const R* image, hipStream_t s,
         done = true;
       }
     }
-    if (!done) {
+    if constexpr (!reg_always<R, M>) {
 #define PC_PASS_BF(MASKED)                                                                      \
   set_lds((const void*)passB_fwd_kernel<R, M, NBB, NTB, MASKED>, ldb);                          \
   hipLaunchKernelGGL((passB_fwd_kernel<R, M, NBB, NTB, MASKED>), dim3((M / 4) / NBB), dim3(NTB), \
                      ldb, s, g, image, (cpx<R>*)p->H, (const cpx<R>*)p->twiddle,                \
                      (const R*)p->corr, bits)
-    if (rows) {
-      PC_PASS_BF(true);
-    } else {
-      PC_PASS_BF(false);
-    }
+      if (done) {
+      } else if (rows) {
+        PC_PASS_BF(true);
+      } else {
+        PC_PASS_BF(false);
+      }
 #undef PC_PASS_BF
     }
     PC_LAUNCH_CHECK("passB_fwd");
@@ -2490,17 +2477,18 @@ static void run_passes_fwd(pc_plan* p, const R* image, hipStream_t s,
       done = true;
     }
   }
-  if (!done) {
+  if constexpr (!reg_always<R, M>) {
 #define PC_PASS_AF(MASKED)                                                                      \
   set_lds((const void*)passA_fwd_kernel<R, M, NBA, NTA, MASKED>, lda);                          \
   hipLaunchKernelGGL((passA_fwd_kernel<R, M, NBA, NTA, MASKED>), dim3((g.nv + NBA - 1) / NBA),  \
                      dim3(NTA), lda, s, g, (const cpx<R>*)p->H, (cpx<R>*)p->grid,               \
                      (const cpx<R>*)p->twiddle, cols)
-  if (rows) {
-    PC_PASS_AF(true);
-  } else {
-    PC_PASS_AF(false);
-  }
+    if (done) {
+    } else if (rows) {
+      PC_PASS_AF(true);
+    } else {
+      PC_PASS_AF(false);
+    }
 #undef PC_PASS_AF
   }
   PC_LAUNCH_CHECK("passA_fwd");
@@ -2777,8 +2765,7 @@ struct PassShape {
 int passA_blocks(int M, int nv) {
   switch (M) {
 #define PC_M(m) case m: return (nv + PassShape<m>::NBA - 1) / PassShape<m>::NBA;
-    PC_M(32) PC_M(64) PC_M(128) PC_M(256) PC_M(512) PC_M(1024) PC_M(2048) PC_M(4096) PC_M(8192)
-    PC_M(16384)
+    PC_M(32) PC_M(64) PC_M(128) PC_M(256) PC_M(512) PC_M(1024) PC_M(2048) PC_M(8192) PC_M(16384)
 #undef PC_M
   }
   return 0;
@@ -2787,8 +2774,7 @@ int passA_blocks(int M, int nv) {
 int passB_blocks(int M) {
   switch (M) {
 #define PC_M(m) case m: return (m / 4) / PassShape<m>::NBB;
-    PC_M(32) PC_M(64) PC_M(128) PC_M(256) PC_M(512) PC_M(1024) PC_M(2048) PC_M(4096) PC_M(8192)
-    PC_M(16384)
+    PC_M(32) PC_M(64) PC_M(128) PC_M(256) PC_M(512) PC_M(1024) PC_M(2048) PC_M(8192) PC_M(16384)
 #undef PC_M
   }
   return 0;
@@ -2832,8 +2818,7 @@ void pass_batch(int M, bool reg, bool passA, const AdjJob* jobs, const int2* ite
     }
   switch (M) {
 #define PC_M(m) case m: launch_pass_batch<m>(passA, jobs, items, nitems, s); return;
-    PC_M(32) PC_M(64) PC_M(128) PC_M(256) PC_M(512) PC_M(1024) PC_M(2048) PC_M(4096) PC_M(8192)
-    PC_M(16384)
+    PC_M(32) PC_M(64) PC_M(128) PC_M(256) PC_M(512) PC_M(1024) PC_M(2048) PC_M(8192) PC_M(16384)
 #undef PC_M
   }
   fail(PC_ERR_UNSUPPORTED, "fine grid size");
