@@ -42,8 +42,8 @@
  *              plan owns its workspace: pc_plan_create allocates what
  *              pc_plan_footprint reports; per-call scratch that depends on the
  *              request (atom tables and partial sums of the direct sums, sized
- *              by the number of atoms; the dirty-image buffer and per-scale
- *              keys of pc_adjoint_grid_ms; the row and atom tables of
+ *              by the number of atoms; the dirty-image buffer (no point scale of
+ *              weight one) and keys of pc_adjoint_grid_ms; the row and atom tables of
  *              pc_restricted_gradient_grid) is added on first use and kept,
  *              and pc_plan_get_info's `footprint` is the total held at the
  *              time.  pc_restricted_gradient_noalloc adds none.
@@ -113,8 +113,8 @@ typedef struct {
   int32_t kernel_width;  /* w, exponential-of-semicircle kernel support       */
   double kernel_beta;    /* beta of phi(z) = exp(beta (sqrt(1 - z^2) - 1))     */
   int32_t band_u0, band_nu; /* occupied fine-grid band along u (cells)        */
-  int32_t band_v0, band_nv; /* occupied fine-grid band along v                */
-  int32_t wraps;         /* 1 if the band is the whole (periodic) grid        */
+  int32_t band_v0, band_nv; /* the same along v (coplanar plans: v >= 0 only)   */
+  int32_t wraps;         /* 1 if footprints cross the periodic grid's edge    */
   int32_t tile;          /* spreading tile side in cells                      */
   int64_t n_tiles;       /* tiles in the band                                 */
   int64_t n_chunks;      /* spreading work items                              */
@@ -153,15 +153,19 @@ PC_API pc_status pc_plan_create(const pc_geometry* geom, void* stream, pc_plan**
  * plan creation allocates (each buffer rounded up to its pool size class).
  * Entry points add per-call scratch on first use and keep it: the atom table
  * (40 bytes per atom), the restricted adjoint's partial sums (at most
- * 8 bytes x atoms x a few hundred) and, for pc_adjoint_grid_ms, one npix^2
- * float image; info.footprint then reports the larger total. */
+ * 8 bytes x atoms x a few hundred) and, for pc_adjoint_grid_ms without a
+ * point scale of weight one, one npix^2 float image; info.footprint then
+ * reports the larger total.  A non-coplanar plan holds the buffers of up to
+ * eight w-planes (at most 512 MiB, at least one plane), and of fewer than
+ * pc_plan_footprint counts where the device has no room for them. */
 PC_API void pc_plan_destroy(pc_plan* plan);
 PC_API pc_status pc_plan_get_info(const pc_plan* plan, pc_plan_info* info);
 
 /* Frees every buffer parked in the device pool of `device` (see
  * pc_plan_destroy), for callers that need the memory elsewhere (another
- * allocator in the process).  hipFree waits for the device.  *released (may
- * be NULL) gets the bytes freed.  Errors: PC_ERR_INVALID_ARG (device < 0),
+ * allocator in the process), and, when no plan holds one, the pinned host
+ * words that maxima are read back into.  hipFree waits for the device.
+ * *released (may be NULL) gets the device bytes freed.  Errors: PC_ERR_INVALID_ARG (device < 0),
  * PC_ERR_DEVICE. */
 PC_API pc_status pc_device_pool_trim(int32_t device, size_t* released);
 

@@ -320,6 +320,13 @@ __device__ __forceinline__ void spread_body(
 // Taps outside the tile (visibilities spilling from a neighbour) go to row 32,
 // which no operand reads.  FP32 products and sums; deterministic (each cell
 // receives its terms in a fixed order).
+//
+// Against the register window of SpreadCfg in FP32 (spread alone): 13.7 -> 5.6 us
+// for 3,968 visibilities on a 256^2 fine grid, 29 -> 22 for 424,800 on 2048^2,
+// 89 -> 63 for 2,088,960 on 8192^2; 8,372,224 on 16384^2 with the fold 255 -> 232.
+// Of 208 us there (plan-order input) 46 go with the matrix instructions, 20
+// with the weights' exponentials and 11 with the clearing, each left out
+// alone: bound by the issue of the staging and the loads together.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 struct SpreadM {
@@ -738,7 +745,7 @@ __device__ __forceinline__ cpx<R> turns_pos(cpx<R> v, int q) {
 // them together).  At the 16384 fine grid, whose pass A stores a thread's
 // columns 4k, 4k + 1 and 4k + 2, 4k + 3 at different times, the pairs of each
 // kind are grouped apart, so that neighbouring lanes fill a block's row at
-// once.
+// once (half-filled lines cost pass A 82 -> 115 us there).
 constexpr int kSplitGrid = 16384;
 template <int M>
 constexpr int khb_for() {
@@ -922,7 +929,11 @@ struct alignas(4 * sizeof(R)) cpair {
 // band row per workgroup, the band within the window of 4096 slots centred on
 // M / 2 (reg_window).  Outputs f = S t + s + 256 S k3 are the columns
 // i = S t + s + 256 S q, q = (k3 + 4) mod 16 < 8; the S residues of a thread
-// are adjacent columns, written two at a time.
+// are adjacent columns, written two at a time.  Four workgroups share a compute
+// unit, so that one's LDS exchanges run under another's arithmetic (the
+// full-length transform's single 1024-thread workgroup alternated): 82 -> 72 us
+// at 16384 (its bytes at the copy rate: 40), 78 -> 51 with a row mask; 31 -> 25 us
+// at 8192, 17 -> 15 at 4096.
 __host__ __device__ constexpr bool reg_window(int M, int lo, int hi) {  // slots [lo, hi)
   return M == kRegN ||
          (M > kRegN && M <= 4 * kRegN && lo >= M / 2 - kRegN / 2 && hi <= M / 2 + kRegN / 2);
@@ -1160,6 +1171,9 @@ __device__ __forceinline__ void passB_adj_w_body(const GridGeom& g, const cpx<R>
 // one of the four cells c, c + M, M - c, 2M - c lies in the band: pair_main
 // names it (rel, and whether its conjugate enters), pair_rest adds the others
 // (called for the few slots where pair_edge says so).
+//
+// 8192^2 image: pass A 150 -> 83 us and pass B 356 -> 232 us against the full
+// plane.
 struct PairGeom {
   int M, v0, nv;
 };
@@ -1378,10 +1392,16 @@ __global__ __launch_bounds__(NT) void passB_adj_kernel(GridGeom g, const cpx<R>*
                                xcd_local(blockIdx.x, gridDim.x), rows);
 }
 
+// Adjacent pixels of a caller's image, at a float's alignment.
+typedef float image2 __attribute__((ext_vector_type(2), aligned(4)));
+typedef float image4 __attribute__((ext_vector_type(4), aligned(4)));
+
 // Pass B of the adjoint by register-held transforms (FP32, M = 4096 S): one
 // pair of image rows per workgroup, the completed column within the window of
 // 4096 slots centred on M / 2.  Thread t holds the pixels j = S t + s + 256 S q
-// (q < 8), two adjacent ones per store.
+// (q < 8), two adjacent ones per store.  231 -> 178 us at 16384 (its bytes at the
+// copy rate: 85), 55 -> 42 at 8192, 33 -> 28 at 4096; bound by the transforms'
+// arithmetic.
 template <int S>
 __device__ __forceinline__ void passB_reg_body(const GridGeom& g, const c32* __restrict__ H,
                                                float* __restrict__ image,
@@ -1479,6 +1499,7 @@ __device__ __forceinline__ void passB_reg_body(const GridGeom& g, const c32* __r
     }
     fold();
   } else {
+    float2 e0[8], e1[8];  // S = 4: the first two pixels of four, until all are formed
     auto pair = [&](auto s0) {
       c32 y0[16], y1[16];
       if constexpr (s0 > 0) __syncthreads();
@@ -1493,8 +1514,18 @@ __device__ __forceinline__ void passB_reg_body(const GridGeom& g, const c32* __r
         float2 p0, p1;
         pixel(y0[k3], j, cj.x, p0.x, p1.x);
         pixel(y1[k3], j + 1, cj.y, p0.y, p1.y);
-        if (set0) *reinterpret_cast<float2*>(row0 + j) = p0;
-        if (set1) *reinterpret_cast<float2*>(row1 + j) = p1;
+        if constexpr (S == 2) {
+          if (set0) *reinterpret_cast<image2*>(row0 + j) = image2{p0.x, p0.y};
+          if (set1) *reinterpret_cast<image2*>(row1 + j) = image2{p1.x, p1.y};
+        } else if constexpr (s0 == 0) {
+          e0[q] = p0;
+          e1[q] = p1;
+        } else {
+          if (set0)
+            *reinterpret_cast<image4*>(row0 + j - 2) = image4{e0[q].x, e0[q].y, p0.x, p0.y};
+          if (set1)
+            *reinterpret_cast<image4*>(row1 + j - 2) = image4{e1[q].x, e1[q].y, p1.x, p1.y};
+        }
       }
       fold();
     };
@@ -1516,7 +1547,7 @@ __device__ __forceinline__ void passB_reg_body(const GridGeom& g, const c32* __r
 }
 
 template <int S, bool MASKED>
-__global__ __launch_bounds__(kRegT, 4) void passB_adj_reg_kernel(
+__global__ __launch_bounds__(kRegT, S == 4 ? 3 : 4) void passB_adj_reg_kernel(
     GridGeom g, const c32* __restrict__ H, float* __restrict__ image, const c32* __restrict__ tw,
     const float* __restrict__ corr, float scale, unsigned long long* __restrict__ maxkey,
     int positive, const uint32_t* __restrict__ rows) {
@@ -1525,7 +1556,7 @@ __global__ __launch_bounds__(kRegT, 4) void passB_adj_reg_kernel(
 }
 
 template <int S>
-__global__ __launch_bounds__(kRegT, 4) void passB_reg_batch_kernel(const AdjJob* __restrict__ jobs,
+__global__ __launch_bounds__(kRegT, S == 4 ? 3 : 4) void passB_reg_batch_kernel(const AdjJob* __restrict__ jobs,
                                                                    const int2* __restrict__ items) {
   const int2 it = items[xcd_local(blockIdx.x, gridDim.x)];
   const AdjJob& J = jobs[it.x];
@@ -1546,7 +1577,9 @@ __global__ __launch_bounds__(NT) void passB_adj_w_kernel(GridGeom g, const cpx<R
 // h_k exp(2 pi i w_k c_mid) psi((w_k - w_j) / dw) within the kernel's reach
 // |w_k - w_j| <= (W/2) dw, zero beyond it; a visibility with w_k < 0 enters as
 // its conjugate at -w_k (the plan grids it at (-u, -v)).  perm: NULL when h is
-// in plan order.  One thread forms a visibility's values for every plane.
+// in plan order.  One thread forms a visibility's values for every plane:
+// its w and value are read once per group (5 -> 1.6 us per plane at 424,800
+// visibilities).
 __global__ __launch_bounds__(256) void wplane_kernel(int64_t L, const double* __restrict__ Cw,
                                                      const cpx<float>* __restrict__ h,
                                                      const int32_t* __restrict__ perm, WPlane wp,
@@ -1840,6 +1873,10 @@ __global__ __launch_bounds__(kRegT, 4) void passB_fwd_reg_kernel(
   const float c0 = corr[i0], c1 = corr[i0 + 1];
   const float* row0 = image + (size_t)i0 * n;
   const float* row1 = row0 + n;
+  auto two = [](const float* at) {
+    const image2 v = *reinterpret_cast<const image2*>(at);
+    return float2{v.x, v.y};
+  };
   auto pixel = [&](float a, float b, float cj, int j) {
     const float mm = (float)(j - n / 2) * dl;
     return c32{a * c0 * cj * __builtin_amdgcn_rsqf(1.0f - l0 * l0 - mm * mm),
@@ -1857,8 +1894,8 @@ __global__ __launch_bounds__(kRegT, 4) void passB_fwd_reg_kernel(
         if (set0) a[q].x = row0[j];
         if (set1) b[q].x = row1[j];
       } else {
-        if (set0) a[q] = *reinterpret_cast<const float2*>(row0 + j);
-        if (set1) b[q] = *reinterpret_cast<const float2*>(row1 + j);
+        if (set0) a[q] = two(row0 + j);
+        if (set1) b[q] = two(row1 + j);
       }
     }
 #pragma unroll

@@ -560,7 +560,9 @@ static Layout build_layout(const pc_geometry* geo, bool full) {
     // than an even share of all the work per resident wave (16 per compute
     // unit), so that no wave outlasts the launch: at most 1024, and at least
     // 64 (32 on a band of few tiles), below which the partial tiles and their
-    // fold cost more than the shorter items give.
+    // fold cost more than the shorter items give.  (Leaving tiles of up to 8 kq
+    // whole, to save partial tiles: 85 -> 137 us for 2,088,960 visibilities on an
+    // 8192^2 grid, whose longest items then end last.)
     constexpr int G = kSpreadQuad;
     int64_t events = 0, occupied = 0;
     for (int64_t t = 0; t < ntiles; ++t) {
@@ -746,7 +748,9 @@ static std::vector<double> correction_table(const GridGeom& g) {
 
 // Planes of a w-stacked adjoint worked on together: at most eight (the
 // launches are full by then), in groups of even size, and no more than
-// kWGroupBytes of per-plane buffers.
+// kWGroupBytes of per-plane buffers.  One plane at a time the launches of a
+// 1024^2 plane end with most compute units idle: 17 planes take 999 us so and
+// 690 us in groups of 6, 6 and 5.
 constexpr size_t kWGroupBytes = size_t(512) << 20;
 static int planes_together(const Layout& lay) {
   const GridGeom& g = lay.g;
@@ -836,21 +840,35 @@ extern "C" pc_status pc_plan_create_impl(const pc_geometry* geom, void* stream, 
     p->fold = (FoldItem*)dalloc(p, lay.fold.size() * sizeof(FoldItem));
     p->tile_flags = (uint8_t*)dalloc(p, lay.tile_flags.size());
     p->interp = (InterpItem*)dalloc(p, lay.interp.size() * sizeof(InterpItem));
-    const size_t planes = (size_t)lay.ws.together;
-    p->grid = dalloc(p, planes * g.nu * g.nv * cb);
-    p->H = dalloc(p, planes * g.nv * g.n * cb);
-    p->partials = dalloc(p, planes * lay.n_partials * kTile * kTile * cb);
     p->twiddle = dalloc(p, (size_t)twiddle_entries(g.M) * cb);
     p->corr = dalloc(p, (size_t)g.n * rb);
     p->maxkey = (unsigned long long*)dalloc(p, 256 + 8 * kMaxRowWords);
     p->rowmask = (uint32_t*)((unsigned char*)p->maxkey + 256);
     p->vis_scratch = dalloc(p, L * cb);
-    p->ws = lay.ws;
     if (lay.ws.nplanes > 0) {
       p->Cw = (double*)dalloc(p, L * 8);
-      p->wvals = dalloc(p, planes * L * cb);
       p->wquad = (double*)dalloc(p, (size_t)lay.ws.nquad * 16);
     }
+    // the buffers of the planes worked on together: of fewer planes where the
+    // device has no room for the group
+    for (const size_t mark = p->owned.size();;) {
+      const size_t planes = (size_t)lay.ws.together;
+      try {
+        p->grid = dalloc(p, planes * g.nu * g.nv * cb);
+        p->H = dalloc(p, planes * g.nv * g.n * cb);
+        p->partials = dalloc(p, planes * lay.n_partials * kTile * kTile * cb);
+        if (lay.ws.nplanes > 0) p->wvals = dalloc(p, planes * L * cb);
+        break;
+      } catch (const Error& e) {
+        if (e.status != PC_ERR_OUT_OF_MEMORY || planes == 1) throw;
+        for (; p->owned.size() > mark; p->owned.pop_back()) {
+          p->footprint -= p->owned.back().bytes;
+          pool_release(p->device, p->owned.back().ptr, p->owned.back().bytes);
+        }
+        lay.ws.together = (lay.ws.together + 1) / 2;
+      }
+    }
+    p->ws = lay.ws;
 
     // Host staging of converted tables; copies complete before return.
     PC_HIP(hipMemcpyAsync(p->perm, lay.perm.data(), L * 4, hipMemcpyHostToDevice, s));

@@ -454,7 +454,10 @@ struct Pfw {
   // gridded operators about 28 ps per visibility (spread or interpolation),
   // 3.4 ps per fine-grid point of the band rows' transforms and 2.7 ps per
   // fine-grid point of the image rows' transforms (at most one row per
-  // atom), plus 15 us of launches.
+  // atom), plus 15 us of launches.  (The register-held passes have since
+  // fallen to about 1.5 ps per point of the band rows at 16384^2, and the half
+  // plane to half the rows: near the line the direct sums, exact up to their
+  // sines, are kept, and the Gram form serves sets that small before either.)
   int64_t grid_crossover() const {
     if (p->Cw) return INT64_MAX / 8;  // no gridded forward with the w-term: direct sums only
     if (prm.grid_atoms > 0) return prm.grid_atoms;
