@@ -64,7 +64,7 @@ KERNEL_SYMBOLS = {
     "adjoint_sparse_acc64": "adjoint_sparse_kernel<float, double, false, false>",
     "psf_sums_acc64": "adjoint_sparse_kernel<float, double, true, false>",
     "spread": "spread_quad_kernel<", "fold": "fold_kernel<float>",
-    "passA_adj": "passA_adj_kernel<float", "passB_adj": "passB_adj_kernel<float",
+    "passA_adj": "passA_adj_reg_kernel<", "passB_adj": "passB_adj_reg_kernel<",
     "dict_analysis": "dict_tile_h_kernel<16>",  # the widest of the paper's scales (sigma 8)
 }
 PROFILES = os.path.join(ROOT, "profiles")

@@ -1399,9 +1399,10 @@ typedef float image4 __attribute__((ext_vector_type(4), aligned(4)));
 // Pass B of the adjoint by register-held transforms (FP32, M = 4096 S): one
 // pair of image rows per workgroup, the completed column within the window of
 // 4096 slots centred on M / 2.  Thread t holds the pixels j = S t + s + 256 S q
-// (q < 8), two adjacent ones per store.  231 -> 178 us at 16384 (its bytes at the
-// copy rate: 85), 55 -> 42 at 8192, 33 -> 28 at 4096; bound by the transforms'
-// arithmetic.
+// (q < 8), stored two adjacent ones at a time, or four at 16384, where two pairs
+// stored apart left the L2 as half lines (523 MB written for 268): 231 -> 178 us
+// there, and 136 in fours (its bytes at the copy rate: 85); 55 -> 42 at 8192,
+// 33 -> 28 at 4096; bound by the transforms' arithmetic.
 template <int S>
 __device__ __forceinline__ void passB_reg_body(const GridGeom& g, const c32* __restrict__ H,
                                                float* __restrict__ image,
