@@ -123,9 +123,10 @@ struct GridGeom {
   // wrap: the band is the whole periodic grid along u, wrapv: along v.
   // Coplanar plans hold the half plane v >= 0 only: the image is real, and
   // Re(h e^{+i t}) = Re(h* e^{-i t}), so a visibility with v < 0 is gridded as
-  // its conjugate at (-u, -v) (kFlip in its cell).  Their band runs from
-  // about M/2 (zero frequency) up to at most M + W/2 and never wraps along v
-  // (cells at M and past it alias cells 0 ... of the periodic transform).
+  // its conjugate at (-u, -v) (kFlip in its cell).  Their band runs from the
+  // tile of the lowest occupied cell (M/2 - W/2 at the least; M/2 is zero
+  // frequency) up to at most M + W/2 and never wraps along v (cells at M and
+  // past it alias cells 0 ... of the periodic transform).
   int32_t wrap, wrapv;
   double dl;       // pixel step (direction cosine)
 };
