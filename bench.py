@@ -51,7 +51,8 @@ KERNEL_FILES = {
     "adjoint_sparse": ["kernels_dft.hip"], "adjoint_sparse_reduce": ["kernels_dft.hip"],
     "forward_sparse": ["kernels_dft.hip"], "forward_adjoint_sparse": ["kernels_dft.hip"],
     "adjoint_sparse_acc64": ["kernels_dft.hip"], "psf_sums_acc64": ["kernels_dft.hip"],
-    "spread": ["kernels_grid.hip", "fft_lds.h"], "fold": ["kernels_grid.hip", "fft_lds.h"],
+    "spread": ["kernels_grid.hip", "es_kernel.h", "fft_lds.h"],
+    "fold": ["kernels_grid.hip", "fft_lds.h"],
     "passA_adj": ["kernels_grid.hip", "fft_lds.h"],
     "passB_adj": ["kernels_grid.hip", "fft_lds.h", "half_plane.h"],
     "dict_analysis": ["kernels_dict.hip"],

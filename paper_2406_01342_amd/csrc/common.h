@@ -64,6 +64,7 @@ using c64 = cpx<double>;
 // cells) therefore touches at most the next tile along each axis.
 constexpr int kTile = 32;
 constexpr int kMaxWidth = 16;
+constexpr double kEsBeta = 2.30;  // the gridding kernel's beta per cell of its width
 
 // Spreading register window (FP64): a wave's lanes cover a spread_span(W)-wide
 // square of cells, the union of the footprints of all visibilities whose
@@ -115,8 +116,7 @@ struct GridGeom {
   int32_t n;       // image side
   int32_t M;       // fine grid side
   int32_t W;       // kernel width
-  float beta;      // kernel shape
-  double beta64;
+  double beta64;   // kernel shape
   int32_t u0, nu;  // band origin / extent along u (cells, multiple of kTile)
   int32_t v0, nv;  // band along v
   int32_t ntu, ntv;

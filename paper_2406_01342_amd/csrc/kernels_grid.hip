@@ -34,23 +34,17 @@
 #include <type_traits>
 
 #include "common.h"
+#include "es_kernel.h"
 #include "fft_lds.h"
 #include "half_plane.h"
 
 namespace pc {
 
-template <typename R>
-__device__ __forceinline__ R es_kernel(R z, R beta) {
-  // exponential of semicircle: exp(beta (sqrt(1 - z^2) - 1)) on |z| < 1
-  R t = R(1) - z * z;
-  if (!(t > R(0))) return R(0);
-  if constexpr (sizeof(R) == 4) {
-    // hardware square root (about 1 ulp): the correctly rounded expansion
-    // costs a dozen more instructions for no gain at this accuracy
-    return __expf(beta * (__builtin_amdgcn_sqrtf(t) - 1.0f));
-  } else {
-    return exp(beta * (sqrt(t) - 1.0));
-  }
+// Exponential of semicircle in FP64, exp(beta (sqrt(1 - z^2) - 1)) on |z| < 1
+// (FP32: es_tap).
+__device__ __forceinline__ double es_kernel(double z, double beta) {
+  const double t = 1.0 - z * z;
+  return t > 0.0 ? exp(beta * (sqrt(t) - 1.0)) : 0.0;
 }
 
 // Tap position relative to an output tile's origin; returns false if the tap
@@ -188,7 +182,7 @@ __device__ __forceinline__ void spread_body(
   const int ov = g.v0 + tv * kTile, ou = g.u0 + tu * kTile;
   const bool single_u = g.wrap && g.M == kTile, single_v = g.wrapv && g.M == kTile;
   const R inv = R(2) / R(W);
-  const R beta = sizeof(R) == 4 ? (R)g.beta : (R)g.beta64;
+  const R beta = g.beta64;
   // cumulative range boundaries
   const int c1 = ch.end[0] - ch.beg[0];
   const int c2 = c1 + ch.end[1] - ch.beg[1];
@@ -235,8 +229,8 @@ __device__ __forceinline__ void spread_body(
       for (int j = 0; j < C::BS; ++j) my[j] = my[C::BS + j] = R(0);
 #pragma unroll
       for (int t = 0; t < W; ++t) {
-        my[dv + t] = es_kernel<R>((nx.sv + R(t)) * inv, beta);
-        my[C::BS + du + t] = es_kernel<R>((nx.su + R(t)) * inv, beta);
+        my[dv + t] = es_kernel((nx.sv + R(t)) * inv, beta);
+        my[C::BS + du + t] = es_kernel((nx.su + R(t)) * inv, beta);
       }
       my[2 * C::BS] = nx.val.x;
       my[2 * C::BS + 1] = nx.cell & kFlip ? -nx.val.y : nx.val.y;
@@ -340,16 +334,6 @@ struct SpreadM {
   static constexpr size_t lds_bytes = kSpreadQuad * sizeof(float) * WAVE_F;
 };
 
-// Exponential-of-semicircle weight of a tap at distance x (cells) from the
-// visibility, in the form the staging evaluates it: with R = W/2,
-// phi = exp(beta (sqrt(1 - (x/R)^2) - 1)) = exp2(c1 sqrt(R^2 - x^2) - c0),
-// c0 = beta log2(e), c1 = c0 / R.  |x| <= R for every tap of a footprint;
-// max(., 0) only absorbs rounding at |x| = R.
-__device__ __forceinline__ float es_weight(float x, float R2, float c1, float c0) {
-  const float q = fmaxf(fmaf(-x, x, R2), 0.0f);
-  return __builtin_amdgcn_exp2f(fmaf(c1, __builtin_amdgcn_sqrtf(q), -c0));
-}
-
 __device__ __forceinline__ void lds_order() {  // a wave's own LDS writes before its reads
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
@@ -376,9 +360,6 @@ __device__ __forceinline__ void spread_group_accumulate(
   const bool single = g.M == kTile && wrap;  // the periodic grid is one tile wide
   const bool periodic = (g.wrap | g.wrapv) != 0;
   const int bside = cols ? 8 : 16;           // the axis's block side
-  constexpr float R = 0.5f * (float)W;
-  const float c0 = g.beta * 1.44269504088896341f;  // beta log2(e)
-  const float c1 = c0 / R;
   const int c1n = ch.end[0] - ch.beg[0];
   const int c2n = c1n + ch.end[1] - ch.beg[1];
   const int c3n = c2n + ch.end[2] - ch.beg[2];
@@ -446,7 +427,7 @@ __device__ __forceinline__ void spread_group_accumulate(
     const int hi = lo + W - 1;
     float w[W];
 #pragma unroll
-    for (int t = 0; t < W; ++t) w[t] = es_weight(rk.off + (float)t, R * R, c1, c0);
+    for (int t = 0; t < W; ++t) w[t] = es_tap<W>(rk.off, t);
     // lanes past the end stage values of zero and reach no block
     const float vr = valid ? rk.val.x : 0.f;
     const float vi = valid ? __uint_as_float(__float_as_uint(rk.val.y) ^ (rk.cell & kFlip)) : 0.f;
@@ -1528,7 +1509,7 @@ __global__ __launch_bounds__(NT) void passB_adj_w_kernel(GridGeom g, const cpx<R
 __global__ __launch_bounds__(256) void wplane_kernel(int64_t L, const double* __restrict__ Cw,
                                                      const cpx<float>* __restrict__ h,
                                                      const int32_t* __restrict__ perm, WPlane wp,
-                                                     double inv_dw, float R2, float c1, float c0,
+                                                     double inv_dw, float R2, float inv_R, float c,
                                                      cpx<float>* __restrict__ out) {
   const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= L) return;
@@ -1549,8 +1530,8 @@ __global__ __launch_bounds__(256) void wplane_kernel(int64_t L, const double* __
     const float t = (float)((wk - (wp.w0 + j * wp.dw)) * inv_dw);
     cpx<float> o{0.f, 0.f};
     if (t * t <= R2) {
-      const float q = fmaxf(fmaf(-t, t, R2), 0.0f);
-      const float psi = __builtin_amdgcn_exp2f(fmaf(c1, __builtin_amdgcn_sqrtf(q), -c0));
+      const float z = t * inv_R;
+      const float psi = es_from_q(fmaf(-z, z, 1.0f), c);
       o = {psi * v.x, psi * v.y};
     }
     out[(size_t)j * L + k] = o;
@@ -1918,16 +1899,16 @@ __global__ __launch_bounds__(256) void interp_kernel(GridGeom g, int64_t L,
   const int cu = cell_u(c), cv = cell_v(c);
   const R su = off[2 * s], sv = off[2 * s + 1];
   const R inv = R(2) / R(W);
-  const R beta = sizeof(R) == 4 ? (R)g.beta : (R)g.beta64;
+  const R beta = g.beta64;
   R ku[W];
 #pragma unroll
-  for (int t = 0; t < W; ++t) ku[t] = es_kernel<R>((su + R(t)) * inv, beta);
+  for (int t = 0; t < W; ++t) ku[t] = es_kernel((su + R(t)) * inv, beta);
   R ax = 0, ay = 0;
   // rows: not fully unrolled (W^2 loads in flight would exhaust registers for
   // wide kernels); the row weight is evaluated in the loop
 #pragma unroll 2
   for (int a = 0; a < W; ++a) {
-    const R kva = es_kernel<R>((sv + R(a)) * inv, beta);
+    const R kva = es_kernel((sv + R(a)) * inv, beta);
     int y = cv + a - g.v0;
     if (g.wrapv && y >= g.M) y -= g.M;
     R rx = 0, ry = 0;
@@ -1998,9 +1979,6 @@ __global__ __launch_bounds__(kInterpThreads) void interp_lds_kernel(GridGeom g,
     reg[y * C::SP + x] = v;
   }
   __syncthreads();
-  constexpr float R = 0.5f * (float)W;
-  const float c0 = g.beta * 1.44269504088896341f;  // beta log2(e)
-  const float c1 = c0 / R;
   const int ou = g.u0 + ru0, ov = g.v0 + rv0;
   double r2 = 0.0, vr = 0.0;
   // a caller-order base's source index one visibility ahead of its use
@@ -2014,12 +1992,12 @@ __global__ __launch_bounds__(kInterpThreads) void interp_lds_kernel(GridGeom g,
     const float2 o = reinterpret_cast<const float2*>(off)[sidx];
     float ku[W];
 #pragma unroll
-    for (int t = 0; t < W; ++t) ku[t] = es_weight(o.x + (float)t, R * R, c1, c0);
+    for (int t = 0; t < W; ++t) ku[t] = es_tap<W>(o.x, t);
     float ax = 0.f, ay = 0.f;
     const float2* rp = reg + y * C::SP + x;
 #pragma unroll
     for (int a = 0; a < W; ++a) {
-      const float kva = es_weight(o.y + (float)a, R * R, c1, c0);
+      const float kva = es_tap<W>(o.y, a);
       float rx = 0.f, ry = 0.f;
 #pragma unroll
       for (int b = 0; b < W; ++b) {
@@ -2682,7 +2660,6 @@ static void adjoint_grid_w(pc_plan* p, const c32* vis, bool vis_sorted, float* i
                            hipStream_t s) {
   const WStack& ws = p->ws;
   const float R = 0.5f * (float)p->g.W;
-  const float c0 = (float)(p->g.beta64 * 1.4426950408889634);  // beta log2(e)
   const unsigned nb = (unsigned)((p->L + 255) / 256);
   for (int j = 0; j < ws.nplanes; j += ws.together) {
     const int count = std::min(ws.together, ws.nplanes - j);
@@ -2690,7 +2667,7 @@ static void adjoint_grid_w(pc_plan* p, const c32* vis, bool vis_sorted, float* i
     {
       ProfScope ps(p, s, "wplane", p->L * (16.0 + 8.0 * count), (double)p->L * count);
       hipLaunchKernelGGL(wplane_kernel, dim3(nb), dim3(256), 0, s, p->L, p->Cw, vis,
-                         vis_sorted ? nullptr : p->perm, wp, 1.0 / ws.dw, R * R, c0 / R, c0,
+                         vis_sorted ? nullptr : p->perm, wp, 1.0 / ws.dw, R * R, 1.0f / R, es_c(p->g.W),
                          (c32*)p->wvals);
       PC_LAUNCH_CHECK("wplane");
     }

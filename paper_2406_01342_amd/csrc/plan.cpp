@@ -242,7 +242,7 @@ struct Layout {
 
 static int planes_together(const Layout& lay);
 
-static double kernel_beta(int W) { return 2.30 * W; }
+static double kernel_beta(int W) { return kEsBeta * W; }
 
 // Entries of the FFT's two-level twiddle table (matches the kernels' layout).
 static int twiddle_entries(int M) { return 64 + std::max(1, M / 64); }
@@ -320,7 +320,6 @@ static Layout build_layout(const pc_geometry* geo, bool full) {
   g.M = M;
   g.W = W;
   g.beta64 = kernel_beta(W);
-  g.beta = (float)g.beta64;
   g.dl = dl;
   lay.L = L;
 

@@ -5,7 +5,8 @@ host-only and checked against the DFT's definition in long double
 the even/odd split shows up as an O(1) error.  And the half plane's index
 arithmetic (half_plane.h) over the bands of plan.cpp's own layout
 (tests/host_fft/half_plane_check.cpp): every row read lies in the band, every
-cell enters each slot it belongs to once."""
+cell enters each slot it belongs to once.  And the FP32 gridding kernel's
+error against FP64 at every width (tests/host_fft/es_kernel_check.cpp)."""
 import os
 import subprocess
 
@@ -32,6 +33,11 @@ def _run(tmp_path, name):
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not available")
 def test_half_plane_reads_its_band(tmp_path):
     _run(tmp_path, "half_plane_check")
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not available")
+def test_gridding_kernel_error(tmp_path):
+    _run(tmp_path, "es_kernel_check")
 
 
 @pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not available")
