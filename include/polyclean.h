@@ -155,9 +155,14 @@ PC_API pc_status pc_plan_create(const pc_geometry* geom, void* stream, pc_plan**
  * (40 bytes per atom), the restricted adjoint's partial sums (at most
  * 8 bytes x atoms x a few hundred) and, for pc_adjoint_grid_ms without a
  * point scale of weight one, one npix^2 float image; info.footprint then
- * reports the larger total.  A non-coplanar plan holds the buffers of up to
- * eight w-planes (at most 512 MiB, at least one plane), and of fewer than
- * pc_plan_footprint counts where the device has no room for them. */
+ * reports the larger total.  A non-coplanar plan holds the buffers of one
+ * w-plane.  The non-coplanar plans of a device further share one workspace, in
+ * which up to eight planes are worked on together: at most 512 MiB per device
+ * however many plans there are, counted in no plan's footprint, held while
+ * such a plan exists and parked in the device pool after the last.  It is given
+ * up where a plan's allocation would otherwise fail, and never needed: calls
+ * without it, and calls on a stream in capture, work plane by plane, with the
+ * same image.  Calls on different streams take it in turn. */
 PC_API void pc_plan_destroy(pc_plan* plan);
 PC_API pc_status pc_plan_get_info(const pc_plan* plan, pc_plan_info* info);
 

@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <cstdint>
 #include <cstdio>
+#include <mutex>
 #include <stdexcept>
 #include <string>
 #include <vector>
@@ -171,8 +172,9 @@ __host__ __device__ inline double n_minus_one(double l, double m) {
 // the band the kernel is designed for at upsampling 2.
 struct WStack {
   int nplanes = 0;  // 0: coplanar plan
-  // Planes worked on together, each with its own band, pass-A buffer and
-  // partial tiles: a plane's kernels alone leave most of the device idle.
+  // Planes worked on together at most, each with its own band, pass-A buffer
+  // and partial tiles (see WPlanes): a plane's kernels alone leave most of the
+  // device idle.
   int together = 1;
   double w0 = 0, dw = 0;
   double cmid = 0;
@@ -265,7 +267,8 @@ struct pc_plan {
   void* vis_scratch = nullptr;  // complex [L] in plan order (residual etc.)
   unsigned long long* key_host = nullptr;  // pinned slot that maxkey_read reads back into
   pc::WStack ws;                // w-stacking planes (nplanes 0: coplanar)
-  void* wvals = nullptr;        // complex [together][L]: the planes' weighted visibilities
+  void* wvals = nullptr;        // complex [L]: a plane's weighted visibilities
+  bool w_shared = false;        // counted among the users of the device's plane workspace
   double* wquad = nullptr;      // [2 nquad] doubles: Psi's Chebyshev series (kPsiCheb terms)
   void* atom_scratch = nullptr; // per-atom staging
   size_t atom_capacity = 0;
@@ -317,6 +320,30 @@ size_t pool_trim(int device);
 unsigned long long* pinned_slot();
 void pinned_slot_release(unsigned long long* slot);
 void pinned_slots_trim();
+// The plane buffers of one w-stacked adjoint.  A plan owns those of a single
+// plane; groups of planes work in one workspace per device that its
+// non-coplanar plans share (at most kWGroupBytes, held while such a plan lives
+// and parked in the pool afterwards, given up first where an allocation would
+// otherwise fail).  Construction takes the workspace for the calling thread,
+// orders the stream after its last use and points the plan's buffers into it;
+// destruction records the use and puts the plan's own back.  A stream in
+// capture (a graph may be replayed at any time), and a device without room for
+// the workspace, get the plan's own plane: the same image bit for bit, as at
+// any group size.
+constexpr size_t kWGroupBytes = size_t(512) << 20;
+struct WPlanes {
+  int planes = 1;
+  WPlanes(pc_plan* plan, hipStream_t stream);
+  ~WPlanes();
+  WPlanes(const WPlanes&) = delete;
+  WPlanes& operator=(const WPlanes&) = delete;
+
+ private:
+  pc_plan* p;
+  hipStream_t s;
+  void *grid, *H, *partials, *wvals;  // the plan's own
+  std::unique_lock<std::mutex> lock;  // held: the workspace is in use
+};
 // Work of a plan's entry points is followed by an event on the call's stream
 // (one per stream the plan has seen); destroying the plan waits for these
 // events only.

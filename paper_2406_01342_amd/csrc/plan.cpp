@@ -36,8 +36,8 @@ size_t pool_class(size_t bytes) {
 
 size_t pool_trim(int device);
 
-void* pool_alloc(int device, size_t bytes, size_t* got) {
-  const size_t cls = pool_class(bytes);
+// A buffer of size class cls from the pool or the device, NULL if there is none.
+static void* pool_try(int device, size_t cls) {
   if (device >= 0 && device < kPoolDevices) {
     DevicePool& P = g_pool[device];
     std::lock_guard<std::mutex> lk(P.mu);
@@ -46,7 +46,6 @@ void* pool_alloc(int device, size_t bytes, size_t* got) {
         void* ptr = it->ptr;
         P.held -= cls;
         P.free.erase(it);
-        *got = cls;
         return ptr;
       }
   }
@@ -57,10 +56,18 @@ void* pool_alloc(int device, size_t bytes, size_t* got) {
     (void)hipGetLastError();
     if (pool_trim(device) > 0) e = hipMalloc(&ptr, cls);
   }
-  if (e != hipSuccess) {
-    (void)hipGetLastError();
-    fail(PC_ERR_OUT_OF_MEMORY, "hipMalloc of " + std::to_string(cls) + " bytes failed");
-  }
+  if (e == hipSuccess) return ptr;
+  (void)hipGetLastError();
+  return nullptr;
+}
+
+static bool w_shared_drop(int device);
+
+void* pool_alloc(int device, size_t bytes, size_t* got) {
+  const size_t cls = pool_class(bytes);
+  void* ptr = pool_try(device, cls);
+  if (!ptr && w_shared_drop(device)) ptr = pool_try(device, cls);
+  if (!ptr) fail(PC_ERR_OUT_OF_MEMORY, "hipMalloc of " + std::to_string(cls) + " bytes failed");
   *got = cls;
   return ptr;
 }
@@ -139,6 +146,124 @@ void pinned_slots_trim() {
   for (void* p : pages) (void)hipHostFree(p);
 }
 
+// The workspace of the w-planes worked on together, one per device.
+namespace {
+struct WShared {
+  std::mutex mu;
+  void* ptr = nullptr;
+  size_t bytes = 0;  // the size class
+  int users = 0;     // plans that work in it
+  hipEvent_t done = nullptr;
+  bool used = false;  // `done` has been recorded
+};
+WShared g_w_shared[kPoolDevices];
+
+// Offsets of the buffers of `planes` planes within one block.
+struct WBlock {
+  size_t grid, H, partials, wvals, bytes;
+};
+WBlock w_block(const GridGeom& g, int64_t L, int64_t n_partials, int planes) {
+  auto al = [](size_t b) { return (b + 255) / 256 * 256; };
+  const size_t k = 8 * (size_t)planes;
+  WBlock b{};
+  b.H = al(k * g.nu * g.nv);
+  b.partials = b.H + al(k * g.nv * g.n);
+  b.wvals = b.partials + al(k * n_partials * kTile * kTile);
+  b.bytes = b.wvals + al(k * L);
+  return b;
+}
+}  // namespace
+
+// Gives the workspace back to the device, for an allocation that failed
+// (waits for its last use).  False if there is none, or another thread has it.
+static bool w_shared_drop(int device) {
+  if (device < 0 || device >= kPoolDevices) return false;
+  WShared& S = g_w_shared[device];
+  std::unique_lock<std::mutex> lk(S.mu, std::try_to_lock);
+  if (!lk.owns_lock() || !S.ptr) return false;
+  if (S.used) (void)hipEventSynchronize(S.done);
+  (void)hipFree(S.ptr);
+  S.ptr = nullptr;
+  S.bytes = 0;
+  return true;
+}
+
+// Counts the plan among the workspace's users and makes it large enough for
+// the plan's group; where the device has no room it stays as it is.
+static void w_shared_join(pc_plan* p) {
+  if (p->ws.together < 2 || p->device < 0 || p->device >= kPoolDevices) return;
+  const size_t cls = pool_class(w_block(p->g, p->L, p->n_partials, p->ws.together).bytes);
+  WShared& S = g_w_shared[p->device];
+  std::lock_guard<std::mutex> lk(S.mu);
+  if (!S.done) PC_HIP(hipEventCreateWithFlags(&S.done, hipEventDisableTiming));
+  ++S.users;
+  p->w_shared = true;
+  if (S.bytes >= cls) return;
+  void* ptr = pool_try(p->device, cls);
+  if (!ptr) return;
+  if (S.ptr) {
+    if (S.used) (void)hipEventSynchronize(S.done);
+    pool_release(p->device, S.ptr, S.bytes);
+  }
+  S.ptr = ptr;
+  S.bytes = cls;
+}
+
+static void w_shared_leave(pc_plan* p) {
+  if (!p->w_shared) return;
+  p->w_shared = false;
+  WShared& S = g_w_shared[p->device];
+  std::lock_guard<std::mutex> lk(S.mu);
+  if (--S.users > 0) return;
+  if (S.used) (void)hipEventSynchronize(S.done);
+  (void)hipEventDestroy(S.done);
+  S.done = nullptr;
+  S.used = false;
+  pool_release(p->device, S.ptr, S.bytes);
+  S.ptr = nullptr;
+  S.bytes = 0;
+}
+
+WPlanes::WPlanes(pc_plan* plan, hipStream_t stream)
+    : p(plan), s(stream), grid(p->grid), H(p->H), partials(p->partials), wvals(p->wvals) {
+  if (!p->w_shared) return;
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+    (void)hipGetLastError();
+    return;
+  }
+  if (st != hipStreamCaptureStatusNone) return;
+  WShared& S = g_w_shared[p->device];
+  lock = std::unique_lock<std::mutex>(S.mu);
+  int k = p->ws.together;
+  while (k > 1 && w_block(p->g, p->L, p->n_partials, k).bytes > S.bytes) --k;
+  if (k < 2) {
+    lock.unlock();
+    return;
+  }
+  if (S.used) PC_HIP(hipStreamWaitEvent(s, S.done, 0));
+  const WBlock b = w_block(p->g, p->L, p->n_partials, k);
+  unsigned char* base = static_cast<unsigned char*>(S.ptr);
+  planes = k;
+  p->grid = base + b.grid;
+  p->H = base + b.H;
+  p->partials = base + b.partials;
+  p->wvals = base + b.wvals;
+}
+
+WPlanes::~WPlanes() {
+  if (!lock.owns_lock()) return;
+  WShared& S = g_w_shared[p->device];
+  if (hipEventRecord(S.done, s) == hipSuccess)
+    S.used = true;
+  else  // (no record to wait for later: wait here)
+    (void)hipStreamSynchronize(s);
+  p->grid = grid;
+  p->H = H;
+  p->partials = partials;
+  p->wvals = wvals;
+}
+
 void plan_touch(pc_plan* p, hipStream_t s) {
   for (auto& t : p->touched)
     if (t.first == s) {
@@ -170,6 +295,7 @@ void plan_release(pc_plan* p) {
   p->touched.clear();
   pinned_slot_release(p->key_host);
   p->key_host = nullptr;
+  w_shared_leave(p);
   for (auto& b : p->owned) pool_release(p->device, b.ptr, b.bytes);
   p->owned.clear();
   if (p->ev_a) (void)hipEventDestroy(p->ev_a);
@@ -746,16 +872,15 @@ static std::vector<double> correction_table(const GridGeom& g) {
 }
 
 // Planes of a w-stacked adjoint worked on together: at most eight (the
-// launches are full by then), in groups of even size, and no more than
-// kWGroupBytes of per-plane buffers.  One plane at a time the launches of a
-// 1024^2 plane end with most compute units idle: 17 planes take 999 us so and
-// 690 us in groups of 6, 6 and 5.
-constexpr size_t kWGroupBytes = size_t(512) << 20;
+// launches are full by then), in groups of even size, in a block of at most
+// kWGroupBytes.  One plane at a time the launches of a 1024^2 plane end with
+// most compute units idle: 17 planes take 999 us so and 690 us in groups of 6,
+// 6 and 5.
 static int planes_together(const Layout& lay) {
-  const GridGeom& g = lay.g;
-  const size_t each = 8 * ((size_t)g.nu * g.nv + (size_t)g.nv * g.n + (size_t)lay.L +
-                           (size_t)lay.n_partials * kTile * kTile);
-  const int most = (int)std::max<size_t>(1, std::min<size_t>(8, kWGroupBytes / each));
+  int most = 8;
+  while (most > 1 &&
+         pool_class(w_block(lay.g, lay.L, lay.n_partials, most).bytes) > kWGroupBytes)
+    --most;
   const int groups = (lay.ws.nplanes + most - 1) / most;
   return (lay.ws.nplanes + groups - 1) / groups;
 }
@@ -773,17 +898,16 @@ static size_t layout_bytes(const Layout& lay, int prec) {
   add(lay.fold.size() * sizeof(FoldItem));
   add(lay.tile_flags.size());
   add(lay.interp.size() * sizeof(InterpItem));
-  const size_t planes = (size_t)lay.ws.together;
-  add(planes * g.nu * g.nv * cb);            // grid band
-  add(planes * g.nv * g.n * cb);             // H
-  add(planes * lay.n_partials * kTile * kTile * cb);
+  add((size_t)g.nu * g.nv * cb);             // grid band
+  add((size_t)g.nv * g.n * cb);              // H
+  add((size_t)lay.n_partials * kTile * kTile * cb);
   add((size_t)twiddle_entries(g.M) * cb);    // twiddles
   add((size_t)g.n * rb);                     // correction
   add(256 + 8 * kMaxRowWords);               // max key, row mask and its row pairs
   add(lay.L * cb);                           // vis scratch
   if (lay.ws.nplanes > 0) {
     add(lay.L * 8);                          // w
-    add(planes * lay.L * cb);                // the planes' weighted visibilities
+    add(lay.L * cb);                         // one plane's weighted visibilities
     add((size_t)lay.ws.nquad * 16);          // Psi quadrature
   }
   return b;
@@ -848,25 +972,10 @@ extern "C" pc_status pc_plan_create_impl(const pc_geometry* geom, void* stream, 
       p->Cw = (double*)dalloc(p, L * 8);
       p->wquad = (double*)dalloc(p, (size_t)lay.ws.nquad * 16);
     }
-    // the buffers of the planes worked on together: of fewer planes where the
-    // device has no room for the group
-    for (const size_t mark = p->owned.size();;) {
-      const size_t planes = (size_t)lay.ws.together;
-      try {
-        p->grid = dalloc(p, planes * g.nu * g.nv * cb);
-        p->H = dalloc(p, planes * g.nv * g.n * cb);
-        p->partials = dalloc(p, planes * lay.n_partials * kTile * kTile * cb);
-        if (lay.ws.nplanes > 0) p->wvals = dalloc(p, planes * L * cb);
-        break;
-      } catch (const Error& e) {
-        if (e.status != PC_ERR_OUT_OF_MEMORY || planes == 1) throw;
-        for (; p->owned.size() > mark; p->owned.pop_back()) {
-          p->footprint -= p->owned.back().bytes;
-          pool_release(p->device, p->owned.back().ptr, p->owned.back().bytes);
-        }
-        lay.ws.together = (lay.ws.together + 1) / 2;
-      }
-    }
+    p->grid = dalloc(p, (size_t)g.nu * g.nv * cb);
+    p->H = dalloc(p, (size_t)g.nv * g.n * cb);
+    p->partials = dalloc(p, (size_t)lay.n_partials * kTile * kTile * cb);
+    if (lay.ws.nplanes > 0) p->wvals = dalloc(p, L * cb);
     p->ws = lay.ws;
 
     // Host staging of converted tables; copies complete before return.
@@ -964,6 +1073,7 @@ extern "C" pc_status pc_plan_create_impl(const pc_geometry* geom, void* stream, 
     }
     PC_HIP(hipEventCreate(&p->ev_a));
     PC_HIP(hipEventCreate(&p->ev_b));
+    w_shared_join(p);
     PC_HIP(hipStreamSynchronize(s));
   } catch (...) {
     plan_release(p);
