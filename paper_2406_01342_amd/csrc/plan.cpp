@@ -681,21 +681,36 @@ static Layout build_layout(const pc_geometry* geo, bool full) {
     // items of similar length; a heavier tile is cut into chunks of at most
     // G kq, each shared by the G waves of one workgroup (combine), which write
     // the tile itself when one chunk covers it and a partial tile otherwise.
-    // The longest item is then kq, the largest power of two that is no more
-    // than an even share of all the work per resident wave (16 per compute
-    // unit), so that no wave outlasts the launch: at most 1024, and at least
-    // 64 (32 on a band of few tiles), below which the partial tiles and their
-    // fold cost more than the shorter items give.  (Leaving tiles of up to 8 kq
-    // whole, to save partial tiles: 85 -> 137 us for 2,088,960 visibilities on an
-    // 8192^2 grid, whose longest items then end last.)
+    // The longest item is then kq.  Short items leave more partial tiles to
+    // fold, long ones end last: kq is at least 0.22 times the square root of the
+    // work (and 64, 32 on a band of few tiles), which is where 4,000 to 570,000
+    // visibilities are fastest (64^2, 60,001: 26.6 us at 64, 29.8 at 32, 30.9 at
+    // 256; LOFAR-like 1024^2: 50.9 at 192, 53.4 at 128, 56.0 at 512).  Larger
+    // work is shared out over the resident waves (16 per compute unit).  Where
+    // the mean tile takes several workgroups at any kq, items are made to fill
+    // whole rounds of them, as many as keep kq at 0.2 ... 0.35 times that root:
+    // 3,800,001 visibilities on 64^2 ... 512^2 take 140 ... 142 us in 1.2 rounds
+    // and 130 ... 134 in two.  Where most tiles are few items rounds mean little,
+    // and kq is the largest power of two within an even share (4096^2,
+    // 3,900,001: 188 us, 193 by rounds); 1024 at the most.
+    // (Leaving tiles of up to 8 kq whole, to save partial tiles: 85 -> 137 us for
+    // 2,088,960 visibilities on an 8192^2 grid, whose longest items then end
+    // last.)
     constexpr int G = kSpreadQuad;
     int64_t events = 0, occupied = 0;
     for (int64_t t = 0; t < ntiles; ++t) {
       events += totals[t];
       occupied += totals[t] > 0;
     }
+    const double root = std::sqrt((double)events);
     int64_t kq = occupied < 256 ? 32 : 64;
-    while (kq < 1024 && 2 * kq * kSpreadWaves <= events) kq *= 2;
+    if (events >= 4 * 1024 * occupied) {
+      const double rounds = std::max(1.0, std::floor(root / 1024.0 + 0.4));
+      kq = std::max(kq, (int64_t)(1.03 * (double)events / (rounds * kSpreadWaves)));
+    } else {
+      while (2 * kq * kSpreadWaves <= events) kq *= 2;
+    }
+    kq = std::min<int64_t>(1024, (std::max(kq, (int64_t)(0.22 * root)) + 31) / 32 * 32);
     // wave w's share of [q0, q1) starts here: whole batches of 32 but the last
     auto share = [](int64_t q0, int64_t q1, int w) {
       const int64_t batches = (q1 - q0 + 31) / 32;
