@@ -95,14 +95,27 @@ constexpr int kSpreadWaves = 4096;  // its waves resident on the device (LDS: 16
 
 // Interpolation work item: the plan-order visibilities [beg, end) whose first
 // cells lie in `tile` (a tile's own visibilities, in chunks of at most
-// kInterpChunk).
+// interp_chunk()).
 struct InterpItem {
   int32_t tile;
   int32_t beg;
   int32_t end;
   int32_t pad;
 };
-constexpr int kInterpChunk = 2048;
+// A workgroup of 256 threads takes one item and copies its tile once, so long
+// items amortise the copy and short ones fill the device: one visibility per
+// thread up to 262,144 visibilities, about 1024 items' worth each beyond, up to
+// 2048 where a thousand tiles make items enough and 1024 elsewhere.  Measured
+// over 256 ... 2048 (forward of an image): 60,001 on 64^2 ... 512^2, 16.6 ... 20.2
+// us at 256 and 22.5 ... 24.6 at 2048; 424,800 on 1024^2, 39.6 at 512 and 43.6;
+// 1,000,001 on 64^2 ... 512^2, 30 ... 33 at 1024, 31 ... 34.4 at 2048 and 32 ... 36
+// at 256; 3,800,001 there, 67.8 ... 72 at 1024 and 71.7 ... 74.8; 2,088,960 on
+// 4096^2, 102.7 at 2048 and 103.9 at 1024.
+constexpr int64_t interp_chunk(int64_t L, int64_t tiles) {
+  const int64_t most = tiles >= 1024 ? 2048 : 1024;
+  const int64_t c = 256 * ((L + (int64_t(1) << 18) - 1) >> 18);
+  return c < most ? c : most;
+}
 
 // A split ("hot") tile: its partial tiles occupy slots [first, first+count).
 struct FoldItem {

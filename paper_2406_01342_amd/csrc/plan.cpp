@@ -668,13 +668,15 @@ static Layout build_layout(const pc_geometry* geo, bool full) {
       // Tiles no footprint reaches get no work item and are never written;
       // the first FFT pass reads them as zeros from the occupancy flags.
       lay.tile_flags[t] = totals[t] > 0 ? 1 : 0;
-      // interpolation: the tile's own visibilities (first cell inside it)
-      for (int64_t q = bstart[t * 4]; q < bstart[t * 4 + 4]; q += kInterpChunk)
-        lay.interp.push_back(InterpItem{(int32_t)t, (int32_t)q,
-                                        (int32_t)std::min<int64_t>(q + kInterpChunk,
-                                                                   bstart[t * 4 + 4]),
-                                        0});
     }
+  // Interpolation: the tile's own visibilities (first cell inside it).
+  int64_t own_tiles = 0;
+  for (int64_t t = 0; t < ntiles; ++t) own_tiles += bstart[t * 4 + 4] > bstart[t * 4];
+  const int64_t chunk = interp_chunk(L, own_tiles);
+  for (int64_t t = 0; t < ntiles; ++t)
+    for (int64_t q = bstart[t * 4]; q < bstart[t * 4 + 4]; q += chunk)
+      lay.interp.push_back(InterpItem{(int32_t)t, (int32_t)q,
+                                      (int32_t)std::min<int64_t>(q + chunk, bstart[t * 4 + 4]), 0});
   if (lay.quads) {
     // Grouped spread: workgroups of G = kSpreadQuad waves.  A tile with at
     // most kq visibilities is one wave's item, packed G to a workgroup with
