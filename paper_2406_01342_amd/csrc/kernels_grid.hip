@@ -1135,6 +1135,17 @@ __device__ __forceinline__ void passB_adj_w_body(const GridGeom& g, const cpx<R>
   }
 }
 
+// Pass-B workgroups whose transforms (of `total` elements) have few radix-16
+// butterflies: their pixels go through LDS, one per thread and step.  From a
+// butterfly's registers a few lanes would handle 16 pixels each of both rows,
+// one after the other, and that chain is what such a launch waits for.
+// Adjoint at fine grids 128, 256 and 512: 6.5, 6.9 and 7.2 -> 5.5, 5.6 and 6.3
+// us; forward at 128 and 256: 4.9 and 6.4 -> 4.1 and 4.5 (8.0 -> 4.8 with cold
+// caches), and no faster at 512.
+constexpr bool few_butterflies(bool adjoint, int total) {
+  return total / 16 < (adjoint ? 64 : 32);
+}
+
 // Pass B of the adjoint (coplanar plans): NB pairs of image rows; FFT along v
 // of each pair's completed column; correction; both image rows written; fused
 // max |eta| (max(eta, 0) with ``positive``, the positivity-constrained solve)
@@ -1281,13 +1292,24 @@ __device__ __forceinline__ void passB_adj_body(const GridGeom& g, const cpx<R>* 
       best = key > best ? key : best;
     }
   };
+  auto finish = [&](auto ns) {
+    if constexpr (few_butterflies(true, NB * M)) {
+      fft_stages<R, M, NB, NT, +1, ns>(buf, tws);  // ends with a barrier
+      for (int e = (int)threadIdx.x; e < NB * n; e += NT) {
+        const int bb = e / n, f = (e - bb * n - n / 2) & (M - 1);
+        store(bb, f, buf[pidx(bb * M + f)]);
+      }
+    } else {
+      lds_fft_store<R, M, NB, NT, +1, ns>(buf, tws, keep, store);
+    }
+  };
   if constexpr (RAD0 <= 4) {
     if (pruned)
-      lds_fft_store<R, M, NB, NT, +1, RAD0>(buf, tws, keep, store);
+      finish(std::integral_constant<int, RAD0>{});
     else
-      lds_fft_store<R, M, NB, NT, +1>(buf, tws, keep, store);
+      finish(std::integral_constant<int, 1>{});
   } else {
-    lds_fft_store<R, M, NB, NT, +1>(buf, tws, keep, store);
+    finish(std::integral_constant<int, 1>{});
   }
   // block max
   for (int o = 32; o > 0; o >>= 1) {
@@ -1682,9 +1704,8 @@ __device__ __forceinline__ void passB_fwd_body(const GridGeom& g, const R* __res
   // with a row mask, workgroups of zero rows write nothing (pass A reads
   // those columns of H as zeros), and the rows cleared are not read
   if (rows && !any_row_set<2 * NB>(rows, i0)) return;
-  load_twiddles<R, M, NT>(tws, tw);
   const R dl = (R)g.dl;
-  central_first_stage<R, M, NB, NT, -1>(buf, [&](int b, int j) -> cpx<R> {
+  auto pixel = [&](int b, int j) -> cpx<R> {
     R x[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -1700,9 +1721,20 @@ __device__ __forceinline__ void passB_fwd_body(const GridGeom& g, const R* __res
                                          : R(0);
     }
     return {x[0], x[1]};
-  });
-  __syncthreads();
-  fft_stages<R, M, NB, NT, -1, first_radix(M)>(buf, tws);  // ends with a barrier
+  };
+  if constexpr (few_butterflies(false, NB * M)) {
+    for (int e = (int)threadIdx.x; e < NB * M; e += NT) {
+      const int b = e / M, m = e - b * M, j = (m + n / 2) & (M - 1);  // (0 <= j < n: a pixel)
+      buf[pidx(e)] = j < n ? pixel(b, j) : cpx<R>{R(0), R(0)};
+    }
+    load_twiddles<R, M, NT>(tws, tw);  // ends with a barrier
+    fft_stages<R, M, NB, NT, -1, 1>(buf, tws);  // the same
+  } else {
+    load_twiddles<R, M, NT>(tws, tw);
+    central_first_stage<R, M, NB, NT, -1>(buf, pixel);
+    __syncthreads();
+    fft_stages<R, M, NB, NT, -1, first_radix(M)>(buf, tws);  // ends with a barrier
+  }
   constexpr int KHB = khb_for<M>();
   const int v0 = g.v0, nv = g.nv;
   for (int e = (int)threadIdx.x; e < NB * nv; e += NT) {
