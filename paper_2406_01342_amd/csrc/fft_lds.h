@@ -121,6 +121,16 @@ __host__ __device__ __forceinline__ void bfly_tw(cpx<R>& a, cpx<R>& b, cpx<R> t)
   a = p;
 }
 
+// u^2 for u of modulus one up to rounding, as (1 - 2 y^2, 2 x y).  The product
+// u u would double the modulus' error with each squaring; here the cosine comes
+// from the sine, which for the angles of a stage's own twiddles (up to 1/16
+// turn) is the more accurate of the two.
+template <typename R>
+__host__ __device__ __forceinline__ cpx<R> unit_square(cpx<R> u) {
+  const R t = u.y + u.y;
+  return {fmar(-t, u.y, R(1)), t * u.x};
+}
+
 // Twiddled DFT of length N (a power of two) in registers:
 // x[f] <- sum_r x[r] (u exp(SIGN 2 pi i f / N))^r, the input twiddles u^r of a
 // Stockham stage folded into the transform.  Splitting r into even and odd
@@ -138,7 +148,7 @@ __host__ __device__ __forceinline__ void dft_tw(cpx<R>* x, cpx<R> u) {
       o[i] = x[2 * i + 1];
     }
     if constexpr (N > 2) {
-      const cpx<R> u2 = cmul(u, u);
+      const cpx<R> u2 = unit_square(u);
       dft_tw<R, N / 2, SIGN>(e, u2);
       dft_tw<R, N / 2, SIGN>(o, u2);
     }
