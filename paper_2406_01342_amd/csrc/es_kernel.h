@@ -5,6 +5,8 @@
 #ifndef PC_ES_KERNEL_H
 #define PC_ES_KERNEL_H
 
+#include <cmath>
+
 #include "common.h"
 
 namespace pc {
@@ -13,8 +15,9 @@ namespace pc {
 // c = beta log2(e): the peak is exactly one at every width.  (Two constants,
 // c0 and c1 = c0 / R for sqrt(R^2 - x^2), put a factor of up to 1 +- 1e-6 on
 // all weights, and a root in [R/2, R] rounds up to twice as coarsely as one in
-// [1/2, 1]: 4.9e-7 relative L2 error at W = 6 against 2.7e-7 so, 7.7e-7 against
-// 4.1e-7 at W = 9.)  max(., 0) absorbs rounding at |z| = 1.
+// [1/2, 1].)  Relative L2 error of the weights on the device: 2.9e-7, 3.5e-7 and
+// 4.3e-7 at W = 6, 7 and 9, with two constants 7.3e-7, 4.4e-7 and 1.0e-6.
+// max(., 0) absorbs rounding at |z| = 1.
 __host__ __device__ __forceinline__ float es_from_q(float q, float c) {
   q = q > 0.0f ? q : 0.0f;
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -43,6 +46,17 @@ __host__ __device__ __forceinline__ float es_tap(float s, int t) {
     q = __builtin_fmaf(-(x * (float)(4.0 / (W * W))), x, 1.0f);
   }
   return es_from_q(q, es_c(W));
+}
+
+// The kernel that the device's FP32 weights are in the mean, in FP64: c as
+// rounded, and the hardware square root, which is low by 7.3e-9 in the mean
+// over the weights (a factor of -1.1e-7 on all of them per axis at W = 7, which
+// taking the root's residual into account would cost the spread 4 %).  The
+// correction tables of FP32 plans are this kernel's transform.
+constexpr double kRootLow = 7.3e-9;
+inline double es_device(double z, int W) {
+  const double q = 1.0 - z * z;
+  return std::exp2((double)es_c(W) * (std::sqrt(q > 0.0 ? q : 0.0) * (1.0 - kRootLow) - 1.0));
 }
 
 }  // namespace pc

@@ -14,6 +14,7 @@
 #include <numeric>
 
 #include "common.h"
+#include "es_kernel.h"
 
 namespace pc {
 
@@ -869,9 +870,14 @@ static void gauss_legendre(int q, std::vector<double>& x, std::vector<double>& w
   }
 }
 
+// phi as the plan's precision evaluates it.
+static double kernel_value(const GridGeom& g, double z, bool f64) {
+  return f64 ? std::exp(g.beta64 * (std::sqrt(1.0 - z * z) - 1.0)) : es_device(z, g.W);
+}
+
 // psi(a) = (W/2) int_{-1}^{1} phi(z) cos(pi a W z / M) dz, the Fourier
 // transform of the spreading kernel at output frequency a; corr = (-1)^a/psi.
-static std::vector<double> correction_table(const GridGeom& g) {
+static std::vector<double> correction_table(const GridGeom& g, bool f64) {
   std::vector<double> x, w;
   gauss_legendre(2 * g.W + 120, x, w);
   std::vector<double> c(g.n);
@@ -879,8 +885,7 @@ static std::vector<double> correction_table(const GridGeom& g) {
     const int a = i - g.n / 2;
     double s = 0;
     for (size_t q = 0; q < x.size(); ++q) {
-      const double phi = std::exp(g.beta64 * (std::sqrt(1.0 - x[q] * x[q]) - 1.0));
-      s += w[q] * phi * std::cos(M_PI * a * g.W * x[q] / g.M);
+      s += w[q] * kernel_value(g, x[q], f64) * std::cos(M_PI * a * g.W * x[q] / g.M);
     }
     const double psi = 0.5 * g.W * s;
     c[i] = ((a & 1) ? -1.0 : 1.0) / psi;
@@ -1037,9 +1042,8 @@ extern "C" pc_status pc_plan_create_impl(const pc_geometry* geom, void* stream, 
       gauss_legendre(2 * lay.ws.nquad, x, w);
       for (size_t q = 0; q < x.size(); ++q) {
         if (x[q] <= 0) continue;
-        const double phi = std::exp(g.beta64 * (std::sqrt(1.0 - x[q] * x[q]) - 1.0));
         wq.push_back(x[q]);
-        wq.push_back(g.W * w[q] * phi);
+        wq.push_back(g.W * w[q] * kernel_value(g, x[q], f64));
       }
       PC_REQUIRE((int)wq.size() == 2 * lay.ws.nquad, "quadrature nodes");
       // the device evaluates Psi on xi in [-1/4, 1/4] (the range of
@@ -1075,7 +1079,7 @@ extern "C" pc_status pc_plan_create_impl(const pc_geometry* geom, void* stream, 
       PC_HIP(hipMemcpyAsync(p->wquad, cheb.data(), K * 8, hipMemcpyHostToDevice, s));
       PC_HIP(hipStreamSynchronize(s));  // (cheb is a local)
     }
-    std::vector<double> corr64 = correction_table(g);
+    std::vector<double> corr64 = correction_table(g, f64);
     std::vector<float> tw32, corr32;
     if (f64) {
       PC_HIP(hipMemcpyAsync(p->twiddle, tw64.data(), ntw * 16, hipMemcpyHostToDevice, s));
