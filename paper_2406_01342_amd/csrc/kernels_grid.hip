@@ -47,15 +47,8 @@ __device__ __forceinline__ double es_kernel(double z, double beta) {
   return t > 0.0 ? exp(beta * (sqrt(t) - 1.0)) : 0.0;
 }
 
-// Tap position relative to an output tile's origin; returns false if the tap
-// falls outside the tile.  In periodic (wrap) mode base is in (-W, M - W].
-__device__ __forceinline__ bool tap_local(int base, int t, int M, int wrap, int& out) {
-  int x = base + t;
-  if (wrap && x < 0) x += M;
-  out = x;
-  return (unsigned)x < (unsigned)kTile;
-}
-
+// A cell relative to an output tile's origin, in (-W, M - W] in periodic (wrap)
+// mode.
 __device__ __forceinline__ int tile_base(int c, int origin, int M, int W, int wrap) {
   int b = c - origin;  // in (-M, M): both are cells of the periodic grid
   if (wrap) {
@@ -101,10 +94,10 @@ __device__ __forceinline__ int block_key(int bu, int bv) { return ((bv + 64) << 
 constexpr int kNoBlock = -1;
 
 // Adds a run's per-cell register sums into the LDS tile and clears them.
-// single_u, single_v: the periodic grid is one tile wide along that axis, so
-// window cells left of (above) the tile wrap onto its other end.
+// single_u: the periodic grid is one tile wide along u, so window cells left of
+// the tile wrap onto its other end (FP64 plans are coplanar: no wrap along v).
 template <typename R, int W>
-__device__ __forceinline__ void spread_flush(int lane, int key, bool single_u, bool single_v,
+__device__ __forceinline__ void spread_flush(int lane, int key, bool single_u,
                                              R (&accr)[SpreadCfg<R, W>::NPASS],
                                              R (&acci)[SpreadCfg<R, W>::NPASS], R* tre,
                                              R* tim) {
@@ -115,8 +108,8 @@ __device__ __forceinline__ void spread_flush(int lane, int key, bool single_u, b
     for (int ps = 0; ps < C::NPASS; ++ps) {
       const int tap = lane + 64 * ps;
       const int a = tap / C::BS, b = tap - (tap / C::BS) * C::BS;
-      int y = bv + a, x = bu + b;
-      if (single_v) y &= kTile - 1;
+      const int y = bv + a;
+      int x = bu + b;
       if (single_u) x &= kTile - 1;
       if ((C::BS * C::BS % 64 == 0 || tap < C::BS * C::BS) && (unsigned)y < (unsigned)kTile &&
           (unsigned)x < (unsigned)kTile) {
@@ -180,7 +173,7 @@ __device__ __forceinline__ void spread_body(
   R* stg = tim + C::TILE;  // [64][REC]
   const int tv = ch.tile / g.ntu, tu = ch.tile - tv * g.ntu;
   const int ov = g.v0 + tv * kTile, ou = g.u0 + tu * kTile;
-  const bool single_u = g.wrap && g.M == kTile, single_v = g.wrapv && g.M == kTile;
+  const bool single_u = g.wrap && g.M == kTile;
   const R inv = R(2) / R(W);
   const R beta = g.beta64;
   // cumulative range boundaries
@@ -222,7 +215,7 @@ __device__ __forceinline__ void spread_body(
       const int cu = cell_u(nx.cell), cv = cell_v(nx.cell);
       const int du = cu % C::RB, dv = cv % C::RB;
       const int bu = tile_base(cu - du, ou, g.M, C::BS, g.wrap);
-      const int bv = tile_base(cv - dv, ov, g.M, C::BS, g.wrapv);
+      const int bv = cv - dv - ov;
       // the W taps of each axis land at window positions d .. d + W - 1
       // (d = dv or du < RB); the other BS - W positions are zero
 #pragma unroll
@@ -262,7 +255,7 @@ __device__ __forceinline__ void spread_body(
         if (v0 + u < nb) {
           const int k = __builtin_amdgcn_readfirstlane(key[u]);
           if (k != ckey) {  // same for every lane of the wave
-            spread_flush<R, W>(lane, ckey, single_u, single_v, accr, acci, tre, tim);
+            spread_flush<R, W>(lane, ckey, single_u, accr, acci, tre, tim);
             ckey = k;
           }
 #pragma unroll
@@ -277,7 +270,7 @@ __device__ __forceinline__ void spread_body(
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
-  spread_flush<R, W>(lane, ckey, single_u, single_v, accr, acci, tre, tim);
+  spread_flush<R, W>(lane, ckey, single_u, accr, acci, tre, tim);
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -1918,6 +1911,7 @@ __global__ __launch_bounds__(kRegT, 4) void passA_fwd_reg_kernel(
 }
 
 // Interpolation: V_k = sum of w x w taps of the fine grid (type-2 gather).
+// Coplanar plans only, whose band never wraps along v.
 template <typename R, int W>
 __global__ __launch_bounds__(256) void interp_kernel(GridGeom g, int64_t L,
                                                      const uint32_t* __restrict__ cell,
@@ -1941,8 +1935,7 @@ __global__ __launch_bounds__(256) void interp_kernel(GridGeom g, int64_t L,
 #pragma unroll 2
   for (int a = 0; a < W; ++a) {
     const R kva = es_kernel((sv + R(a)) * inv, beta);
-    int y = cv + a - g.v0;
-    if (g.wrapv && y >= g.M) y -= g.M;
+    const int y = cv + a - g.v0;
     R rx = 0, ry = 0;
 #pragma unroll
     for (int b = 0; b < W; ++b) {
@@ -2000,9 +1993,9 @@ __global__ __launch_bounds__(kInterpThreads) void interp_lds_kernel(GridGeom g,
   const int rv0 = tv * kTile, ru0 = tu * kTile;  // region origin in the band
   for (int e = tid; e < C::S * C::S; e += kInterpThreads) {
     const int y = e / C::S, x = e - y * C::S;
-    int rv = rv0 + y, ru = ru0 + x;
+    const int rv = rv0 + y;
+    int ru = ru0 + x;
     float2 v = make_float2(0.f, 0.f);
-    if (g.wrapv && rv >= g.M) rv -= g.M;
     if (g.wrap && ru >= g.M) ru -= g.M;
     if (rv < g.nv && ru < g.nu) {
       const c32 c = grid[(size_t)rv * g.nu + ru];
