@@ -316,8 +316,8 @@ __device__ __forceinline__ void lds_fft_store(cpx<R>* buf, const cpx<R>* tw, Kee
 // LDS exchanges per residue replace the four of a padded length-M transform.
 // Slots at or above M / 2 (r < 8) carry w^(4096 S/2 s), those below
 // w^(4096 (S/2 - 1) s): quarter or half turns known at compile time.
-// 35 KB of LDS and 256 threads: four workgroups per compute unit, whose
-// barriers are independent.
+// 36 to 39 KB of LDS with the twiddles and flags, and 256 threads: four
+// workgroups per compute unit (160 KB), whose barriers are independent.
 constexpr int kRegN = 4096, kRegT = 256;
 constexpr int kRegBuf = 4352;  // exchange buffer (elements): 256 x 17 and 16 x 272
 

@@ -1108,7 +1108,8 @@ __device__ __forceinline__ void passB_adj_w_plane(const GridGeom& g, const cpx<R
 // Pass B of w-planes: NB image rows i; for each plane in order, FFT along v of
 // H[:, i] (the whole plane: the rotation makes the transform's outputs
 // complex), correction, rotation by the plane's phase, and the real part added
-// into the image rows (by the same thread each time).
+// into the image rows in memory (each pixel read and written per plane, by the
+// same thread each time).
 template <typename R, int M, int NB, int NT>
 __device__ __forceinline__ void passB_adj_w_body(const GridGeom& g, const cpx<R>* __restrict__ H,
                                                  R* __restrict__ image,
@@ -1962,9 +1963,9 @@ __global__ __launch_bounds__(256) void interp_kernel(GridGeom g, int64_t L,
 // interp_kernel.  With base (plan-order output), the output is base - Phi x:
 // the residual, in the same FP32 subtraction a separate pass would do.  base is
 // in plan order, or with base_perm in caller order: the gather is a load per
-// visibility issued ahead of its taps and hides behind them (as a pass of its
-// own it was bound by its random 64-byte sectors, 145 us for 8,372,224
-// visibilities).  With stats as well, each work item also writes its sums of
+// visibility issued ahead of its taps.  It is bound by its random 64-byte
+// sectors all the same: 8,372,224 visibilities take 75 us without it and 189
+// with it, 35 less than with a pass of its own.  With stats as well, each work item also writes its sums of
 // |r|^2 and Re(conj(base) r) in FP64 to stats[2 item], [2 item + 1] (threads
 // combined in a fixed order).
 constexpr int kInterpThreads = 256;
@@ -2357,7 +2358,8 @@ static void run_passes_adj(pc_plan* p, R* image, R scale, hipStream_t s,
       const size_t ldw = (size_t)padded(NBW * M) * CB;
       set_lds((const void*)passB_adj_w_kernel<R, M, NBW, NTW>, ldw);
       ProfScope ps(p, s, "passB_adj_w",
-                   wp->count * nvn + (double)g.n * g.n * sizeof(R) * (wp->first ? 1 : 2),
+                   wp->count * nvn +
+                       (double)g.n * g.n * sizeof(R) * (2 * wp->count - (wp->first ? 1 : 0)),
                    wp->count * (double)g.n * M);
       hipLaunchKernelGGL((passB_adj_w_kernel<R, M, NBW, NTW>), dim3((M / 2) / NBW), dim3(NTW),
                          ldw, s, g, (const cpx<R>*)p->H, image, (const cpx<R>*)p->twiddle,

@@ -450,7 +450,9 @@ static Layout build_layout(const pc_geometry* geo, bool full) {
   g.dl = dl;
   lay.L = L;
 
-  // Per-visibility phase rates and first cells (unwrapped, in [-W/2, M)).
+  // Per-visibility phase rates and first cells, unwrapped: in [-W/2, M] along
+  // both axes (a coplanar plan's v cells from M/2 - W/2 on, and kept so; the
+  // others are wrapped into the band below).
   std::vector<double> A(L), B(L);
   std::vector<int32_t> c0u(L), c0v(L);
   std::vector<double> su(L), sv(L);

@@ -449,15 +449,19 @@ struct Pfw {
   }
 
   // Crossover between the direct sums and the gridded operators (restricted
-  // to the image rows that hold atoms), per direction, from rates measured on
-  // gfx950: the direct sums about 0.45 ps per visibility-atom pair; the
-  // gridded operators about 28 ps per visibility (spread or interpolation),
-  // 3.4 ps per fine-grid point of the band rows' transforms and 2.7 ps per
-  // fine-grid point of the image rows' transforms (at most one row per
-  // atom), plus 15 us of launches.  (The register-held passes have since
-  // fallen to about 1.5 ps per point of the band rows at 16384^2, and the half
-  // plane to half the rows: near the line the direct sums, exact up to their
-  // sines, are kept, and the Gram form serves sets that small before either.)
+  // to the image rows that hold atoms), per direction, by a model of both: the
+  // direct sums 0.45 ps per visibility-atom pair; the gridded operators 28 ps per
+  // visibility (spread or interpolation), 3.4 ps per fine-grid point of the band
+  // rows' transforms and 2.7 ps per fine-grid point of the image rows'
+  // transforms (at most one row per atom), plus 15 us of launches.  These are the
+  // rates of the full-length transforms; today's gridded operators are faster,
+  // and the line lies above where a pair of operators costs the same: at 186,
+  // 127 and 96 atoms on the LOFAR-like, the 4096^2 and the 8192^2 workload
+  // (424,800, 2,088,960 and 8,372,224 visibilities).  Measured there, direct
+  // against gridded: 63 us at 128 atoms and 77 at 160 against 70; 154 at 65 and
+  // 191 at 128 against 160; 351 at 64, 551 at 65 (the one-pass kernel ends) and
+  // 632 at 100 against 402.  Between the two the direct sums, exact up to their
+  // sines, are kept at up to 1.5 times the cost.
   int64_t grid_crossover() const {
     if (p->Cw) return INT64_MAX / 8;  // no gridded forward with the w-term: direct sums only
     if (prm.grid_atoms > 0) return prm.grid_atoms;

@@ -103,3 +103,18 @@ def test_w_adjoint_at_large_fine_grids(n, reach):
     say("w at", n, reach, plan.info, err)
     assert err <= 1e-4
     assert mx == np.abs(img).max() and am == int(np.abs(img).argmax())
+
+
+def test_bytes_counted_for_the_rotating_pass():
+    """Pass B of the w-planes reads each plane's pass-A buffer once, writes the
+    image for the first plane and reads and writes it for every other."""
+    a = api()
+    n = 128
+    plan, h, *_ = _plan(n, 3001, 4, 4000.0)
+    info = plan.info
+    a.pc_plan_profile(plan, True)
+    a.pc_adjoint_grid(plan, h)
+    stat = next(s for s in a.pc_plan_kernel_stats(plan) if s["name"] == "passB_adj_w")
+    planes = info["w_planes"]
+    assert planes > 8  # more than one group
+    assert stat["bytes"] == planes * 8.0 * info["band_nv"] * n + 4.0 * n * n * (2 * planes - 1)
