@@ -61,17 +61,38 @@ static void set_device(const pc_plan* p) { PC_HIP(hipSetDevice(p->device)); }
 
 // Marks the end of an entry point's work on its stream (plan_touch) when the
 // entry point returns, so that pc_plan_destroy can wait for it alone.
+// adjoint_last: no work follows the call's adjoint unless it is waited for, so
+// that the record a w-stacked one makes is enough.
 struct Touch {
   pc_plan* p;
   hipStream_t s;
-  Touch(pc_plan* plan, void* stream) : p(plan), s((hipStream_t)stream) {}
+  bool adjoint_last;
+  Touch(pc_plan* plan, void* stream, bool last = false)
+      : p(plan), s((hipStream_t)stream), adjoint_last(last) {
+    p->touch_recorded = p->w_eager = false;
+  }
   ~Touch() {
+    if (adjoint_last && p->touch_recorded) return;
     try {
       plan_touch(p, s);
     } catch (...) {
     }
   }
 };
+
+// The gridded adjoint, then its maximum where one is asked for.
+static void adjoint_and_max(pc_plan* p, const c32* vis, bool vis_sorted, float* image, float scale,
+                            hipStream_t s, double* max_abs, int64_t* argmax) {
+  if (!max_abs && !argmax) {
+    adjoint_grid<float>(p, vis, vis_sorted, image, scale, s);
+    return;
+  }
+  std::unique_ptr<WPlanes> group;  // held until the stream has been waited for
+  if (p->w_shared) group.reset(new WPlanes(p, s));
+  adjoint_grid<float>(p, vis, vis_sorted, image, scale, s);
+  maxkey_read(p, s, max_abs, argmax);
+  if (group) group->waited();
+}
 
 // Launch tables of pc_adjoint_grid_batch, per device (calls are serialised).
 constexpr int kMaxDevices = 64;
@@ -146,10 +167,8 @@ pc_status pc_adjoint_grid(pc_plan* p, const void* vis, float* image, double* max
     check_plan(p, PC_PREC_FP32);
     PC_REQUIRE(vis != nullptr && image != nullptr, "vis and image must not be NULL");
     set_device(p);
-    Touch touch(p, stream);
-    hipStream_t s = (hipStream_t)stream;
-    adjoint_grid<float>(p, (const c32*)vis, false, image, 1.0f, s);
-    if (max_abs || argmax) maxkey_read(p, s, max_abs, argmax);
+    Touch touch(p, stream, true);
+    adjoint_and_max(p, (const c32*)vis, false, image, 1.0f, (hipStream_t)stream, max_abs, argmax);
     return PC_OK;
   });
 }
@@ -416,13 +435,12 @@ pc_status pc_dual_certificate(pc_plan* p, const void* vis, int64_t natoms, const
     PC_REQUIRE(vis != nullptr && cert != nullptr, "vis and cert must not be NULL");
     PC_REQUIRE(std::isfinite(lambda) && lambda > 0, "lambda must be finite and > 0");
     set_device(p);
-    Touch touch(p, stream);
+    Touch touch(p, stream, true);
     hipStream_t s = (hipStream_t)stream;
     c32* r = (c32*)p->vis_scratch;
     // residual in plan order: r = V - Phi x
     forward_sparse<float>(p, natoms, pix, weight, (const c32*)vis, false, r, true, s);
-    adjoint_grid<float>(p, r, true, cert, (float)(1.0 / lambda), s);
-    if (max_abs || argmax) maxkey_read(p, s, max_abs, argmax);
+    adjoint_and_max(p, r, true, cert, (float)(1.0 / lambda), s, max_abs, argmax);
     return PC_OK;
   });
 }

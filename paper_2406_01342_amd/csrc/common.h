@@ -242,6 +242,8 @@ struct Prof {
   std::vector<hipEvent_t> pool;
 };
 
+struct WPlanes;
+
 }  // namespace pc
 
 // The opaque plan.
@@ -282,6 +284,9 @@ struct pc_plan {
   pc::WStack ws;                // w-stacking planes (nplanes 0: coplanar)
   void* wvals = nullptr;        // complex [L]: a plane's weighted visibilities
   bool w_shared = false;        // counted among the users of the device's plane workspace
+  pc::WPlanes* w_group = nullptr;  // the plane buffers in use (during a call)
+  bool w_eager = false;         // the call's stream is known not to be in capture
+  bool touch_recorded = false;  // a w-stacked adjoint has recorded its call's plan_touch
   double* wquad = nullptr;      // [2 nquad] doubles: Psi's Chebyshev series (kPsiCheb terms)
   void* atom_scratch = nullptr; // per-atom staging
   size_t atom_capacity = 0;
@@ -339,10 +344,13 @@ void pinned_slots_trim();
 // and parked in the pool afterwards, given up first where an allocation would
 // otherwise fail).  Construction takes the workspace for the calling thread,
 // orders the stream after its last use and points the plan's buffers into it;
-// destruction records the use and puts the plan's own back.  A stream in
-// capture (a graph may be replayed at any time), and a device without room for
-// the workspace, get the plan's own plane: the same image bit for bit, as at
-// any group size.
+// destruction records the use by the plan's own event of the call (one more per
+// call took 5 us of 40 at 64^2) and puts the plan's own buffers back.  Where the
+// caller waits for the stream meanwhile, waited() says so and nothing is
+// recorded: an event ahead of the maximum's readback took 5 us of 70.  A stream
+// in capture (a graph may be replayed at any time), and a device without room
+// for the workspace, get the plan's own plane: the same image bit for bit, as
+// at any group size.
 constexpr size_t kWGroupBytes = size_t(512) << 20;
 struct WPlanes {
   int planes = 1;
@@ -350,17 +358,21 @@ struct WPlanes {
   ~WPlanes();
   WPlanes(const WPlanes&) = delete;
   WPlanes& operator=(const WPlanes&) = delete;
+  void waited() { complete = true; }
 
  private:
   pc_plan* p;
   hipStream_t s;
   void *grid, *H, *partials, *wvals;  // the plan's own
+  bool complete = false;
   std::unique_lock<std::mutex> lock;  // held: the workspace is in use
 };
 // Work of a plan's entry points is followed by an event on the call's stream
 // (one per stream the plan has seen); destroying the plan waits for these
 // events only.
-void plan_touch(pc_plan* p, hipStream_t s);
+// Returns the event; NULL, and none recorded, for a w-stacked plan on a stream
+// in capture.
+hipEvent_t plan_touch(pc_plan* p, hipStream_t s);
 void* dalloc(pc_plan* p, size_t bytes);
 void plan_release(pc_plan* p);
 void* ensure_atom_scratch(pc_plan* p, size_t bytes);

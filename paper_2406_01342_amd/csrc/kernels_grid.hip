@@ -2688,9 +2688,11 @@ static void adjoint_grid_w(pc_plan* p, const c32* vis, bool vis_sorted, float* i
   const WStack& ws = p->ws;
   const float R = 0.5f * (float)p->g.W;
   const unsigned nb = (unsigned)((p->L + 255) / 256);
-  const WPlanes group(p, s);
-  for (int j = 0; j < ws.nplanes; j += group.planes) {
-    const int count = std::min(group.planes, ws.nplanes - j);
+  std::unique_ptr<WPlanes> own;  // (unless the caller holds the buffers)
+  if (!p->w_group) own.reset(new WPlanes(p, s));
+  const int together = p->w_group->planes;
+  for (int j = 0; j < ws.nplanes; j += together) {
+    const int count = std::min(together, ws.nplanes - j);
     const WPlane wp{ws.w0 + j * ws.dw, ws.dw, ws.cmid, j == 0 ? 1 : 0, count, plane_stride(p).H};
     {
       ProfScope ps(p, s, "wplane", p->L * (16.0 + 8.0 * count), (double)p->L * count);

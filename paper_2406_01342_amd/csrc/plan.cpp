@@ -154,8 +154,10 @@ struct WShared {
   void* ptr = nullptr;
   size_t bytes = 0;  // the size class
   int users = 0;     // plans that work in it
+  // the plan that used it last and the event that followed (the plan's own, see
+  // plan_touch; NULL when that work is known to be complete)
+  const pc_plan* last = nullptr;
   hipEvent_t done = nullptr;
-  bool used = false;  // `done` has been recorded
 };
 WShared g_w_shared[kPoolDevices];
 
@@ -182,7 +184,7 @@ static bool w_shared_drop(int device) {
   WShared& S = g_w_shared[device];
   std::unique_lock<std::mutex> lk(S.mu, std::try_to_lock);
   if (!lk.owns_lock() || !S.ptr) return false;
-  if (S.used) (void)hipEventSynchronize(S.done);
+  if (S.done) (void)hipEventSynchronize(S.done);
   (void)hipFree(S.ptr);
   S.ptr = nullptr;
   S.bytes = 0;
@@ -196,53 +198,59 @@ static void w_shared_join(pc_plan* p) {
   const size_t cls = pool_class(w_block(p->g, p->L, p->n_partials, p->ws.together).bytes);
   WShared& S = g_w_shared[p->device];
   std::lock_guard<std::mutex> lk(S.mu);
-  if (!S.done) PC_HIP(hipEventCreateWithFlags(&S.done, hipEventDisableTiming));
   ++S.users;
   p->w_shared = true;
   if (S.bytes >= cls) return;
   void* ptr = pool_try(p->device, cls);
   if (!ptr) return;
   if (S.ptr) {
-    if (S.used) (void)hipEventSynchronize(S.done);
+    if (S.done) (void)hipEventSynchronize(S.done);
     pool_release(p->device, S.ptr, S.bytes);
   }
   S.ptr = ptr;
   S.bytes = cls;
 }
 
+// (The plan's work is complete, its events not yet destroyed.)
 static void w_shared_leave(pc_plan* p) {
   if (!p->w_shared) return;
   p->w_shared = false;
   WShared& S = g_w_shared[p->device];
   std::lock_guard<std::mutex> lk(S.mu);
+  if (S.last == p) {
+    S.last = nullptr;
+    S.done = nullptr;
+  }
   if (--S.users > 0) return;
-  if (S.used) (void)hipEventSynchronize(S.done);
-  (void)hipEventDestroy(S.done);
-  S.done = nullptr;
-  S.used = false;
   pool_release(p->device, S.ptr, S.bytes);
   S.ptr = nullptr;
   S.bytes = 0;
 }
 
+static bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &st) != hipSuccess) (void)hipGetLastError();
+  return st != hipStreamCaptureStatusNone;
+}
+
 WPlanes::WPlanes(pc_plan* plan, hipStream_t stream)
     : p(plan), s(stream), grid(p->grid), H(p->H), partials(p->partials), wvals(p->wvals) {
-  if (!p->w_shared) return;
-  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &st) != hipSuccess) {
-    (void)hipGetLastError();
+  if (!p->w_shared || capturing(s)) {
+    p->w_group = this;
     return;
   }
-  if (st != hipStreamCaptureStatusNone) return;
   WShared& S = g_w_shared[p->device];
+  p->w_eager = true;
   lock = std::unique_lock<std::mutex>(S.mu);
   int k = p->ws.together;
   while (k > 1 && w_block(p->g, p->L, p->n_partials, k).bytes > S.bytes) --k;
   if (k < 2) {
     lock.unlock();
+    p->w_group = this;
     return;
   }
-  if (S.used) PC_HIP(hipStreamWaitEvent(s, S.done, 0));
+  // (a plan's own calls are ordered by its caller, as for all its buffers)
+  if (S.done && S.last != p) PC_HIP(hipStreamWaitEvent(s, S.done, 0));
   const WBlock b = w_block(p->g, p->L, p->n_partials, k);
   unsigned char* base = static_cast<unsigned char*>(S.ptr);
   planes = k;
@@ -250,31 +258,42 @@ WPlanes::WPlanes(pc_plan* plan, hipStream_t stream)
   p->H = base + b.H;
   p->partials = base + b.partials;
   p->wvals = base + b.wvals;
+  p->w_group = this;
 }
 
 WPlanes::~WPlanes() {
+  p->w_group = nullptr;
   if (!lock.owns_lock()) return;
   WShared& S = g_w_shared[p->device];
-  if (hipEventRecord(S.done, s) == hipSuccess)
-    S.used = true;
-  else  // (no record to wait for later: wait here)
-    (void)hipStreamSynchronize(s);
+  S.last = nullptr;
+  S.done = nullptr;
+  if (!complete) try {
+      S.done = plan_touch(p, s);
+      S.last = p;
+      p->touch_recorded = true;
+    } catch (...) {  // no record to wait for later: wait here
+      (void)hipStreamSynchronize(s);
+    }
   p->grid = grid;
   p->H = H;
   p->partials = partials;
   p->wvals = wvals;
 }
 
-void plan_touch(pc_plan* p, hipStream_t s) {
+hipEvent_t plan_touch(pc_plan* p, hipStream_t s) {
+  // Not in a capture: another plan may wait for a w-stacked plan's event.  (The
+  // check takes a microsecond: none for other plans, nor after one in the call.)
+  if (p->w_shared && !p->w_eager && capturing(s)) return nullptr;
   for (auto& t : p->touched)
     if (t.first == s) {
       PC_HIP(hipEventRecord(t.second, s));
-      return;
+      return t.second;
     }
   hipEvent_t ev = nullptr;
   PC_HIP(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
   p->touched.push_back({s, ev});
   PC_HIP(hipEventRecord(ev, s));
+  return ev;
 }
 
 void* dalloc(pc_plan* p, size_t bytes) {
@@ -289,14 +308,12 @@ void* dalloc(pc_plan* p, size_t bytes) {
 void plan_release(pc_plan* p) {
   prof_release(p);
   // the plan's own work only (no device-wide wait)
-  for (auto& t : p->touched) {
-    (void)hipEventSynchronize(t.second);
-    (void)hipEventDestroy(t.second);
-  }
+  for (auto& t : p->touched) (void)hipEventSynchronize(t.second);
+  w_shared_leave(p);
+  for (auto& t : p->touched) (void)hipEventDestroy(t.second);
   p->touched.clear();
   pinned_slot_release(p->key_host);
   p->key_host = nullptr;
-  w_shared_leave(p);
   for (auto& b : p->owned) pool_release(p->device, b.ptr, b.bytes);
   p->owned.clear();
   if (p->ev_a) (void)hipEventDestroy(p->ev_a);

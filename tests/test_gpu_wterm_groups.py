@@ -118,3 +118,27 @@ def test_bytes_counted_for_the_rotating_pass():
     planes = info["w_planes"]
     assert planes > 8  # more than one group
     assert stat["bytes"] == planes * 8.0 * info["band_nv"] * n + 4.0 * n * n * (2 * planes - 1)
+
+
+def test_last_use_followed_from_plan_to_plan():
+    """Uses that end in an event and uses that the caller waited for (a maximum
+    asked for), of plans on streams of their own, one of them destroyed right
+    after its use: each image equals the one computed alone."""
+    a = api()
+    made = [_plan(64, 701, 11, 9000.0), _plan(256, 20001, 12, 4000.0), _plan(128, 3001, 13, 4000.0)]
+    alone = [a.pc_adjoint_grid(plan, h)[0].clone() for plan, h, *_ in made]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in made]
+    outs = []
+    for turn in range(6):
+        for k, (plan, h, *_) in enumerate(made):
+            with torch.cuda.stream(streams[k]):
+                outs.append((k, a.pc_adjoint_grid(plan, h, want_max=(turn + k) % 3 == 0)[0]))
+        if turn == 2:  # the plan that used the memory last
+            made.pop()[0].close()
+    for s in streams:
+        s.synchronize()
+    for k, img in outs:
+        assert torch.equal(img, alone[k])
+    for plan, *_ in made:
+        plan.close()
