@@ -168,8 +168,9 @@ PC_API pc_status pc_plan_get_info(const pc_plan* plan, pc_plan_info* info);
 
 /* Frees every buffer parked in the device pool of `device` (see
  * pc_plan_destroy), for callers that need the memory elsewhere (another
- * allocator in the process), and, when no plan holds one, the pinned host
- * words that maxima are read back into.  hipFree waits for the device.
+ * allocator in the process), the pinned host staging that solves keep (16 MiB
+ * at most) and, when no plan holds one, the pinned host words that maxima are
+ * read back into.  hipFree waits for the device.
  * *released (may be NULL) gets the device bytes freed.  Errors: PC_ERR_INVALID_ARG (device < 0),
  * PC_ERR_DEVICE. */
 PC_API pc_status pc_device_pool_trim(int32_t device, size_t* released);

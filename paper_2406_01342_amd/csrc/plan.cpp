@@ -147,6 +147,54 @@ void pinned_slots_trim() {
   for (void* p : pages) (void)hipHostFree(p);
 }
 
+namespace {
+std::mutex g_staging_mu;
+std::vector<DeviceBuf> g_staging;  // free ones (host memory)
+size_t g_staging_held = 0;
+}  // namespace
+
+void* staging_alloc(size_t bytes, size_t* got) {
+  size_t cls = 4096;
+  while (cls < bytes) cls *= 2;
+  *got = cls;
+  {
+    std::lock_guard<std::mutex> lk(g_staging_mu);
+    for (auto it = g_staging.begin(); it != g_staging.end(); ++it)
+      if (it->bytes == cls) {
+        void* ptr = it->ptr;
+        g_staging_held -= cls;
+        g_staging.erase(it);
+        return ptr;
+      }
+  }
+  void* ptr = nullptr;
+  PC_HIP(hipHostMalloc(&ptr, cls, hipHostMallocPortable));
+  return ptr;
+}
+
+void staging_release(void* ptr, size_t bytes) {
+  if (!ptr) return;
+  {
+    std::lock_guard<std::mutex> lk(g_staging_mu);
+    if (g_staging_held + bytes <= kStagingHeld) {
+      g_staging.push_back({ptr, bytes});
+      g_staging_held += bytes;
+      return;
+    }
+  }
+  (void)hipHostFree(ptr);
+}
+
+void staging_trim() {
+  std::vector<DeviceBuf> drop;
+  {
+    std::lock_guard<std::mutex> lk(g_staging_mu);
+    drop.swap(g_staging);
+    g_staging_held = 0;
+  }
+  for (auto& b : drop) (void)hipHostFree(b.ptr);
+}
+
 // The workspace of the w-planes worked on together, one per device.
 namespace {
 struct WShared {
@@ -962,6 +1010,7 @@ extern "C" pc_status pc_device_pool_trim_impl(int32_t device, size_t* released) 
   PC_REQUIRE(device >= 0, "device must be >= 0");
   const size_t n = pool_trim(device);
   pinned_slots_trim();
+  staging_trim();
   if (released) *released = n;
   return PC_OK;
 }

@@ -100,11 +100,10 @@ struct Pinned {
     armed = false;
     if (bytes > cap) {  // grow geometrically: pinning memory is slow
       const size_t want = std::max<size_t>(bytes, 2 * cap + 4096);
-      if (ptr) (void)hipHostFree(ptr);
+      staging_release(ptr, cap);  // (no copy from or to it is pending)
       ptr = nullptr;
       cap = 0;
-      PC_HIP(hipHostMalloc((void**)&ptr, want));
-      cap = want;
+      ptr = (unsigned char*)staging_alloc(want, &cap);
     }
     return ptr;
   }
@@ -118,7 +117,7 @@ struct Pinned {
       if (armed) (void)hipEventSynchronize(fence);
       (void)hipEventDestroy(fence);
     }
-    if (ptr) (void)hipHostFree(ptr);
+    staging_release(ptr, cap);
   }
 };
 
