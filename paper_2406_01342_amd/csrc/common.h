@@ -341,7 +341,7 @@ void pinned_slots_trim();
 // Pinned host staging, kept between uses up to kStagingHeld bytes (beyond that,
 // and by pc_device_pool_trim, it is freed); sizes are rounded up to a power of
 // two.  A solve takes three or four pieces of some kB: allocated and freed by
-// each solve they took 0.7 ms of its 1.7 (a 128^2 image, 50,400 visibilities),
+// each solve they took 0.7 ms of its 1.7 (512^2, 50,400 visibilities, five iterations),
 // or nearly nothing, as the runtime's own blocks happened to lie.
 // The releaser guarantees that no pending copy still uses the memory.
 constexpr size_t kStagingHeld = size_t(16) << 20;
